@@ -140,7 +140,7 @@ typedef struct {
                                      200, 216, 240, 250, 256):
                                      the two-pass schedule.  The x2 transform is split four-step
                                      style (N = N1 N2); a slab pass holds N1 rows of one x1 plane
-                                     (of two at N = 128, 160 and 256, whose rows the state holds
+                                     (of two with some tiles, whose rows the state holds
                                      interleaved between the passes of a chunk)
                                      and does the x3 transforms around the potential factor and
                                      the stride-N2 part of x2, a pencil pass holds N2 consecutive
@@ -149,15 +149,15 @@ typedef struct {
                                      passes over the state per step instead of four (schedule
                                      autotuning; ignored with QFDTD_F_AB_SCHEME). */
 /* Flag bits 7-8: the split-x2 variant (schedule autotuning), read as QFDTD_SPLIT_VARIANT(flags):
- *   0: the size's default x2 = N1 x N2 with pencil tiles of 4 x3 columns (2 where 4 does not
- *      divide N);
- *   1 (QFDTD_F_SPLIT_NARROW): the same factors, pencil tiles of 2 columns (half the on-chip
- *      memory per tile, so two tiles share a compute unit);
+ *   0: the size's default factors x2 = N1 x N2 with its fastest tiles;
+ *   1 (QFDTD_F_SPLIT_NARROW): the same factors with other tiles (mostly pencil tiles of fewer
+ *      columns, so that two tiles share a compute unit);
  *   2 (QFDTD_F_SPLIT_WIDE), N = 128 and 256: 8 consecutive rows per pencil tile and 8 columns
  *      (row pieces twice as long as with 4 columns);
  *   3 (QFDTD_F_SPLIT_SWAPPED): the default factors swapped, x2 = N2 x N1 (fewer rows per slab
  *      tile, more per pencil tile), at the sizes where they differ.
- * A variant a size does not have runs the schedule the other flags select. */
+ * Tiles do not change results, factors do (FP32 rounding).  A variant a size does not have runs
+ * the schedule the other flags select. */
 #define QFDTD_F_SPLIT_NARROW 128u
 #define QFDTD_F_SPLIT_WIDE 256u
 #define QFDTD_F_SPLIT_SWAPPED 384u

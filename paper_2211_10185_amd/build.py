@@ -17,8 +17,11 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 OUT = os.path.join(HERE, "libqfdtd.so")
 # (source, object name, extra flags): the transform passes are instantiated
-# per lattice size in five groups so that they compile in parallel
-SOURCES = [("fft_inst.hip", "fft_inst%d" % g, ["-DQF_GROUP=%d" % g]) for g in range(5)] + [
+# per lattice size in groups (the split-x2 passes in groups of their own) so
+# that they compile in parallel, the longest first
+SOURCES = [("fft_inst.hip", "fft_inst%d" % g, ["-DQF_GROUP=%d" % g]) for g in (1, 4, 2, 3)] + [
+    ("split_inst.hip", "split_inst%d" % g, ["-DQF_SPLIT_PART=%d" % g]) for g in range(8)] + [
+    ("fft_inst.hip", "fft_inst0", ["-DQF_GROUP=0"]),
     ("aux_kernels.hip", "aux_kernels", []), ("qfdtd_api.hip", "qfdtd_api", []),
     ("potential_io.cpp", "potential_io", [])]
 # The DFT-stage measurement tool (VALU butterfly against MFMA), a library of its own

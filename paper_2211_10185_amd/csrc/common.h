@@ -118,13 +118,13 @@ __host__ __device__ inline int red_blocks(size_t n) {
 // Kinetic kinds (eqs. HK0..HK3)
 enum { KIN_FDTD = 0, KIN_P2 = 1, KIN_SIN2 = 2, KIN_REL = 3 };
 
-// Mode bits of a real-space (plane or row) pass and of a column pass.
+// Mode bits of a real-space (plane, row or slab) pass and of a column or pencil pass.
 enum : uint32_t {
-  M_PRE = 1u,    // x h before the forward transform (chunk start)
+  M_PRE = 1u,    // x h before the forward transform (chunk start); pencil pass: x2 is transformed already
   M_INV = 2u,    // inverse transform first
   M_MID = 4u,    // x h^2 between inverse and forward (steady state)
   M_FWD = 8u,    // forward transform
-  M_POST = 16u,  // x h after the inverse transform (chunk end)
+  M_POST = 16u,  // x h after the inverse transform (chunk end); pencil pass: leave x2 transformed
   M_KIN = 32u,   // column pass: x e^{-dt T(k)}/N^3 between forward and inverse
   M_AXIS1 = 64u, // column pass along x1 (else x2)
   M_SWAP = 128u, // stencil: read alt, write psi (else read psi, write alt)
@@ -132,6 +132,8 @@ enum : uint32_t {
   // A/B update of the FFT kinetic terms (the legacy iteration with H_K^(1..3)):
   M_COMB = 512u,  // real-space pass: input dt H_K psi (transformed) from alt; after the inverse,
                   // psi' = A psi - B (dt H_K psi) with psi read from and psi' written to psi
+  M_SPLIT = 2048u, // plane pass at the edge of a split-x2 chunk: the transformed side is in the
+                  // split order of x2 (row k1 + N1 k2 of the plane at row N2 k1 + k2)
   M_ALT = 1024u   // transforms work on alt: column passes read/write alt, a real-space pass
                   // without M_COMB reads psi and writes its forward transform to alt
 };
@@ -211,6 +213,20 @@ __device__ __forceinline__ int find_entry(const LaunchList &L, int blk) {
   return lo;
 }
 
+// Kernels of one split-x2 variant (x2 = n1 x N/n1, plane groups of xi, pencil tiles of pencil_tt x3
+// columns); pencil is null where the variant does not exist, and a slab entry where the variant has
+// no use for that kind.  plane_edges: chunks start and end with plane passes (M_SPLIT) instead of
+// slab passes.
+enum { SLAB_REAL = 0, SLAB_COMPLEX = 1, SLAB_EDGE = 2, SLAB_AB = 3, SLAB_KINDS = 4 };
+constexpr int SPLIT_VARIANTS = 5;
+struct SplitKernels {
+  const void *slab[SLAB_KINDS];
+  const void *pencil;
+  size_t slab_lds, pencil_lds;
+  int slab_nt, pencil_nt, n1, xi, pencil_tt;
+  bool plane_edges;
+};
+
 // Transform-pass kernels instantiated for one lattice size (index 0: complex64,
 // 1: complex128); plane entries are null where an N^2 plane does not fit LDS.
 struct FftKernels {
@@ -219,14 +235,7 @@ struct FftKernels {
   const void *col[2];
   size_t plane_lds[2], row_lds[2], col_lds[2];
   int plane_nt;
-  // split-x2 two-pass schedule (slab and pencil passes, complex64), where instantiated, by
-  // variant (x2 = N1 x N2 and the pencil tile width)
-  const void *slab[4], *slab_edge[4];   // steady pass; chunk-edge and plain-transform passes
-  size_t slab_lds[4];
-  int slab_nt[4], split_n1[4], split_xi[4];
-  const void *pencil[4];
-  size_t pencil_lds[4];
-  int pencil_nt[4], pencil_tt[4];
+  SplitKernels split[2][SPLIT_VARIANTS];   // two-pass split-x2 schedule: precision, variant
 };
 
 // Multi-size transform-pass kernels of one size group (see fft_inst.hip).

@@ -424,22 +424,51 @@ template <int NL, int P> struct ColsGeo {
 // lanes stride through it and collide on LDS banks).  Tables of the radix
 // plan come first, then those of the reversed plan.
 
-template <typename T, int N, bool REV> __host__ __device__ constexpr RPlan plan_of() {
-  RPlan p = make_rplan(N, sizeof(T) == 8);
+// A plan kind PK names the radix plan of N: 0 and 1 are make_rplan's plans for complex64 and
+// complex128; rp(s0, s1, ...) spells the stages out, each a radix or st(ra, rb): the two radices ra and
+// rb in turn with both butterflies in registers.  A fused stage does the operations of its two
+// stages (same twiddles, same order), so it gives their bits without the LDS exchange between them.
+template <typename T> constexpr int PKT = sizeof(T) == 8 ? 1 : 0;
+__host__ __device__ constexpr int st(int ra, int rb) { return ra | rb << 5; }
+__host__ __device__ constexpr int rp(int s0, int s1, int s2 = 0) { return s0 | s1 << 10 | s2 << 20; }
+
+struct PStage { int ra, rb, first; };        // rb = 1: a plain stage; first: its first radix in the plan
+struct PPlan { int n; PStage s[8]; };
+template <int PK, int N, bool REV> __host__ __device__ constexpr PPlan stages_of() {
+  PPlan p{0, {}};
+  if (PK < 2) {
+    const RPlan q = make_rplan(N, PK == 1);
+    for (int i = 0; i < q.n; ++i) p.s[p.n++] = {q.r[i], 1, 0};
+  } else {
+    for (int k = PK; k > 0; k >>= 10) p.s[p.n++] = {k & 31, (k >> 5 & 31) ? (k >> 5 & 31) : 1, 0};
+  }
   if (REV) {
-    RPlan q = p;
-    for (int i = 0; i < p.n; ++i) q.r[i] = p.r[p.n - 1 - i];
-    return q;
+    const PPlan q = p;
+    for (int i = 0; i < p.n; ++i) {
+      const PStage &x = q.s[p.n - 1 - i];
+      p.s[i] = x.rb > 1 ? PStage{x.rb, x.ra, 0} : x;
+    }
+  }
+  for (int i = 1; i < p.n; ++i) p.s[i].first = p.s[i - 1].first + (p.s[i - 1].rb > 1 ? 2 : 1);
+  return p;
+}
+// the same plan, one radix after the other
+template <int PK, int N, bool REV> __host__ __device__ constexpr RPlan plan_of() {
+  const PPlan q = stages_of<PK, N, REV>();
+  RPlan p{0, {0, 0, 0, 0, 0, 0, 0, 0}};
+  for (int i = 0; i < q.n; ++i) {
+    p.r[p.n++] = q.s[i].ra;
+    if (q.s[i].rb > 1) p.r[p.n++] = q.s[i].rb;
   }
   return p;
 }
-template <typename T, int N, bool REV, int S> __host__ __device__ constexpr int ns_before() {
+template <int PK, int N, bool REV, int S> __host__ __device__ constexpr int ns_before() {
   int ns = 1;
-  for (int i = 0; i < S; ++i) ns *= plan_of<T, N, REV>().r[i];
+  for (int i = 0; i < S; ++i) ns *= plan_of<PK, N, REV>().r[i];
   return ns;
 }
-template <typename T, int N, bool REV> __host__ __device__ constexpr int tw_plan_size() {
-  constexpr RPlan p = plan_of<T, N, REV>();
+template <int PK, int N, bool REV> __host__ __device__ constexpr int tw_plan_size() {
+  constexpr RPlan p = plan_of<PK, N, REV>();
   int sz = 0, ns = 1;
   for (int i = 0; i < p.n; ++i) {
     if (ns > 1) sz += (p.r[i] - 1) * ns;
@@ -447,10 +476,13 @@ template <typename T, int N, bool REV> __host__ __device__ constexpr int tw_plan
   }
   return sz;
 }
-template <typename T, int N> __host__ __device__ constexpr int tw_total() { return tw_plan_size<T, N, false>() + tw_plan_size<T, N, true>(); }
-template <typename T, int N, bool REV, int S> __host__ __device__ constexpr int tw_off() {
-  constexpr RPlan p = plan_of<T, N, REV>();
-  int off = REV ? tw_plan_size<T, N, false>() : 0, ns = 1;
+template <int PK, int N> __host__ __device__ constexpr int tw_total() {
+  static_assert(ns_before<PK, N, false, plan_of<PK, N, false>().n>() == N, "the radices multiply to N");
+  return tw_plan_size<PK, N, false>() + tw_plan_size<PK, N, true>();
+}
+template <int PK, int N, bool REV, int S> __host__ __device__ constexpr int tw_off() {
+  constexpr RPlan p = plan_of<PK, N, REV>();
+  int off = REV ? tw_plan_size<PK, N, false>() : 0, ns = 1;
   for (int i = 0; i < S; ++i) {
     if (ns > 1) off += (p.r[i] - 1) * ns;
     ns *= p.r[i];
@@ -458,96 +490,32 @@ template <typename T, int N, bool REV, int S> __host__ __device__ constexpr int 
   return off;
 }
 
-template <typename T, int N, bool REV, int NT, int S>
+template <typename T, int PK, int N, bool REV, int NT, int S>
 __device__ __forceinline__ void fill_tw_plan(C<T> *lt, const C<T> *gtw) {
-  constexpr RPlan p = plan_of<T, N, REV>();
+  constexpr RPlan p = plan_of<PK, N, REV>();
   if constexpr (S < p.n) {
     constexpr int R = p.r[S];
-    constexpr int NS = ns_before<T, N, REV, S>();
+    constexpr int NS = ns_before<PK, N, REV, S>();
     if constexpr (NS > 1) {
-      constexpr int off = tw_off<T, N, REV, S>();
+      constexpr int off = tw_off<PK, N, REV, S>();
       constexpr int twstep = N / (NS * R);
       for (int i = threadIdx.x; i < (R - 1) * NS; i += NT) {
         const int r = i / NS + 1, kk = i - (r - 1) * NS;
         lt[off + i] = gtw[r * kk * twstep];
       }
     }
-    fill_tw_plan<T, N, REV, NT, S + 1>(lt, gtw);
+    fill_tw_plan<T, PK, N, REV, NT, S + 1>(lt, gtw);
   }
 }
 
 // stage twiddle tables of both plans from the roots of unity w^m, m < N (global)
-template <typename T, int N, int NT>
+template <typename T, int PK, int N, int NT>
 __device__ __forceinline__ void fill_twiddles(C<T> *lt, const C<T> *gtw) {
-  fill_tw_plan<T, N, false, NT, 0>(lt, gtw);
-  fill_tw_plan<T, N, true, NT, 0>(lt, gtw);
+  fill_tw_plan<T, PK, N, false, NT, 0>(lt, gtw);
+  fill_tw_plan<T, PK, N, true, NT, 0>(lt, gtw);
 }
 
 // ----------------------------------------------------------------- stages
-
-template <typename T, int N, int R, int NS, bool INV, class G, int NT, int TWOFF>
-__device__ __forceinline__ void tstage(C<T> *buf, const C<T> *tw) {
-  constexpr int NR = N / R;
-  constexpr int total = G::nlines * NR;
-  constexpr int CAPQ = (total + NT - 1) / NT;
-  const int tid = threadIdx.x;
-  C<T> v[CAPQ][R];
-  int jq[CAPQ], bq[CAPQ];
-#pragma unroll
-  for (int q = 0; q < CAPQ; ++q) {
-    const int f = tid + q * NT;
-    if (total % NT == 0 || f < total) {
-      int j, b;
-      if constexpr (G::linefast) { b = f % G::nlines; j = f / G::nlines; }
-      else { j = f % NR; b = f / NR; }
-      jq[q] = j;
-      bq[q] = b;
-      const int kk = j % NS;
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        C<T> x = buf[G::at(b, j + r * NR)];
-        if constexpr (NS > 1) {
-          if (r > 0) {
-            C<T> w = tw[TWOFF + (r - 1) * NS + kk];
-            if (INV) w.y = -w.y;
-            x = cmul(x, w);
-          }
-        }
-        v[q][r] = x;
-      }
-      Dft<R, INV, C<T>>::run(v[q]);
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < CAPQ; ++q) {
-    if (total % NT == 0 || tid + q * NT < total) {
-      const int j = jq[q], b = bq[q];
-      const int kk = j % NS;
-      const int base = (j - kk) * R + kk;
-#pragma unroll
-      for (int r = 0; r < R; ++r) buf[G::at(b, base + r * NS)] = v[q][r];
-    }
-  }
-  __syncthreads();
-}
-
-template <typename T, int N, bool INV, class G, int NT, int S, int NS>
-__device__ __forceinline__ void run_stages(C<T> *buf, const C<T> *tw) {
-  constexpr RPlan P = make_rplan(N, sizeof(T) == 8);
-  if constexpr (S < P.n) {
-    constexpr int R = P.r[S];
-    tstage<T, N, R, NS, INV, G, NT, tw_off<T, N, false, S>()>(buf, tw);
-    run_stages<T, N, INV, G, NT, S + 1, NS * R>(buf, tw);
-  }
-}
-
-template <typename T, int N, bool INV, class G, int NT>
-__device__ __forceinline__ void fft_lines_t(C<T> *buf, const C<T> *tw) {
-  run_stages<T, N, INV, G, NT, 0, 1>(buf, tw);
-}
-
-// ------------------------------------------- stages with explicit data paths
 //
 // The steady-state passes fuse the first and last radix stages with global
 // memory (inputs loaded straight into registers, outputs stored straight from
@@ -612,19 +580,106 @@ __device__ __forceinline__ void st_write(C<T> (&v)[CQ][R], Dst dst) {
   }
 }
 
-// stages [S0, S1) of plan (N, REV), LDS -> LDS
-template <typename T, int N, bool REV, bool INV, class G, int NT, int S0, int S1>
+// Two stages in registers: radix RA with NS, then radix RB with NS RA, on the RA RB inputs
+// v[r] = x[j + r N/(RA RB)] of index j (kk = j mod NS).  The first stage's butterflies are
+// j + rb N/(RA RB) (inputs r = rb + RB ra), their outputs ra feed the second stage's butterfly ra, and its
+// output rb is element ra + RA rb of the result, written like that of one stage of radix RA RB.
+template <typename T, int RA, int RB, int NS, bool INV, int OFFA, int OFFB>
+__device__ __forceinline__ void fused_dft(C<T> *v, const C<T> *tw, int kk) {
+  C<T> y[RA][RB];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    C<T> t[RA];
+#pragma unroll
+    for (int ra = 0; ra < RA; ++ra) {
+      t[ra] = v[rb + RB * ra];
+      if constexpr (NS > 1) {
+        if (ra > 0) {
+          C<T> w = tw[OFFA + (ra - 1) * NS + kk];
+          if (INV) w.y = -w.y;
+          t[ra] = cmul(t[ra], w);
+        }
+      }
+    }
+    Dft<RA, INV, C<T>>::run(t);
+#pragma unroll
+    for (int ra = 0; ra < RA; ++ra) y[ra][rb] = t[ra];
+  }
+#pragma unroll
+  for (int ra = 0; ra < RA; ++ra) {
+#pragma unroll
+    for (int rb = 1; rb < RB; ++rb) {
+      C<T> w = tw[OFFB + (rb - 1) * NS * RA + ra * NS + kk];
+      if (INV) w.y = -w.y;
+      y[ra][rb] = cmul(y[ra][rb], w);
+    }
+    Dft<RB, INV, C<T>>::run(y[ra]);
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) v[ra + RA * rb] = y[ra][rb];
+  }
+}
+
+// Stage S of plan (PK, N, REV): its radix (of both parts), NS and table offsets.
+template <int PK, int N, bool REV, int S> struct StageOf {
+  static constexpr PStage P = stages_of<PK, N, REV>().s[S];
+  static constexpr int R = P.ra * P.rb;
+  static constexpr int NS = ns_before<PK, N, REV, P.first>();
+  static constexpr int OFFA = tw_off<PK, N, REV, P.first>();
+  static constexpr int OFFB = tw_off<PK, N, REV, P.first + (P.rb > 1 ? 1 : 0)>();
+};
+// inputs of the stage from src(b, n) and its butterflies
+template <typename T, int PK, int N, bool REV, int S, bool INV, class G, int NT, int CQ, int R, class Src>
+__device__ __forceinline__ void stage_read(C<T> (&v)[CQ][R], const C<T> *tw, Src src) {
+  using SO = StageOf<PK, N, REV, S>;
+  static_assert(R == SO::R, "the stage's inputs");
+  if constexpr (SO::P.rb == 1) {
+    st_read<T, N, SO::R, SO::NS, INV, G, NT, SO::OFFA>(v, tw, src);
+  } else {
+    using Q = SG<G, N, SO::R, NT>;
+#pragma unroll
+    for (int q = 0; q < Q::CAPQ; ++q) {
+      if (Q::active(q)) {
+        int j, b;
+        Q::jb(q, j, b);
+#pragma unroll
+        for (int r = 0; r < SO::R; ++r) v[q][r] = src(b, j + r * Q::NR);
+        fused_dft<T, SO::P.ra, SO::P.rb, SO::NS, INV, SO::OFFA, SO::OFFB>(v[q], tw, j % SO::NS);
+      }
+    }
+  }
+}
+// the plan's first stage on inputs that are already in registers
+template <typename T, int PK, int N, bool REV, bool INV>
+__device__ __forceinline__ void stage_first(C<T> *v, const C<T> *tw) {
+  using SO = StageOf<PK, N, REV, 0>;
+  if constexpr (SO::P.rb == 1) Dft<SO::R, INV, C<T>>::run(v);
+  else fused_dft<T, SO::P.ra, SO::P.rb, 1, INV, SO::OFFA, SO::OFFB>(v, tw, 0);
+}
+template <typename T, int PK, int N, bool REV, int S, class G, int NT, int CQ, int R, class Dst>
+__device__ __forceinline__ void stage_write(C<T> (&v)[CQ][R], Dst dst) {
+  using SO = StageOf<PK, N, REV, S>;
+  static_assert(R == SO::R, "the stage's outputs");
+  st_write<T, N, SO::R, SO::NS, G, NT>(v, dst);
+}
+
+// stages [S0, S1) of plan (PK, N, REV), LDS -> LDS
+template <typename T, int PK, int N, bool REV, bool INV, class G, int NT, int S0, int S1>
 __device__ __forceinline__ void lds_stages(C<T> *buf, const C<T> *tw) {
   if constexpr (S0 < S1) {
-    constexpr int R = plan_of<T, N, REV>().r[S0];
-    constexpr int NS = ns_before<T, N, REV, S0>();
+    constexpr int R = StageOf<PK, N, REV, S0>::R;
     C<T> v[SG<G, N, R, NT>::CAPQ][R];
-    st_read<T, N, R, NS, INV, G, NT, tw_off<T, N, REV, S0>()>(v, tw, [&](int b, int n) { return buf[G::at(b, n)]; });
+    stage_read<T, PK, N, REV, S0, INV, G, NT>(v, tw, [&](int b, int n) { return buf[G::at(b, n)]; });
     __syncthreads();
-    st_write<T, N, R, NS, G, NT>(v, [&](int b, int n, C<T> x) { buf[G::at(b, n)] = x; });
+    stage_write<T, PK, N, REV, S0, G, NT>(v, [&](int b, int n, C<T> x) { buf[G::at(b, n)] = x; });
     __syncthreads();
-    lds_stages<T, N, REV, INV, G, NT, S0 + 1, S1>(buf, tw);
+    lds_stages<T, PK, N, REV, INV, G, NT, S0 + 1, S1>(buf, tw);
   }
+}
+
+// a whole transform of the lines in LDS (every stage of the plan)
+template <typename T, int PK, int N, bool INV, class G, int NT>
+__device__ __forceinline__ void fft_lines_t(C<T> *buf, const C<T> *tw) {
+  lds_stages<T, PK, N, false, INV, G, NT, 0, stages_of<PK, N, false>().n>(buf, tw);
 }
 
 }  // namespace qf

@@ -30,6 +30,14 @@ void register_fft_group1(FftKernels *t, GroupKernels *g);
 void register_fft_group2(FftKernels *t, GroupKernels *g);
 void register_fft_group3(FftKernels *t, GroupKernels *g);
 void register_fft_group4(FftKernels *t, GroupKernels *g);
+void register_split_part0(FftKernels *t);
+void register_split_part1(FftKernels *t);
+void register_split_part2(FftKernels *t);
+void register_split_part3(FftKernels *t);
+void register_split_part4(FftKernels *t);
+void register_split_part5(FftKernels *t);
+void register_split_part6(FftKernels *t);
+void register_split_part7(FftKernels *t);
 void launch_tables(bool dbl, void *tw, double2 *tw64, double *ksym64, int N, int kin, double a, double m, hipStream_t st);
 void launch_potential(double *v64, int vcomplex, int N, double a, int kind, const double *p, const double *knots, int nk,
                       const double2 *add, hipStream_t st);
@@ -110,6 +118,14 @@ hipError_t fft_table_init() {
   register_fft_group2(g_fft, &g_grp[2]);
   register_fft_group3(g_fft, &g_grp[3]);
   register_fft_group4(g_fft, &g_grp[4]);
+  register_split_part0(g_fft);
+  register_split_part1(g_fft);
+  register_split_part2(g_fft);
+  register_split_part3(g_fft);
+  register_split_part4(g_fft);
+  register_split_part5(g_fft);
+  register_split_part6(g_fft);
+  register_split_part7(g_fft);
   for (int n = 8; n <= 256; ++n)
     for (int w = 0; w < 2; ++w) {
       const int gi = size_group(n);
@@ -138,15 +154,18 @@ hipError_t fft_table_init() {
         }
     }
   for (int n = 0; n <= 256; ++n)
-    for (int v = 0; v < 4; ++v) {
-      const void *fs[3] = {g_fft[n].slab[v], g_fft[n].slab_edge[v], g_fft[n].pencil[v]};
-      const size_t ls[3] = {g_fft[n].slab_lds[v], g_fft[n].slab_lds[v], g_fft[n].pencil_lds[v]};
-      for (int q = 0; q < 3; ++q)
-        if (fs[q]) {
-          hipError_t e = hipFuncSetAttribute(fs[q], hipFuncAttributeMaxDynamicSharedMemorySize, (int)ls[q]);
+    for (int w = 0; w < 2; ++w)
+      for (int v = 0; v < SPLIT_VARIANTS; ++v) {
+        const SplitKernels &k = g_fft[n].split[w][v];
+        if (!k.pencil) continue;
+        hipError_t e = hipFuncSetAttribute(k.pencil, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.pencil_lds);
+        if (e != hipSuccess) return e;
+        for (const void *f : k.slab) {
+          if (!f) continue;
+          e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.slab_lds);
           if (e != hipSuccess) return e;
         }
-    }
+      }
   done = true;
   return hipSuccess;
 }
@@ -189,16 +208,6 @@ int col_tiles(int N, int k, bool dbl) {
   const int tc = col_tile(dbl);
   return k * N * ((N + tc - 1) / tc);
 }
-// split-x2 schedule: slab tiles (group of split_xi x1 planes, fast x2 digit; a tile carries every
-// state), pencil tiles (state, slow x2 frequency, x3 column block)
-int slab_tiles(int N, int v) { return N / g_fft[N].split_xi[v] * (N / g_fft[N].split_n1[v]); }
-// At small N the slab tiles are few (N * N2, each taking all k states in turn), so up to this size
-// each state gets tiles of its own (aux 1), which reread the factor rows from cache.  Measured at
-// k = 3 on one stream: 42.7 -> 35.5 us per step at 96, 48.1 -> 45.4 at 108, but 60.0 -> 65.9 at
-// 120 and 58.0 -> 58.8 at 128.
-constexpr int SLAB_STATE_TILES_MAX_N = 108;
-int pencil_tiles(int N, int k, int v) { return k * g_fft[N].split_n1[v] * (N / g_fft[N].pencil_tt[v]); }
-
 }  // namespace
 
 constexpr int MAX_GROUPS = 3;   // state groups of one FFT solve on their own streams
@@ -250,6 +259,24 @@ struct qfdtd_ctx {
 };
 
 namespace {
+
+// split-x2 schedule: slab tiles (group of xi x1 planes, fast x2 digit; a tile carries every
+// state), pencil tiles (state, slow x2 frequency, x3 column block)
+const SplitKernels &split_of(const qfdtd_ctx *c) { return g_fft[c->N].split[c->dbl][c->split_v]; }
+int slab_tiles(const qfdtd_ctx *c) {
+  const SplitKernels &k = split_of(c);
+  return c->N / k.xi * (c->N / k.n1);
+}
+// At small N the slab tiles are few (N * N2, each taking all k states in turn), so up to this size
+// each state gets tiles of its own (aux 1), which reread the factor rows from cache.  Measured at
+// k = 3 on one stream, microseconds per step: complex64 19.9 -> 16.1 at 64, 36.9 -> 32.2 at 96,
+// 41.0 -> 39.4 at 108, but 49.5 either way at 120 and 50.4 -> 53.3 at 128; complex128 31.9 -> 28.0 at
+// 64, 49.8 -> 48.1 at 96, but 54.9 -> 55.5 at 100.
+int slab_state_tiles(const qfdtd_ctx *c, int k) { return c->N <= (c->dbl ? 96 : 108) && k > 1 ? k : 1; }
+int pencil_tiles(const qfdtd_ctx *c, int k) {
+  const SplitKernels &s = split_of(c);
+  return k * s.n1 * (c->N / s.pencil_tt);
+}
 
 void *dalloc(qfdtd_ctx *c, size_t bytes) {
   void *p = nullptr;
@@ -336,10 +363,17 @@ struct Entry {
   int aux;
 };
 
-// F_SLAB: slab passes of any mode (split below into the steady kernel and F_SLAB_EDGE, the kernel
-// of the chunk-edge and plain-transform modes)
+// F_SLAB: slab passes of any mode (split below into one launch per kernel kind, F_SLAB_KIND + kind)
 enum Fam { F_PLANE, F_ROW, F_COL, F_STENCIL, F_STENCIL2, F_PARITY, F_TO64, F_GRAM, F_APPLY, F_EPART, F_KPART, F_GFIN, F_EFIN,
-           F_SLAB, F_PENCIL, F_SLAB_EDGE };
+           F_SLAB, F_PENCIL, F_SLAB_KIND };   // F_SLAB_KIND last
+
+// Kernel kind of a slab pass: the steady passes with a real or complex factor and of the A/B update,
+// and every other mode
+int slab_kind(const Entry &e) {
+  if (e.mode == (M_INV | M_MID | M_FWD)) return e.c->vcomplex ? SLAB_COMPLEX : SLAB_REAL;
+  if (e.mode == (M_INV | M_COMB | M_FWD | M_ALT)) return SLAB_AB;
+  return SLAB_EDGE;
+}
 
 // Algorithmic bytes moved by one member's share of a launch (for timing): every state is read
 // and written once, and the per-site potential factor, which all k states of the member share,
@@ -352,11 +386,10 @@ double entry_bytes(const Entry &e, Fam f) {
   const double n3 = (double)c->n3();
   const double s = meas ? 16.0 : (double)c->csz();
   const double fsz = (c->vcomplex ? 2.0 : 1.0) * (meas ? 8.0 : (double)c->rsz());
+  if (f >= F_SLAB_KIND) f = F_ROW;     // the same traffic per state
   switch (f) {
     case F_PLANE:
     case F_ROW:
-    case F_SLAB:
-    case F_SLAB_EDGE:
       // A/B combine: read alt and psi and V, write psi (and alt when the forward follows)
       if (e.mode & M_COMB) return n * (3 * s + ((e.mode & M_FWD) ? s : 0.0)) + n3 * fsz;
       return n * 2 * s + ((e.mode & (M_PRE | M_MID | M_POST)) ? n3 * fsz : 0.0);
@@ -406,14 +439,13 @@ qfdtd_status run_fft_family(Fam f, std::vector<Entry> &es, bool dbl, hipStream_t
 qfdtd_status run_family(Fam f, std::vector<Entry> &es, bool dbl, int KS, hipStream_t sto) {
   if (es.empty()) return QFDTD_OK;
   if (f == F_SLAB) {
-    // steady slab passes and the other modes run in separate kernels
-    const uint32_t steady = M_INV | M_MID | M_FWD;
-    std::vector<Entry> st_es, ed_es;
-    for (auto &e : es) (e.mode == steady ? st_es : ed_es).push_back(e);
-    if (!ed_es.empty()) {
-      if (!st_es.empty()) QF_TRY(run_family(F_SLAB, st_es, dbl, KS, sto));
-      return run_family(F_SLAB_EDGE, ed_es, dbl, KS, sto);
+    for (int kind = 0; kind < SLAB_KINDS; ++kind) {
+      std::vector<Entry> sub;
+      for (auto &e : es)
+        if (slab_kind(e) == kind) sub.push_back(e);
+      QF_TRY(run_family((Fam)(F_SLAB_KIND + kind), sub, dbl, KS, sto));
     }
+    return QFDTD_OK;
   }
   if ((f == F_PLANE || f == F_ROW || f == F_COL) && KS >= 0) return run_fft_family(f, es, dbl, sto);
   const int grp = KS <= -2 ? -2 - KS : -1;   // multi-size kernel of this group
@@ -438,8 +470,8 @@ qfdtd_status run_family(Fam f, std::vector<Entry> &es, bool dbl, int KS, hipStre
       if (f == F_PLANE) l = K.plane_lds[dbl];
       else if (f == F_ROW) l = K.row_lds[dbl];
       else if (f == F_COL) l = K.col_lds[dbl];
-      else if (f == F_SLAB || f == F_SLAB_EDGE) l = K.slab_lds[e.c->split_v];
-      else if (f == F_PENCIL) l = K.pencil_lds[e.c->split_v];
+      else if (f >= F_SLAB_KIND) l = split_of(e.c).slab_lds;
+      else if (f == F_PENCIL) l = split_of(e.c).pencil_lds;
       if (l > lds) lds = l;
       if (grp >= 0 && (f == F_PLANE || f == F_ROW || f == F_COL))
         lds = g_grp_lds[grp][f == F_PLANE ? 0 : (f == F_ROW ? 1 : 2)][dbl];
@@ -455,7 +487,7 @@ qfdtd_status run_family(Fam f, std::vector<Entry> &es, bool dbl, int KS, hipStre
     if (f == F_PLANE || f == F_ROW || f == F_COL)
       cls = meas_copy ? TC_MEAS : (f == F_PLANE ? TC_PLANE : f == F_ROW ? TC_ROW : TC_COL);
     else if (f == F_STENCIL || f == F_STENCIL2) cls = TC_STENCIL;
-    else if (f == F_SLAB || f == F_SLAB_EDGE) cls = TC_SLAB;
+    else if (f >= F_SLAB_KIND) cls = TC_SLAB;
     else if (f == F_PENCIL) cls = TC_PENCIL;
     const int tix = cls >= 0 ? tbegin(c0, cls, bytes, st) : -1;
     const FftKernels &K = g_fft[es[base].c->N];
@@ -472,13 +504,12 @@ qfdtd_status run_family(Fam f, std::vector<Entry> &es, bool dbl, int KS, hipStre
       if (tix >= 0) (void)hipExtLaunchKernel(fn, dim3(total), dim3(nt), kargs, sh, st, ea, eb, 0);
       else (void)hipLaunchKernel(fn, dim3(total), dim3(nt), kargs, sh, st);
     };
-    switch (f) {
+    if (f >= F_SLAB_KIND) go(split_of(c0).slab[f - F_SLAB_KIND], split_of(c0).slab_nt, lds);
+    else switch (f) {
       case F_PLANE: go(fplane, ntplane, lds); break;
       case F_ROW: go(frow, LINE_THREADS, lds); break;
       case F_COL: go(fcol, LINE_THREADS, lds); break;
-      case F_SLAB: go(K.slab[c0->split_v], K.slab_nt[c0->split_v], lds); break;
-      case F_SLAB_EDGE: go(K.slab_edge[c0->split_v], K.slab_nt[c0->split_v], lds); break;
-      case F_PENCIL: go(K.pencil[c0->split_v], K.pencil_nt[c0->split_v], lds); break;
+      case F_PENCIL: go(split_of(c0).pencil, split_of(c0).pencil_nt, lds); break;
       case F_STENCIL: go(stencil_kernel(dbl), RED_THREADS, 0); break;
       case F_STENCIL2: go(stencil2_kernel(), S2_THREADS, 0); break;
       case F_PARITY: launch_parity(L, total, dbl, st); break;
@@ -489,6 +520,7 @@ qfdtd_status run_family(Fam f, std::vector<Entry> &es, bool dbl, int KS, hipStre
       case F_KPART: launch_kin_partials(L, total, KS, st); break;
       case F_GFIN: launch_gram_finalize(L, st); break;
       case F_EFIN: launch_energy_finalize(L, st); break;
+      default: break;
     }
     QF_LAUNCHED(c0);
   }
@@ -510,7 +542,7 @@ qfdtd_status run_by_k(Fam f, std::vector<Entry> &es, bool dbl) {
 // run a single-size kernel family once per distinct N and split variant (split-x2 passes)
 qfdtd_status run_by_size(Fam f, std::vector<Entry> &es, bool dbl) {
   std::vector<int> keys;
-  auto key_of = [&](const Entry &e) { return e.c->N * 4 + e.c->split_v; };
+  auto key_of = [&](const Entry &e) { return e.c->N * 8 + e.c->split_v; };
   for (auto &e : es)
     if (std::find(keys.begin(), keys.end(), key_of(e)) == keys.end()) keys.push_back(key_of(e));
   for (int kk : keys) {
@@ -594,6 +626,28 @@ qfdtd_status energies(std::vector<qfdtd_ctx *> &ms, bool with_trace) {
 
 // ------------------------------------------------------------- one chunk
 
+// Passes of a chunk of n steps of the split-x2 schedule: real-space pass `s` (s = 0: the chunk's
+// start, s = n: its end) and pencil pass `s` < n.  Chunk edges are slab passes, or plane passes that
+// leave or take x2 transformed as a whole, beside which a pencil pass leaves out its x2 part.
+Entry split_pencil(qfdtd_ctx *c, int which, int k, int s, int n) {
+  uint32_t mode = M_FWD | M_KIN | M_INV | (c->scheme == SCHEME_AB ? (uint32_t)M_ALT : 0u);
+  if (split_of(c).plane_edges) mode |= (s == 0 ? (uint32_t)M_PRE : 0u) | (s == n - 1 ? (uint32_t)M_POST : 0u);
+  return {c, which, mode, pencil_tiles(c, k), 0};
+}
+void split_real(qfdtd_ctx *c, int which, int k, int s, int n, std::vector<Entry> &slab, std::vector<Entry> &plane) {
+  const bool ab = c->scheme == SCHEME_AB;    // the transforms work on alt; psi stays for the combine
+  uint32_t mode;
+  if (s == 0) mode = ab ? M_FWD | M_ALT : M_PRE | M_FWD;
+  else if (s == n) mode = ab ? M_INV | M_COMB : M_INV | M_POST;
+  else mode = ab ? M_INV | M_COMB | M_FWD | M_ALT : M_INV | M_MID | M_FWD;
+  if (split_of(c).plane_edges && (s == 0 || s == n)) {
+    plane.push_back({c, which, mode | M_SPLIT, plane_tiles(c->N, k), 0});
+    return;
+  }
+  const int ps = slab_state_tiles(c, k);
+  slab.push_back({c, which, mode, ps * slab_tiles(c), ps > 1 ? 1 : 0});
+}
+
 // One FFT member with its states split into two or three groups, each group's pass
 // chain on its own stream: a group's plane pass (transform arithmetic bound)
 // overlaps the other group's column pass (memory bound); with the split-x2
@@ -608,16 +662,13 @@ qfdtd_status run_chunk_grouped(qfdtd_ctx *c, int n) {
     const int which = 2 + g, kg = c->gk[g];
     hipStream_t st = c->gst[g];
     if (c->split) {
-      const int v = c->split_v;
-      const int ps = (c->N <= SLAB_STATE_TILES_MAX_N && kg > 1) ? kg : 1;
-      std::vector<Entry> s0{{c, which, M_PRE | M_FWD, ps * slab_tiles(c->N, v), ps > 1 ? 1 : 0}};
-      QF_TRY(run_family(F_SLAB, s0, dbl, 0, st));
-      for (int s = 0; s < n; ++s) {
-        std::vector<Entry> pe{{c, which, M_FWD | M_KIN | M_INV, pencil_tiles(c->N, kg, v), 0}};
-        const uint32_t rs = (s == n - 1) ? (M_INV | M_POST) : (M_INV | M_MID | M_FWD);
-        std::vector<Entry> s1{{c, which, rs, ps * slab_tiles(c->N, v), ps > 1 ? 1 : 0}};
+      for (int s = 0; s <= n; ++s) {
+        std::vector<Entry> pe, sl, pl;
+        if (s > 0) pe.push_back(split_pencil(c, which, kg, s - 1, n));
+        split_real(c, which, kg, s, n, sl, pl);
         QF_TRY(run_family(F_PENCIL, pe, dbl, 0, st));
-        QF_TRY(run_family(F_SLAB, s1, dbl, 0, st));
+        QF_TRY(run_family(F_SLAB, sl, dbl, 0, st));
+        QF_TRY(run_family(F_PLANE, pl, dbl, 0, st));
       }
       QF_HIP(c, hipEventRecord(c->ev_join[g], st));
       continue;
@@ -637,11 +688,6 @@ qfdtd_status run_chunk_grouped(qfdtd_ctx *c, int n) {
   return QFDTD_OK;
 }
 
-Entry slab_entry(qfdtd_ctx *c, uint32_t mode) {
-  const int ps = (c->N <= SLAB_STATE_TILES_MAX_N && c->k > 1) ? c->k : 1;
-  return {c, 0, mode, ps * slab_tiles(c->N, c->split_v), ps > 1 ? 1 : 0};
-}
-
 qfdtd_status run_chunk(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n) {
   if (ms.empty()) return QFDTD_OK;
   // while launches are timed the state groups run on one stream, so that every timed launch
@@ -657,7 +703,7 @@ qfdtd_status run_chunk(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n) {
     qfdtd_ctx *c = ms[j];
     if (!c->fft() || n[j] <= 0) continue;
     if (c->split) {
-      sl.push_back(slab_entry(c, M_PRE | M_FWD));
+      split_real(c, 0, c->k, 0, n[j], sl, pl);
       continue;
     }
     // A/B update: the forward transform of psi goes to alt; psi stays for the combine
@@ -691,8 +737,8 @@ qfdtd_status run_chunk(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n) {
       }
       const bool last = (s == n[j] - 1);
       if (c->split) {
-        pen.push_back({c, 0, M_FWD | M_KIN | M_INV, pencil_tiles(c->N, c->k, c->split_v), 0});
-        sl.push_back(slab_entry(c, last ? (uint32_t)(M_INV | M_POST) : (uint32_t)(M_INV | M_MID | M_FWD)));
+        pen.push_back(split_pencil(c, 0, c->k, s, n[j]));
+        split_real(c, 0, c->k, s + 1, n[j], sl, pl);
         continue;
       }
       const bool ab = c->scheme == SCHEME_AB;
@@ -1012,9 +1058,10 @@ qfdtd_status qfdtd_create(qfdtd_ctx **out, int32_t N, double a, double m, int32_
     return fail(nullptr, QFDTD_E_UNSUPPORTED_N, "no transform kernels for this N");
   }
   c->scheme = (c->fft() && (o.flags & QFDTD_F_AB_SCHEME)) ? SCHEME_AB : SCHEME_SPLIT;
-  c->split_v = (int)QFDTD_SPLIT_VARIANT(o.flags);
-  c->split = c->fft() && c->scheme == SCHEME_SPLIT && (o.flags & QFDTD_F_SPLIT_X2) && !c->dbl &&
-             g_fft[N].slab[c->split_v] != nullptr;
+  // the complex64 A/B update keeps the operations of the plane pass (variant 4: its factors and its
+  // chunk edges), so it takes the split-x2 schedule where planes fit LDS
+  c->split_v = c->scheme == SCHEME_AB && !c->dbl ? 4 : (int)QFDTD_SPLIT_VARIANT(o.flags);
+  c->split = c->fft() && (o.flags & QFDTD_F_SPLIT_X2) && split_of(c).pencil != nullptr;
   c->plane = c->fft() && g_fft[N].plane[c->dbl ? 1 : 0] != nullptr && !(o.flags & QFDTD_F_ROWCOL) && !c->split;
   c->plane64 = c->fft() && g_fft[N].plane[1] != nullptr;
   c->nblk_red = red_blocks(n3);
@@ -1136,7 +1183,7 @@ qfdtd_status qfdtd_create(qfdtd_ctx **out, int32_t N, double a, double m, int32_
   }
   // state groups for the two-stream schedule (plane or split-x2 schedule, k >= 2)
   for (int g = 0; g < MAX_GROUPS; ++g) c->hd[2 + g] = c->hd[0];
-  if (c->fft() && (c->plane || c->split) && c->k >= 2 && !(o.flags & QFDTD_F_SINGLE_STREAM) && !ab) {
+  if (c->fft() && ((c->plane && !ab) || c->split) && c->k >= 2 && !(o.flags & QFDTD_F_SINGLE_STREAM)) {
     c->ngroups = ((o.flags & QFDTD_F_THREE_GROUPS) && c->k >= 3) ? 3 : 2;
     size_t first = 0;
     bool okg = hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming) == hipSuccess;
@@ -1144,6 +1191,7 @@ qfdtd_status qfdtd_create(qfdtd_ctx **out, int32_t N, double a, double m, int32_
       // states split as evenly as possible, the larger groups first
       c->gk[g] = c->k / c->ngroups + (g < c->k % c->ngroups ? 1 : 0);
       c->hd[2 + g].psi = (char *)c->psi + first * n3 * cs;
+      if (c->alt) c->hd[2 + g].alt = (char *)c->alt + first * n3 * cs;
       c->hd[2 + g].k = c->gk[g];
       first += (size_t)c->gk[g];
       okg = okg && hipStreamCreateWithFlags(&c->gst[g], hipStreamNonBlocking) == hipSuccess &&

@@ -1,0 +1,671 @@
+// Transform passes of the split-x2 schedule (templates; instantiated per size, precision and
+// variant by split_inst.hip).
+#pragma once
+
+#include "fft_passes.h"
+
+namespace qf {
+
+// ------------------------------------------------- slab and pencil passes (split x2)
+//
+// For large N the x2 transform is split four-step style, N = N1 N2 with i2 = N2 a + b
+// (a < N1, b < N2):
+//   forward  A (slab pass):   Y[k1][b] = W_N^{b k1} sum_a x[N2 a + b] W_N1^{a k1}, stored at row N2 k1 + b;
+//            B (pencil pass): X[k1 + N1 k2] = sum_b Y[k1][b] W_N2^{b k2},        stored at row N2 k1 + k2;
+//   inverse  B^-1 then A^-1 with conjugate roots, on the same rows.
+// The slab pass holds the N1 rows {N2 a + b} of one x1 plane (b fixed): A^-1, the x3
+// transforms around the potential factor, A.  The pencil pass holds the N2 consecutive rows
+// N2 k1 .. N2 k1 + N2 - 1 of TT consecutive x3 columns over all x1: B, the x1 transforms
+// around the kinetic factor (x2 frequency k1 + N1 k2 at row N2 k1 + k2), B^-1.  One step is
+// then two passes over the state (a pencil pass and a slab pass) instead of a row pass and
+// three column passes.  Between the passes of a chunk the state is held in this split x2
+// order; the chunk's first and last slab passes take it from and return it to real space
+// in natural order.
+//
+// Plane groups.  Between the passes the XI x1 planes XI p .. XI p + XI - 1 of a group are also
+// interleaved: the memory of row r of plane XI p + j (its "row slot" j) holds columns
+// j N/XI .. (j + 1) N/XI - 1 of all XI planes of the group, column j N/XI + w / XI of plane
+// XI p + w mod XI at element w.  A pencil tile's (x1, row) piece then spans XI times the bytes of
+// its TT columns, and a slab tile, which holds the N1 rows of all planes of a group, reads and
+// writes exactly the memory of those rows in either order (the in-place chunk-edge passes that
+// convert from and to natural order touch no other tile's memory).
+
+template <typename T, int N, int N1, int XI, int PK> __host__ __device__ constexpr size_t slab_lds_t() {
+  return (size_t)(XI * N1 * padded_len(N) + 8 * (XI - 1) + tw_total<PK, N>()) * sizeof(C<T>);
+}
+// Lines of a slab tile: row a of the group's plane j is line j N1 + a, and the lines of plane j start
+// 8 j elements further, so that the A stages' lanes, which alternate between the planes of one
+// column, fall on distinct LDS banks (N1 P elements is a multiple of 128 bytes at N1 = 16).
+template <int NL, int P, int N1, int XI> struct SlabGeo {
+  static constexpr int nlines = NL;
+  static constexpr bool linefast = false;
+  static __device__ __forceinline__ int at(int b, int n) {
+    if constexpr (XI == 1) return b * P + padn(n);
+    else return b * P + (b / N1) * 8 + padn(n);
+  }
+};
+// Pencil tile in LDS: element n (x1) of line l = k2 TT + c at n PC + l.  PC = lines + 4 (+ 4 more
+// where that is a multiple of 32) puts the 16 lanes of one 128-byte LDS pass (4 x1 positions x 4
+// columns, or 8 x 2) on distinct banks when the B stage writes its outputs.
+template <int N2, int TT> __host__ __device__ constexpr int pencil_pitch() {
+  return N2 * TT + 4 + ((N2 * TT + 4) % 32 == 0 ? 4 : 0);
+}
+template <typename T, int N, int N2, int TT, int PK> __host__ __device__ constexpr size_t pencil_lds_t() {
+  return (size_t)(N * pencil_pitch<N2, TT>() + tw_total<PK, N>()) * sizeof(C<T>) + N * sizeof(T);
+}
+
+// Loads and stores of one state with a block-uniform base and a 32-bit per-lane byte offset.
+// The base goes through readfirstlane, so the compiler holds it (plus any uniform offset) in
+// scalar registers and each access needs one 32-bit offset register instead of a 64-bit address:
+// a lane keeps one access per x2 row of a split-x2 stage in flight.
+// With G the pointer is taken in the global address space and each row's uniform offset is kept in a
+// scalar register (the empty asm stops the compiler from folding it into a 64-bit vector address),
+// so the accesses can use the global forms; without G they are flat accesses.  The slab pass
+// measured faster with the global forms, the pencil pass with flat ones.
+template <typename T, bool G = false> struct StateBuf {
+  typedef __attribute__((address_space(1))) char gchar;
+  typedef T pair_t __attribute__((ext_vector_type(2)));
+  typedef __attribute__((address_space(1))) pair_t gelem;
+  const char *base;
+  __device__ __forceinline__ explicit StateBuf(const void *p) {
+    const uint64_t v = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    base = (const char *)(((uint64_t)hi << 32) | lo);
+  }
+  __device__ __forceinline__ gchar *grow(uint32_t soff) const {
+    asm volatile("" : "+s"(soff));
+    return (gchar *)base + soff;
+  }
+  __device__ __forceinline__ C<T> load(uint32_t voff, uint32_t soff) const {
+    if constexpr (G) {
+      const pair_t v = *(const gelem *)(grow(soff) + voff);
+      return mkc<T>(v.x, v.y);
+    } else {
+      return *(const C<T> *)(base + soff + voff);
+    }
+  }
+  __device__ __forceinline__ void store(C<T> x, uint32_t voff, uint32_t soff) const {
+    if constexpr (G) {
+      pair_t v;
+      v.x = x.x;
+      v.y = x.y;
+      *(gelem *)(grow(soff) + voff) = v;
+    } else {
+      *(C<T> *)(const_cast<char *>(base) + soff + voff) = x;
+    }
+  }
+};
+
+// x with its two parts in scalar registers (x must be the same in every lane of the wave)
+__device__ __forceinline__ float uniform(float x) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))); }
+__device__ __forceinline__ double uniform(double x) {
+  const long long b = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_readfirstlane((int)(b & 0xffffffffLL));
+  const int hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+template <typename V> __device__ __forceinline__ V uniform(V x) { V r; r.x = uniform(x.x); r.y = uniform(x.y); return r; }
+
+// Slab pass on tile (plane group p, fast x2 digit b), for each state of the member in turn, so that
+// the potential factor rows of the tile are read from HBM once for all k states (or, with the
+// entry's aux = 1, for one state per tile: k times the tiles, each reading the factor rows).  The
+// tile's LDS holds row a of the group's plane j as line j N1 + a.  M_INV reads the split order, M_FWD
+// writes it; otherwise the state is read or written in natural order.  KIND:
+//   SLAB_REAL, SLAB_COMPLEX: the steady mode (M_INV | M_MID | M_FWD) for a real or complex factor:
+//     A^-1 from HBM, inverse x3, x h^2 (fused with the last inverse and first forward stages), forward
+//     x3, A to HBM;
+//   SLAB_AB: the steady mode of the A/B update (M_INV | M_COMB | M_FWD | M_ALT): the same on alt, with
+//     psi' = A psi - B (dt H_K psi) as the fused middle stage (psi in natural order);
+//   SLAB_EDGE: the other modes: chunk start (M_PRE | M_FWD: x h, forward x3, A; A/B: M_FWD | M_ALT
+//     from psi to alt), chunk end (M_INV | M_POST: A^-1, inverse x3, x h; A/B: M_INV | M_COMB) and
+//     plain transforms.
+// Kernels of their own, so that the registers of one kind do not weigh on another.
+template <typename T, int N, int N1, int NT, int XI, int PK, int KIND>
+__device__ __forceinline__ void slab_body(const LaunchList &L, int e, int t, unsigned char *smem) {
+  constexpr int N2 = N / N1;
+  constexpr int P = padded_len(N);
+  constexpr int NR = XI * N1;               // LDS lines of a tile
+  constexpr int NH = N / XI;                // columns of each plane in one row slot
+  constexpr int NP = XI * N;                // (row slot, element) positions of one row
+  constexpr int CQ = (NP + NT - 1) / NT;    // positions per thread in the A stages
+  constexpr int TPS = (N / XI) * N2;        // tiles per state
+  using Rows = SlabGeo<NR, P, N1, XI>;
+  constexpr int NST = stages_of<PK, N, false>().n, M = NST - 1;
+  static_assert(N % N1 == 0 && N % XI == 0 && NST >= 2, "slab pass needs N1 | N, XI | N and a plan of two or more stages");
+  static_assert((size_t)N * N * N * sizeof(C<T>) < (1ull << 31), "states below 2 GiB");
+  const PassDesc &d = *(const PassDesc *)L.descp[e];
+  const uint32_t mode = L.mode[e];
+  // aux 1: one state per tile (tiles of state s follow those of state s - 1), else all k states
+  int s0 = 0, s1 = d.k;
+  if (L.aux[e] == 1) {
+    s0 = t / TPS;
+    s1 = s0 + 1;
+    t -= s0 * TPS;
+  }
+  const int p = t / N2, b = t - (t / N2) * N2;
+  // the twiddle tables first, so that their addresses fit the LDS instructions' offset field
+  C<T> *tw = (C<T> *)smem;
+  C<T> *buf = tw + tw_total<PK, N>();
+  constexpr size_t N3 = (size_t)N * N * N;
+  const size_t voff = (size_t)XI * p * N * N;    // the group's first plane
+  const C<T> *gtw = (const C<T> *)d.tw;
+  // offset from the group's first plane of row N2 a + b of plane (or row slot) j, element n
+  auto site = [&](int j, int a, int n) -> size_t { return ((size_t)j * N + N2 * a + b) * N + n; };
+  // W_N^{b k1}, the twiddles of A: b is the same for the whole block, so they stay in scalar
+  // registers
+  C<T> wab[N1];
+#pragma unroll
+  for (int k1 = 1; k1 < N1; ++k1) wab[k1] = uniform(gtw[(b * k1) % N]);
+  // A^-1: the N1 values of each (row slot, element) position are loaded (a_load), then conj twiddles,
+  // inverse DFT over k1, to the LDS lines of the position's plane and column (a_inverse)
+  auto a_load = [&](C<T> (&v)[N1], const StateBuf<T, true> &sb, int q) {
+    const int pos = (int)threadIdx.x + q * NT;
+    if (NP % NT == 0 || pos < NP) {
+      const int j = pos / N, w = pos - (pos / N) * N;
+      const uint32_t vo = (uint32_t)(site(j, 0, w) * sizeof(C<T>));
+#pragma unroll
+      for (int k1 = 0; k1 < N1; ++k1) v[k1] = sb.load(vo, (uint32_t)(k1 * N2 * N * sizeof(C<T>)));
+    }
+  };
+  auto a_inverse = [&](C<T> (&v)[N1], int q) {
+    const int pos = (int)threadIdx.x + q * NT;
+    if (NP % NT == 0 || pos < NP) {
+      const int j = pos / N, w = pos - (pos / N) * N;
+      const int pl = w % XI, col = j * NH + w / XI;
+#pragma unroll
+      for (int k1 = 1; k1 < N1; ++k1) {
+        C<T> w1 = wab[k1];
+        w1.y = -w1.y;
+        v[k1] = cmul(v[k1], w1);
+      }
+      Dft<N1, true, C<T>>::run(v);
+#pragma unroll
+      for (int a = 0; a < N1; ++a) buf[Rows::at(pl * N1 + a, col)] = v[a];
+    }
+  };
+  // the state's split-order rows to the LDS lines.  The loads are issued before the block waits
+  // for the twiddle tables and for the previous state's last reads of the LDS lines.
+  auto a_inverse_to_lds = [&](const C<T> *g) {
+    const StateBuf<T, true> sb(g);
+    if constexpr (CQ == 1) {
+      C<T> v[N1];
+      a_load(v, sb, 0);
+      __syncthreads();
+      a_inverse(v, 0);
+    } else {
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < CQ; ++q) {
+        C<T> v[N1];
+        a_load(v, sb, q);
+        a_inverse(v, q);
+      }
+    }
+    __syncthreads();
+  };
+  // A: columns from the LDS lines, DFT over a, twiddles, to HBM at rows N2 k1 + b
+  auto a_forward_from_lds = [&](C<T> *g) {
+    const StateBuf<T, true> sb(g);
+#pragma unroll
+    for (int q = 0; q < CQ; ++q) {
+      const int pos = (int)threadIdx.x + q * NT;
+      if (NP % NT == 0 || pos < NP) {
+        const int j = pos / N, w = pos - (pos / N) * N;
+        const int pl = w % XI, col = j * NH + w / XI;
+        C<T> v[N1];
+#pragma unroll
+        for (int a = 0; a < N1; ++a) v[a] = buf[Rows::at(pl * N1 + a, col)];
+        Dft<N1, false, C<T>>::run(v);
+#pragma unroll
+        for (int k1 = 1; k1 < N1; ++k1) v[k1] = cmul(v[k1], wab[k1]);
+        const uint32_t vo = (uint32_t)(site(j, 0, w) * sizeof(C<T>));
+#pragma unroll
+        for (int k1 = 0; k1 < N1; ++k1) sb.store(v[k1], vo, (uint32_t)(k1 * N2 * N * sizeof(C<T>)));
+      }
+    }
+  };
+  if constexpr (KIND != SLAB_EDGE) {
+    constexpr bool AB = KIND == SLAB_AB;
+    constexpr int RM = StageOf<PK, N, false, M>::R;
+    using SS = SG<Rows, N, RM, NT>;
+    using F = typename FacT<T, KIND == SLAB_COMPLEX>::type;
+    // potential factors of the fused middle stage, held in registers for all k states (one
+    // fetch per tile)
+    F hq[AB ? 1 : SS::CAPQ][AB ? 1 : RM];
+    if constexpr (!AB) {
+#pragma unroll
+      for (int q = 0; q < SS::CAPQ; ++q) {
+        if (SS::active(q)) {
+          int j, bl;
+          SS::jb(q, j, bl);
+          const int pl = bl / N1, a = bl - (bl / N1) * N1;
+#pragma unroll
+          for (int r = 0; r < RM; ++r) hq[q][r] = ((const F *)d.h2fac)[voff + site(pl, a, j + r * SS::NR)];
+        }
+      }
+    }
+    fill_twiddles<T, PK, N, NT>(tw, gtw);
+    for (int s = s0; s < s1; ++s) {
+      C<T> *g = (C<T> *)(AB ? d.alt : d.psi) + (size_t)s * N3 + voff;
+      a_inverse_to_lds(g);
+      lds_stages<T, PK, N, false, true, Rows, NT, 0, M>(buf, tw);
+      {
+        C<T> v[SS::CAPQ][RM];
+        stage_read<T, PK, N, false, M, true, Rows, NT>(v, tw, [&](int bl, int n) { return buf[Rows::at(bl, n)]; });
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < SS::CAPQ; ++q) {
+          if (SS::active(q)) {
+            if constexpr (AB) {
+              C<T> *gp = (C<T> *)d.psi + (size_t)s * N3 + voff;
+              int j, bl;
+              SS::jb(q, j, bl);
+              const int pl = bl / N1, a = bl - (bl / N1) * N1;
+#pragma unroll
+              for (int r = 0; r < RM; ++r) {
+                const size_t o = site(pl, a, j + r * SS::NR);
+                v[q][r] = ab_combine<T>(gp[o], v[q][r], d, voff + o);
+                gp[o] = v[q][r];
+              }
+            } else {
+#pragma unroll
+              for (int r = 0; r < RM; ++r) {
+                if constexpr (KIND == SLAB_COMPLEX) v[q][r] = cmul(v[q][r], hq[q][r]);
+                else v[q][r] = cscale(v[q][r], hq[q][r]);
+              }
+            }
+            stage_first<T, PK, N, true, false>(v[q], tw);
+          }
+        }
+        stage_write<T, PK, N, true, 0, Rows, NT>(v, [&](int bl, int n, C<T> x) { buf[Rows::at(bl, n)] = x; });
+        __syncthreads();
+      }
+      lds_stages<T, PK, N, true, false, Rows, NT, 1, NST>(buf, tw);
+      a_forward_from_lds(g);
+    }
+    return;
+  }
+  // Natural-order tile accesses (chunk edges, plain transforms): each thread takes elements
+  // threadIdx.x + it NT, UB at a time, with all UB global loads issued before they are used.
+  constexpr int NE = NR * N;
+  constexpr int EPT = (NE + NT - 1) / NT;
+  constexpr int UB = EPT < 8 ? EPT : 8;
+  const bool vc = d.vcomplex != 0;
+  auto fac = [&](const void *f, size_t o) -> C<T> {
+    return vc ? ((const C<T> *)f)[voff + o] : mkc<T>(((const T *)f)[voff + o], 0);
+  };
+  fill_twiddles<T, PK, N, NT>(tw, gtw);
+  // state rows (times the factor f if given) to the LDS lines
+  auto natural_to_lds = [&](const C<T> *g, const void *f) {
+    const StateBuf<T, true> sb(g);
+    __syncthreads();       // the twiddle tables; the previous state's reads of the LDS lines
+#pragma unroll 1
+    for (int it0 = 0; it0 < EPT; it0 += UB) {
+      C<T> v[UB], h[UB];
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        const int idx = (int)threadIdx.x + (it0 + u) * NT;
+        if (it0 + u < EPT && (NE % NT == 0 || idx < NE)) {
+          const int bl = idx / N, n = idx - bl * N, pl = bl / N1, a = bl - pl * N1;
+          v[u] = sb.load((uint32_t)(site(pl, a, n) * sizeof(C<T>)), 0);
+          if (f) h[u] = fac(f, site(pl, a, n));
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        const int idx = (int)threadIdx.x + (it0 + u) * NT;
+        if (it0 + u < EPT && (NE % NT == 0 || idx < NE)) {
+          const int bl = idx / N, n = idx - bl * N;
+          C<T> x = v[u];
+          if (f) x = vc ? cmul(x, h[u]) : cscale(x, h[u].x);
+          buf[Rows::at(bl, n)] = x;
+        }
+      }
+    }
+    __syncthreads();
+  };
+  // LDS lines (times the factor f if given) to the state rows
+  auto lds_to_natural = [&](C<T> *g, const void *f) {
+    const StateBuf<T, true> sb(g);
+#pragma unroll 1
+    for (int it0 = 0; it0 < EPT; it0 += UB) {
+      C<T> h[UB];
+      if (f) {
+#pragma unroll
+        for (int u = 0; u < UB; ++u) {
+          const int idx = (int)threadIdx.x + (it0 + u) * NT;
+          if (it0 + u < EPT && (NE % NT == 0 || idx < NE)) {
+            const int bl = idx / N, n = idx - bl * N, pl = bl / N1, a = bl - pl * N1;
+            h[u] = fac(f, site(pl, a, n));
+          }
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        const int idx = (int)threadIdx.x + (it0 + u) * NT;
+        if (it0 + u < EPT && (NE % NT == 0 || idx < NE)) {
+          const int bl = idx / N, n = idx - bl * N, pl = bl / N1, a = bl - pl * N1;
+          C<T> x = buf[Rows::at(bl, n)];
+          if (f) x = vc ? cmul(x, h[u]) : cscale(x, h[u].x);
+          sb.store(x, (uint32_t)(site(pl, a, n) * sizeof(C<T>)), 0);
+        }
+      }
+    }
+  };
+  const void *fmid = (mode & M_MID) ? d.h2fac : (mode & M_POST) ? d.hfac : nullptr;
+  const bool comb = (mode & M_COMB) != 0;
+  for (int s = s0; s < s1; ++s) {
+    const size_t so = (size_t)s * N3 + voff;
+    C<T> *gp = (C<T> *)d.psi + so;
+    // split order is read from and written to alt in the A/B update, psi otherwise
+    C<T> *gs = (mode & (M_COMB | M_ALT)) ? (C<T> *)d.alt + so : gp;
+    if (mode & M_INV) a_inverse_to_lds(gs);
+    else natural_to_lds(gp, (mode & M_PRE) ? d.hfac : nullptr);
+    if (mode & M_INV) fft_lines_t<T, PK, N, true, Rows, NT>(buf, tw);
+    if (comb) {
+      for (int idx = threadIdx.x; idx < NE; idx += NT) {
+        const int bl = idx / N, n = idx - bl * N, pl = bl / N1, a = bl - pl * N1;
+        const size_t o = site(pl, a, n);
+        gp[o] = ab_combine<T>(gp[o], buf[Rows::at(bl, n)], d, voff + o);
+      }
+      continue;            // the chunk's last combine: no forward transform follows
+    }
+    if (mode & M_FWD) {
+      if (fmid) {
+        for (int idx = threadIdx.x; idx < NE; idx += NT) {
+          const int bl = idx / N, n = idx - bl * N;
+          const int pl = bl / N1, a = bl - pl * N1;
+          const C<T> h = fac(fmid, site(pl, a, n));
+          const int o = Rows::at(bl, n);
+          buf[o] = vc ? cmul(buf[o], h) : cscale(buf[o], h.x);
+        }
+        __syncthreads();
+      }
+      fft_lines_t<T, PK, N, false, Rows, NT>(buf, tw);
+      a_forward_from_lds(gs);
+    } else {
+      // the factor of the chunk end (or a middle factor) is applied on the way out
+      lds_to_natural(gp, fmid);
+    }
+  }
+}
+
+// Pencil pass on tile (state s, slow x2 frequency k1, x3 columns c0 .. c0 + TT - 1): B, forward x1,
+// x e^{-dt T(k)}/N^3, inverse x1, B^-1.  The state (alt in the A/B update) is in split order with
+// plane groups of XI.  Next to a plane pass at the chunk's edges x2 is transformed as a whole there
+// and B (M_PRE) or B^-1 (M_POST) is left out.
+template <typename T, int N, int N2, int TT, int NT, int XI, int PK>
+__device__ __forceinline__ void pencil_body(const LaunchList &L, int e, int t, unsigned char *smem) {
+  constexpr int N1 = N / N2;
+  constexpr int NH = N / XI;
+  constexpr int NL = N2 * TT;
+  constexpr int PC = pencil_pitch<N2, TT>();
+  constexpr int NCB = N / TT;
+  constexpr int PPT = (N * TT + NT - 1) / NT;    // (x1, column) positions per thread in the B stages
+  using Geo = TileGeo<NL, PC>;
+  constexpr int NST = stages_of<PK, N, false>().n, M = NST - 1;
+  static_assert(N % N2 == 0 && N % TT == 0 && N % XI == 0 && N % 2 == 0 && NST >= 2, "pencil tile must divide the lattice");
+  static_assert((size_t)N * N * N * sizeof(C<T>) < (1ull << 31), "states below 2 GiB");
+  const PassDesc &d = *(const PassDesc *)L.descp[e];
+  const int cb = t % NCB;
+  const int u = t / NCB;
+  const int k1 = u % N1, s = u / N1;
+  const int c0 = cb * TT;
+  // the twiddle and kinetic tables first, so that their addresses fit the LDS instructions'
+  // offset field
+  C<T> *tw = (C<T> *)smem;
+  T *ktl = (T *)(tw + tw_total<PK, N>());      // the per-axis kinetic table
+  C<T> *buf = (C<T> *)(ktl + N);
+  constexpr size_t N3 = (size_t)N * N * N;
+  const uint32_t mode = L.mode[e];
+  const StateBuf<T> sb((C<T> *)((mode & M_ALT) ? d.alt : d.psi) + (size_t)s * N3);
+  // the k-space factor of kin_factor_t, with the table read from LDS
+  const bool rel = d.kin == KIN_REL, ab = d.scheme == SCHEME_AB;
+  const T mm = (T)d.m, dtT = (T)d.dt, in3 = (T)d.inv_n3, dtn = (T)(d.dt * d.inv_n3);
+  auto kfac = [&](int i1, int i2, int i3) -> T {
+    if (rel) {
+      const T p2 = ktl[i1] + ktl[i2] + ktl[i3];
+      if constexpr (sizeof(T) == 4) {
+        const float r = __builtin_amdgcn_sqrtf(p2 + mm * mm);
+        if (ab) return p2 * __builtin_amdgcn_rcpf(r + mm) * dtn;
+        return __builtin_amdgcn_exp2f(-dtT * 1.4426950408889634f * (r - mm)) * in3;
+      } else {
+        const T tk = p2 / (sqrt(p2 + mm * mm) + mm);
+        if (ab) return tk * dtn;
+        return exp(-dtT * tk) * in3;
+      }
+    }
+    if (ab) return (ktl[i1] + ktl[i2] + ktl[i3]) * dtn;
+    return ktl[i1] * ktl[i2] * ktl[i3] * in3;
+  };
+  // byte offset of (x1 plane i1, row N2 k1, column c0 + c): row slot (c0 + c) / NH of the plane
+  // group, element XI ((c0 + c) mod NH) + i1 mod XI; rows b apart by b N elements
+  auto at = [&](int i1, int c) -> uint32_t {
+    const int col = c0 + c, j = col / NH, w = XI * (col - j * NH) + i1 % XI;
+    return (uint32_t)((((size_t)(i1 - i1 % XI + j) * N + (size_t)(N2 * k1)) * N + w) * sizeof(C<T>));
+  };
+  auto b_load = [&](C<T> (&v)[N2], int q) {
+    const int pos = (int)threadIdx.x + q * NT;
+    if ((N * TT) % NT == 0 || pos < N * TT) {
+      const int i1 = pos / TT, c = pos - (pos / TT) * TT;
+#pragma unroll
+      for (int bb = 0; bb < N2; ++bb) v[bb] = sb.load(at(i1, c), (uint32_t)(bb * N * sizeof(C<T>)));
+    }
+  };
+  // B: DFT over the N2 rows of each (x1, column) position, outputs to the x1 lines (k2, c)
+  auto b_forward = [&](C<T> (&v)[N2], int q) {
+    const int pos = (int)threadIdx.x + q * NT;
+    if ((N * TT) % NT == 0 || pos < N * TT) {
+      const int i1 = pos / TT, c = pos - (pos / TT) * TT;
+      if (!(mode & M_PRE)) Dft<N2, false, C<T>>::run(v);
+#pragma unroll
+      for (int k2 = 0; k2 < N2; ++k2) buf[Geo::at(k2 * TT + c, i1)] = v[k2];
+    }
+  };
+  {
+    // the first position's loads are in flight while the tables are filled
+    C<T> v[N2];
+    b_load(v, 0);
+    fill_twiddles<T, PK, N, NT>(tw, (const C<T> *)d.tw);
+    for (int i = threadIdx.x; i < N; i += NT) ktl[i] = ((const T *)d.ktab)[i];
+    b_forward(v, 0);
+  }
+#pragma unroll
+  for (int q = 1; q < PPT; ++q) {
+    C<T> v[N2];
+    b_load(v, q);
+    b_forward(v, q);
+  }
+  __syncthreads();
+  lds_stages<T, PK, N, false, false, Geo, NT, 0, M>(buf, tw);
+  {
+    constexpr int R = StageOf<PK, N, false, M>::R;
+    using SS = SG<Geo, N, R, NT>;
+    C<T> v[SS::CAPQ][R];
+    stage_read<T, PK, N, false, M, false, Geo, NT>(v, tw, [&](int l, int n) { return buf[Geo::at(l, n)]; });
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < SS::CAPQ; ++q) {
+      if (SS::active(q)) {
+        int j, l;
+        SS::jb(q, j, l);
+        const int k2 = l / TT, c = l - (l / TT) * TT;
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[q][r] = cscale(v[q][r], kfac(j + r * SS::NR, k1 + N1 * k2, c0 + c));
+        stage_first<T, PK, N, true, true>(v[q], tw);
+      }
+    }
+    stage_write<T, PK, N, true, 0, Geo, NT>(v, [&](int l, int n, C<T> x) { buf[Geo::at(l, n)] = x; });
+    __syncthreads();
+  }
+  lds_stages<T, PK, N, true, true, Geo, NT, 1, NST>(buf, tw);
+  // B^-1: inverse DFT over k2 of each position, to the N2 rows in HBM
+#pragma unroll
+  for (int q = 0; q < PPT; ++q) {
+    const int pos = (int)threadIdx.x + q * NT;
+    if ((N * TT) % NT == 0 || pos < N * TT) {
+      const int i1 = pos / TT, c = pos - (pos / TT) * TT;
+      C<T> v[N2];
+#pragma unroll
+      for (int k2 = 0; k2 < N2; ++k2) v[k2] = buf[Geo::at(k2 * TT + c, i1)];
+      if (!(mode & M_POST)) Dft<N2, true, C<T>>::run(v);
+#pragma unroll
+      for (int bb = 0; bb < N2; ++bb) sb.store(v[bb], at(i1, c), (uint32_t)(bb * N * sizeof(C<T>)));
+    }
+  }
+}
+
+// Tile shapes of the split-x2 passes per size, precision and variant: x2 = N1 x N2 (N1 stride rows
+// per slab tile, N2 consecutive rows per pencil tile; both have register butterflies), plane groups
+// of XI, TT x3 columns per pencil tile, and per pass its threads and the radix plan of its line
+// transforms.  A pencil tile's (x1, row) pieces are XI TT elements.
+//
+// Complex64 factors and plans are fixed by results: the x2 factors and the radix sequence of a size
+// decide every rounding, and energies of complex64 solves keep their digits only as long as both stay
+// (other two-stage plans moved them by 1e-6).  So the plans are make_rplan's, with adjacent stages
+// fused in registers where that is faster, and up to N = 90 the factors are those of the plane pass
+// (see split_row).  The rest, and all of a complex128 shape, was found by timing: plane groups,
+// columns, threads, fused stages (complex128: factors up to 18 and two-stage plans), each slab kernel
+// in turn with the pencil kernels of the same factors, with one and three states on an MI355X.  (In
+// turn, because at small N a pass run by itself finds in its XCD's L2 what it has just written there:
+// 128^3, one state, 21 us for the two passes by themselves and 30 us in turn.)  What decides:
+//   - an LDS exchange less per direction: 240^3, one complex64 state, 16 x (3 x 5) against 16 x 3 x 5:
+//     slab pass 86 -> 62 us, pencil pass 89 -> 77 us;
+//   - the passes are bound by latency, so registers decide: at most 128 leave four waves per SIMD;
+//   - pencil pieces of 32 bytes and more (XI TT >= 4 in complex64, >= 2 in complex128): the L1 is
+//     bound by requests below that;
+//   - at small N more, smaller tiles: one per (plane, row digit) with 64 to 256 threads.
+// Variants:
+//   0: the fastest for three states;  1: complex64 from 96 up: the fastest other shape of the same
+//   factors (complex128: the fastest for one state, where that is another);  2: 8 consecutive rows per
+//   pencil tile and 8 columns;  3: the factors swapped;  4 (not selectable by flags): the A/B update
+//   of complex64 up to N = 128, with the factors of the plane pass.
+struct SplitDef {
+  int N, dbl, v, N1, XI, TT, slab_nt, slab_plan, pencil_nt, pencil_plan;
+};
+constexpr SplitDef SPLIT_DEFS[] = {
+    {96, 0, 0, 16, 1, 4, 128, rp(16, 6), 384, rp(16, 6)},
+    {96, 0, 1, 16, 1, 8, 128, rp(16, 6), 768, rp(16, 6)},
+    {96, 0, 3, 6, 2, 4, 192, rp(16, 6), 384, rp(16, 6)},
+    {100, 0, 0, 10, 1, 4, 128, rp(10, 10), 448, rp(10, 10)},
+    {100, 0, 1, 10, 2, 4, 256, rp(10, 10), 448, rp(10, 10)},
+    {108, 0, 0, 12, 1, 4, 192, rp(12, 9), 448, rp(12, 9)},
+    {108, 0, 1, 12, 2, 2, 320, rp(12, 9), 256, rp(12, 9)},
+    {108, 0, 3, 9, 2, 4, 256, rp(12, 9), 448, rp(12, 9)},
+    {120, 0, 0, 12, 1, 4, 128, rp(8, 15), 512, rp(8, 15)},
+    {120, 0, 1, 12, 2, 4, 256, rp(8, 15), 512, rp(8, 15)},
+    {120, 0, 3, 10, 2, 4, 256, rp(8, 15), 512, rp(8, 15)},
+    {128, 0, 0, 16, 2, 4, 256, rp(16, 8), 512, rp(16, 8)},
+    {128, 0, 1, 16, 1, 4, 128, rp(16, 8), 512, rp(16, 8)},
+    {128, 0, 2, 16, 2, 8, 256, rp(16, 8), 1024, rp(16, 8)},
+    {128, 0, 3, 8, 2, 4, 256, rp(16, 8), 512, rp(16, 8)},
+    {144, 0, 0, 16, 1, 4, 256, rp(16, 9), 576, rp(16, 9)},
+    {144, 0, 1, 16, 2, 2, 512, rp(16, 9), 320, rp(16, 9)},
+    {144, 0, 3, 9, 2, 2, 192, rp(16, 9), 320, rp(16, 9)},
+    {150, 0, 0, 15, 1, 2, 128, rp(6, st(5, 5)), 320, rp(6, 5, 5)},
+    {150, 0, 1, 15, 2, 2, 320, rp(6, st(5, 5)), 320, rp(6, 5, 5)},
+    {150, 0, 3, 10, 1, 2, 256, rp(6, 5, 5), 320, rp(6, 5, 5)},
+    {160, 0, 0, 16, 1, 4, 256, rp(16, 10), 640, rp(16, 10)},
+    {160, 0, 1, 16, 2, 2, 512, rp(16, 10), 320, rp(16, 10)},
+    {160, 0, 3, 10, 2, 2, 256, rp(16, 10), 320, rp(16, 10)},
+    {162, 0, 0, 18, 1, 2, 192, rp(18, 9), 384, rp(18, 9)},
+    {162, 0, 1, 18, 2, 2, 384, rp(18, 9), 384, rp(18, 9)},
+    {162, 0, 3, 9, 1, 2, 192, rp(18, 9), 384, rp(18, 9)},
+    {180, 0, 0, 18, 1, 4, 192, rp(4, 9, 5), 768, rp(4, 9, 5)},
+    {180, 0, 1, 18, 1, 2, 192, rp(4, 9, 5), 384, rp(4, 9, 5)},
+    {180, 0, 3, 10, 1, 4, 256, rp(4, 9, 5), 768, rp(4, 9, 5)},
+    {192, 0, 0, 16, 2, 2, 256, rp(8, st(8, 3)), 384, rp(8, 8, 3)},
+    {192, 0, 1, 16, 2, 4, 256, rp(8, st(8, 3)), 768, rp(8, st(8, 3))},
+    {192, 0, 3, 12, 1, 4, 192, rp(8, 8, 3), 768, rp(8, st(8, 3))},
+    {200, 0, 0, 20, 1, 4, 256, rp(8, st(5, 5)), 832, rp(8, 5, 5)},
+    {200, 0, 1, 20, 1, 2, 256, rp(8, st(5, 5)), 448, rp(8, 5, 5)},
+    {200, 0, 3, 10, 1, 4, 256, rp(8, 5, 5), 832, rp(8, st(5, 5))},
+    {216, 0, 0, 18, 2, 2, 448, rp(8, 9, 3), 448, rp(8, 9, 3)},
+    {216, 0, 1, 18, 1, 2, 256, rp(8, st(9, 3)), 448, rp(8, 9, 3)},
+    {216, 0, 3, 12, 1, 4, 128, rp(8, st(9, 3)), 896, rp(8, st(9, 3))},
+    {240, 0, 0, 16, 1, 4, 256, rp(16, st(3, 5)), 960, rp(16, st(3, 5))},
+    {240, 0, 1, 16, 1, 2, 256, rp(16, st(3, 5)), 512, rp(16, st(3, 5))},
+    {240, 0, 3, 15, 1, 2, 256, rp(16, st(3, 5)), 512, rp(16, st(3, 5))},
+    {250, 0, 0, 25, 1, 2, 256, rp(10, st(5, 5)), 512, rp(10, 5, 5)},
+    {250, 0, 1, 25, 1, 2, 256, rp(10, st(5, 5)), 512, rp(10, st(5, 5))},
+    {250, 0, 3, 10, 2, 2, 256, rp(10, st(5, 5)), 512, rp(10, st(5, 5))},
+    {256, 0, 0, 16, 2, 2, 512, rp(16, 16), 512, rp(16, 16)},
+    {256, 0, 1, 16, 2, 4, 512, rp(16, 16), 1024, rp(16, 16)},
+    {256, 0, 2, 32, 2, 8, 512, rp(16, 16), 1024, rp(16, 16)},
+};
+__host__ __device__ constexpr SplitDef split_def(int N, int dbl, int v) {
+  for (const SplitDef &s : SPLIT_DEFS)
+    if (s.N == N && s.dbl == dbl && s.v == v) return s;
+  return {N, dbl, v, 0, 1, 1, 64, 0, 64, 0};
+}
+// The first variant of the size with the shape of variant v (variants that coincide share kernels).
+__host__ __device__ constexpr int split_same(int N, int dbl, int v) {
+  const SplitDef a = split_def(N, dbl, v);
+  for (int u = 0; u < v; ++u) {
+    const SplitDef b = split_def(N, dbl, u);
+    if (a.N1 == b.N1 && a.XI == b.XI && a.TT == b.TT && a.slab_nt == b.slab_nt && a.slab_plan == b.slab_plan &&
+        a.pencil_nt == b.pencil_nt && a.pencil_plan == b.pencil_plan)
+      return u;
+  }
+  return v;
+}
+
+// Pencil block order: runs of consecutive x3 tiles per XCD, so that the pieces of one 128-byte
+// row segment are fetched by blocks that share an L2.
+constexpr int PENCIL_XCD_RUN = 128;
+
+template <typename T, int N, int V, int KIND>
+__global__ void __launch_bounds__((split_def(N, PKT<T>, V).slab_nt)) k_slab_t(const LaunchList L) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr SplitDef D = split_def(N, PKT<T>, V);
+  const int e = find_entry(L, blockIdx.x);
+  slab_body<T, N, D.N1, D.slab_nt, D.XI, D.slab_plan, KIND>(L, e, blockIdx.x - L.tile_start[e], smem);
+}
+
+template <typename T, int N, int V>
+__global__ void __launch_bounds__((split_def(N, PKT<T>, V).pencil_nt)) k_pencil_t(const LaunchList L) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr SplitDef D = split_def(N, PKT<T>, V);
+  const int blk = xcd_block_chunked(blockIdx.x, gridDim.x, PENCIL_XCD_RUN);
+  const int e = find_entry(L, blk);
+  pencil_body<T, N, N / D.N1, D.TT, D.pencil_nt, D.XI, D.pencil_plan>(L, e, blk - L.tile_start[e], smem);
+}
+
+template <typename T, int N, int V> void register_split_variant(FftKernels *tab) {
+  constexpr SplitDef D = split_def(N, PKT<T>, V);
+  if constexpr (D.N1 > 0) {
+    constexpr int U = split_same(N, PKT<T>, V);
+    constexpr bool F = sizeof(T) == 4;
+    static_assert(slab_lds_t<T, N, D.N1, D.XI, D.slab_plan>() <= 160 * 1024, "slab tile fits LDS");
+    static_assert(pencil_lds_t<T, N, N / D.N1, D.TT, D.pencil_plan>() <= 160 * 1024, "pencil tile fits LDS");
+    SplitKernels &k = tab[N].split[PKT<T>][V];
+    k.plane_edges = F && (N < 96 || V == 4);
+    static_assert(!(F && (N < 96 || V == 4)) || (D.XI == 1 && plan_of<0, N, false>().n == 2 &&
+                                                  D.N1 == plan_of<0, N, false>().r[1]),
+                  "plane passes at the chunk's edges: the factors of split_row, one plane per group");
+    if constexpr (V != 4) {
+      k.slab[SLAB_REAL] = (const void *)k_slab_t<T, N, U, SLAB_REAL>;
+      k.slab[SLAB_COMPLEX] = (const void *)k_slab_t<T, N, U, SLAB_COMPLEX>;
+    }
+    if constexpr (!F || (N >= 96 && V != 4)) k.slab[SLAB_EDGE] = (const void *)k_slab_t<T, N, U, SLAB_EDGE>;
+    if constexpr (!F || V == 4) k.slab[SLAB_AB] = (const void *)k_slab_t<T, N, U, SLAB_AB>;
+    k.slab_nt = D.slab_nt;
+    k.slab_lds = slab_lds_t<T, N, D.N1, D.XI, D.slab_plan>();
+    k.n1 = D.N1;
+    k.xi = D.XI;
+    k.pencil = (const void *)k_pencil_t<T, N, U>;
+    k.pencil_nt = D.pencil_nt;
+    k.pencil_lds = pencil_lds_t<T, N, N / D.N1, D.TT, D.pencil_plan>();
+    k.pencil_tt = D.TT;
+  }
+}
+template <typename T, int N> void register_split(FftKernels *tab) {
+  register_split_variant<T, N, 0>(tab);
+  register_split_variant<T, N, 1>(tab);
+  register_split_variant<T, N, 2>(tab);
+  register_split_variant<T, N, 3>(tab);
+  register_split_variant<T, N, 4>(tab);
+}
+
+}  // namespace qf
