@@ -135,9 +135,10 @@ typedef struct {
                                      so the results are bit-identical) and halves the memory
                                      traffic per step; a chunk of odd length ends with a
                                      single step. */
-#define QFDTD_F_SPLIT_X2 64u     /* FFT kinds, complex64, sizes with a split-x2 instantiation
-                                     (N = 96, 100, 108, 120, 128, 144, 150, 160, 162, 180, 192,
-                                     200, 216, 240, 250, 256):
+#define QFDTD_F_SPLIT_X2 64u     /* FFT kinds, sizes with a split-x2 instantiation (complex64:
+                                     N = 96, 100, 108, 120, 128, 144, 150, 160, 162, 180, 192,
+                                     200, 216, 240, 250, 256; complex128: these and N = 32, 36, 40,
+                                     48, 50, 54, 60, 64, 72, 80, 90):
                                      the two-pass schedule.  The x2 transform is split four-step
                                      style (N = N1 N2); a slab pass holds N1 rows of one x1 plane
                                      (of two with some tiles, whose rows the state holds
@@ -147,7 +148,7 @@ typedef struct {
                                      rows of a few x3 columns over all x1 and does the other part
                                      of x2 and the x1 transforms around the kinetic factor.  Two
                                      passes over the state per step instead of four (schedule
-                                     autotuning; ignored with QFDTD_F_AB_SCHEME). */
+                                     autotuning; ignored with QFDTD_F_AB_SCHEME in complex64). */
 /* Flag bits 7-8: the split-x2 variant (schedule autotuning), read as QFDTD_SPLIT_VARIANT(flags):
  *   0: the size's default factors x2 = N1 x N2 with its fastest tiles;
  *   1 (QFDTD_F_SPLIT_NARROW): the same factors with other tiles (mostly pencil tiles of fewer
@@ -156,8 +157,8 @@ typedef struct {
  *      (row pieces twice as long as with 4 columns);
  *   3 (QFDTD_F_SPLIT_SWAPPED): the default factors swapped, x2 = N2 x N1 (fewer rows per slab
  *      tile, more per pencil tile), at the sizes where they differ.
- * Tiles do not change results, factors do (FP32 rounding).  A variant a size does not have runs
- * the schedule the other flags select. */
+ * Complex128 has variant 0 and, at some sizes, 1.  Tiles do not change results, factors do (rounding).
+ * A variant a size does not have runs the schedule the other flags select. */
 #define QFDTD_F_SPLIT_NARROW 128u
 #define QFDTD_F_SPLIT_WIDE 256u
 #define QFDTD_F_SPLIT_SWAPPED 384u

@@ -31,6 +31,10 @@ PLANE_LIMIT = {0: 128, 1: 96}      # largest N whose plane fits LDS (complex64 /
 SPLIT_SIZES = {0: (96, 100, 108, 120, 128, 144, 150, 160, 162, 180, 192, 200, 216, 240, 250, 256), 1: ()}
 SPLIT_WIDE_SIZES = {0: (128, 256), 1: ()}    # ... and with the 8-row, 8-column variant
 SPLIT_SWAPPED_SIZES = {0: (96, 108, 120, 128, 144, 150, 160, 162, 180, 192, 200, 216, 240, 250), 1: ()}
+# complex128 split-x2 kernels: every size from 32 up, with a second tile shape (variant 1) at some
+SPLIT_C128_SIZES = (32, 36, 40, 48, 50, 54, 60, 64, 72, 80, 90, 96, 100, 108, 120, 128, 144, 150, 160, 162, 180, 192,
+                    200, 216, 240, 250, 256)
+SPLIT_C128_SECOND = (40, 48, 72, 80, 96, 108, 120, 150, 162, 192, 216)
 _cache: Optional[Dict[str, dict]] = None
 
 
@@ -91,6 +95,21 @@ def candidates(N: int, precision: int, k: int):
     return out
 
 
+def single_shape_split(N: int, precision: int) -> bool:
+    """Sizes whose split-x2 kernels come on top of ``candidates`` (see ``more_candidates``)."""
+    return precision == 1 and N in SPLIT_C128_SIZES
+
+
+def more_candidates(N: int, precision: int, k: int):
+    """Split-x2 candidates of the sizes with one or two tile shapes and no choice of factors."""
+    if not single_shape_split(N, precision):
+        return []
+    variants = [0] + ([1] if N in SPLIT_C128_SECOND else [])
+    groups = [1, 2, 3] if k >= 3 else ([1, 2] if k >= 2 else [1])
+    return [{"rowcol": False, "single_stream": g == 1, "groups": g, "split": True, "split_variant": v}
+            for v in variants for g in groups]
+
+
 def candidate_name(c: dict, N: int = 256) -> str:
     if c.get("split"):
         v = c.get("split_variant", 0)
@@ -147,7 +166,7 @@ def tune(sizes: Iterable[int], precisions: Iterable[int] = (0,), states: Iterabl
                         print("tune N=%d prec=%d k=%d: pinned, kept" % (N, prec, k), flush=True)
                     continue
                 times, cands = {}, {}
-                for c in candidates(N, prec, k):
+                for c in candidates(N, prec, k) + more_candidates(N, prec, k):
                     name = candidate_name(c, N)
                     cands[name] = c
                     times[name] = time_schedule(N, prec, k, c, steps)

@@ -593,6 +593,44 @@ constexpr SplitDef SPLIT_DEFS[] = {
     {256, 0, 0, 16, 2, 2, 512, rp(16, 16), 512, rp(16, 16)},
     {256, 0, 1, 16, 2, 4, 512, rp(16, 16), 1024, rp(16, 16)},
     {256, 0, 2, 32, 2, 8, 512, rp(16, 16), 1024, rp(16, 16)},
+    {32, 1, 0, 8, 2, 4, 128, rp(8, 4), 128, rp(8, 4)},
+    {36, 1, 0, 9, 1, 4, 64, rp(6, 6), 192, rp(6, 6)},
+    {40, 1, 0, 8, 1, 4, 64, rp(8, 5), 192, rp(8, 5)},
+    {40, 1, 1, 8, 1, 2, 64, rp(8, 5), 128, rp(8, 5)},
+    {48, 1, 0, 8, 1, 4, 64, rp(8, 6), 192, rp(6, 8)},
+    {48, 1, 1, 6, 1, 2, 64, rp(6, 8), 128, rp(6, 8)},
+    {50, 1, 0, 10, 1, 2, 128, rp(10, 5), 128, rp(10, 5)},
+    {54, 1, 0, 9, 2, 1, 192, rp(9, 6), 64, rp(9, 6)},
+    {60, 1, 0, 10, 1, 4, 128, rp(6, 10), 256, rp(10, 6)},
+    {64, 1, 0, 8, 2, 2, 128, rp(8, 8), 128, rp(8, 8)},
+    {72, 1, 0, 8, 2, 2, 192, rp(9, 8), 192, rp(8, 9)},
+    {72, 1, 1, 9, 1, 4, 128, rp(8, 9), 320, rp(9, 8)},
+    {80, 1, 0, 8, 2, 4, 192, rp(8, 10), 320, rp(8, 10)},
+    {80, 1, 1, 10, 1, 4, 128, rp(10, 8), 320, rp(10, 8)},
+    {90, 1, 0, 10, 2, 2, 256, rp(10, 9), 192, rp(9, 10)},
+    {96, 1, 0, 8, 2, 2, 192, rp(12, 8), 192, rp(12, 8)},
+    {96, 1, 1, 8, 1, 4, 128, rp(8, 12), 384, rp(8, 12)},
+    {100, 1, 0, 10, 2, 4, 256, rp(10, 10), 448, rp(10, 10)},
+    {108, 1, 0, 9, 1, 2, 128, rp(9, 12), 256, rp(9, 12)},
+    {108, 1, 1, 9, 1, 4, 128, rp(9, 12), 448, rp(9, 12)},
+    {120, 1, 0, 12, 1, 2, 128, rp(12, 10), 256, rp(12, 10)},
+    {120, 1, 1, 8, 1, 4, 128, rp(12, 10), 512, rp(10, 12)},
+    {128, 1, 0, 16, 2, 4, 512, rp(16, 8), 512, rp(16, 8)},
+    {144, 1, 0, 12, 1, 2, 192, rp(16, 9), 320, rp(12, 12)},
+    {150, 1, 0, 15, 1, 2, 256, rp(15, 10), 320, rp(15, 10)},
+    {150, 1, 1, 15, 1, 2, 256, rp(10, 15), 320, rp(15, 10)},
+    {160, 1, 0, 16, 1, 4, 256, rp(16, 10), 640, rp(10, 16)},
+    {162, 1, 0, 9, 2, 1, 384, rp(18, 9), 192, rp(9, 18)},
+    {162, 1, 1, 9, 1, 2, 192, rp(2, 9, 9), 384, rp(9, 18)},
+    {180, 1, 0, 10, 2, 1, 384, rp(18, 10), 192, rp(10, 18)},
+    {192, 1, 0, 12, 2, 1, 384, rp(12, 16), 192, rp(16, 12)},
+    {192, 1, 1, 12, 1, 2, 192, rp(16, 12), 384, rp(12, 16)},
+    {200, 1, 0, 10, 1, 2, 256, rp(5, 8, 5), 448, rp(8, 5, 5)},
+    {216, 1, 0, 12, 2, 2, 448, rp(18, 12), 448, rp(12, 18)},
+    {216, 1, 1, 12, 1, 2, 256, rp(12, 18), 448, rp(12, 18)},
+    {240, 1, 0, 15, 1, 2, 256, rp(15, 16), 512, rp(15, 16)},
+    {250, 1, 0, 10, 2, 1, 512, rp(5, 10, 5), 256, rp(5, 10, 5)},
+    {256, 1, 0, 16, 2, 1, 512, rp(16, 16), 256, rp(16, 16)},
 };
 __host__ __device__ constexpr SplitDef split_def(int N, int dbl, int v) {
   for (const SplitDef &s : SPLIT_DEFS)

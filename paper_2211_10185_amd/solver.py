@@ -101,8 +101,10 @@ class Solver:
         if groups is not None:
             single_stream = int(groups) <= 1
         if single_stream is None or rowcol is None or groups is None or split is None:
-            from .autotune import schedule_for
+            from .autotune import schedule_for, single_shape_split
             tuned = schedule_for(self.N, self.kinetic, self.precision, self.k)
+            if split is None and rowcol is not None and single_shape_split(self.N, self.precision):
+                split = False       # plane or row/column passes were asked for
             single_stream = tuned["single_stream"] if single_stream is None else single_stream
             rowcol = tuned["rowcol"] if rowcol is None else rowcol
             if split is None:

@@ -1,0 +1,45 @@
+"""Complex128 on the split-x2 schedule against the oracle, by steps that start, continue and end a chunk."""
+import numpy as np
+import pytest
+
+import oracle as O
+import synthetic as S
+from compare import energy_errors, wavefunction_errors
+
+pytestmark = pytest.mark.gpu
+
+# N, kinetic, potential, states, A/B update, variant: the smallest and largest sizes, tiles of one and of
+# two planes, 1 to 4 columns, two- and three-stage line plans, one tile per state (N <= 96) or for all
+CASES = [(32, S.K_REL, S.V_CORNELL, 3, False, 0), (36, S.K_NR_P2, S.V_HARMONIC, 1, False, 0),
+         (48, S.K_NR_SIN2, S.V_CORNELL, 2, True, 1), (54, S.K_REL, S.V_CORNELL, 1, False, 0),
+         (90, S.K_NR_P2, S.V_HARMONIC, 2, False, 0), (96, S.K_REL, S.V_CORNELL, 2, True, 0),
+         (100, S.K_NR_SIN2, S.V_CORNELL, 3, False, 0), (128, S.K_NR_P2, S.V_HARMONIC, 2, True, 0),
+         (144, S.K_REL, S.V_CORNELL, 1, False, 0), (150, S.K_NR_SIN2, S.V_HARMONIC, 2, False, 1),
+         (160, S.K_REL, S.V_CORNELL, 2, False, 0), (162, S.K_NR_P2, S.V_CORNELL, 1, True, 1),
+         (200, S.K_NR_SIN2, S.V_HARMONIC, 1, False, 0), (250, S.K_REL, S.V_CORNELL, 1, False, 0)]
+
+
+@pytest.mark.parametrize("N,kind,vkind,k,ab,variant", CASES)
+def test_complex128_split_schedule_matches_oracle(N, kind, vkind, k, ab, variant):
+    from paper_2211_10185_amd.solver import Solver
+    a = 0.05
+    m = 1.5
+    vp = (0.4, 0.2, a / 2) if vkind == S.V_CORNELL else (1.0,)
+    dt = 0.9 * 2 / (np.sqrt(12 / a ** 2 + m * m) - m) if ab and kind == S.K_REL else (m * a * a / 8 if ab else a / 8)
+    p = S.Problem(N=N, a=a, m=m, kinetic=kind, vkind=vkind, vparams=vp, k=k,
+                  vgrid_seed=1031 if vkind == S.V_CORNELL else None, precision=S.PREC_C128, dt=dt,
+                  steps=3, measure_every=2, seed=N, scheme=S.SCHEME_AB if ab else S.SCHEME_SPLIT)
+    init = p.init_states()
+    print("complex128 split schedule, N", N, "kind", kind, "A/B", ab, "variant", variant, flush=True)
+    s = Solver.from_problem(p, split=True, split_variant=variant, groups=1)
+    s.enable_kernel_timing(1)
+    s.set_states(init)
+    s.evolve(p.steps, p.dt)
+    E, psi = s.states()
+    ran = s.kernel_stats(5)[0], s.kernel_stats(6)[0]
+    s.close()
+    assert min(ran) > 0, ran
+    ref = O.solve(p, init=init)
+    # the bounds of every complex128 comparison with the oracle
+    assert np.max(energy_errors(E, ref["energies"])) < 1e-10, (E, ref["energies"])
+    assert np.max(wavefunction_errors(psi, ref["states"], ref["energies"])) < 1e-9
