@@ -135,10 +135,7 @@ typedef struct {
                                      so the results are bit-identical) and halves the memory
                                      traffic per step; a chunk of odd length ends with a
                                      single step. */
-#define QFDTD_F_SPLIT_X2 64u     /* FFT kinds, sizes with a split-x2 instantiation (complex64:
-                                     N = 96, 100, 108, 120, 128, 144, 150, 160, 162, 180, 192,
-                                     200, 216, 240, 250, 256; complex128: these and N = 32, 36, 40,
-                                     48, 50, 54, 60, 64, 72, 80, 90):
+#define QFDTD_F_SPLIT_X2 64u     /* FFT kinds, N >= 32 (every even N = 2^a 3^b 5^c up to 256):
                                      the two-pass schedule.  The x2 transform is split four-step
                                      style (N = N1 N2); a slab pass holds N1 rows of one x1 plane
                                      (of two with some tiles, whose rows the state holds
@@ -157,7 +154,8 @@ typedef struct {
  *      (row pieces twice as long as with 4 columns);
  *   3 (QFDTD_F_SPLIT_SWAPPED): the default factors swapped, x2 = N2 x N1 (fewer rows per slab
  *      tile, more per pencil tile), at the sizes where they differ.
- * Complex128 has variant 0 and, at some sizes, 1.  Tiles do not change results, factors do (rounding).
+ * Complex128 has variant 0 and, at some sizes, 1; complex64 below N = 96 has variant 0, with the
+ * operations of the plane passes (the same bits).  Tiles do not change results, factors do (rounding).
  * A variant a size does not have runs the schedule the other flags select. */
 #define QFDTD_F_SPLIT_NARROW 128u
 #define QFDTD_F_SPLIT_WIDE 256u

@@ -34,6 +34,7 @@ SPLIT_SWAPPED_SIZES = {0: (96, 108, 120, 128, 144, 150, 160, 162, 180, 192, 200,
 # complex128 split-x2 kernels: every size from 32 up, with a second tile shape (variant 1) at some
 SPLIT_C128_SIZES = (32, 36, 40, 48, 50, 54, 60, 64, 72, 80, 90, 96, 100, 108, 120, 128, 144, 150, 160, 162, 180, 192,
                     200, 216, 240, 250, 256)
+SPLIT_SMALL_SIZES = (32, 36, 40, 48, 50, 54, 60, 64, 72, 80, 90)     # complex64, one tile shape
 SPLIT_C128_SECOND = (40, 48, 72, 80, 96, 108, 120, 150, 162, 192, 216)
 _cache: Optional[Dict[str, dict]] = None
 
@@ -97,14 +98,14 @@ def candidates(N: int, precision: int, k: int):
 
 def single_shape_split(N: int, precision: int) -> bool:
     """Sizes whose split-x2 kernels come on top of ``candidates`` (see ``more_candidates``)."""
-    return precision == 1 and N in SPLIT_C128_SIZES
+    return N in (SPLIT_C128_SIZES if precision == 1 else SPLIT_SMALL_SIZES)
 
 
 def more_candidates(N: int, precision: int, k: int):
     """Split-x2 candidates of the sizes with one or two tile shapes and no choice of factors."""
     if not single_shape_split(N, precision):
         return []
-    variants = [0] + ([1] if N in SPLIT_C128_SECOND else [])
+    variants = [0] + ([1] if precision == 1 and N in SPLIT_C128_SECOND else [])
     groups = [1, 2, 3] if k >= 3 else ([1, 2] if k >= 2 else [1])
     return [{"rowcol": False, "single_stream": g == 1, "groups": g, "split": True, "split_variant": v}
             for v in variants for g in groups]

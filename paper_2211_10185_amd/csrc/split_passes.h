@@ -545,6 +545,17 @@ struct SplitDef {
   int N, dbl, v, N1, XI, TT, slab_nt, slab_plan, pencil_nt, pencil_plan;
 };
 constexpr SplitDef SPLIT_DEFS[] = {
+    {32, 0, 0, 4, 1, 4, 64, rp(8, 4), 128, rp(8, 4)},
+    {36, 0, 0, 9, 1, 4, 64, rp(4, 9), 192, rp(4, 9)},
+    {40, 0, 0, 5, 1, 2, 64, rp(8, 5), 128, rp(8, 5)},
+    {48, 0, 0, 3, 1, 2, 64, rp(16, 3), 128, rp(16, 3)},
+    {50, 0, 0, 5, 1, 2, 64, rp(10, 5), 128, rp(10, 5)},
+    {54, 0, 0, 9, 1, 2, 64, rp(6, 9), 128, rp(6, 9)},
+    {60, 0, 0, 10, 1, 4, 64, rp(6, 10), 256, rp(6, 10)},
+    {64, 0, 0, 8, 1, 8, 64, rp(8, 8), 512, rp(8, 8)},
+    {72, 0, 0, 9, 1, 8, 128, rp(8, 9), 576, rp(8, 9)},
+    {80, 0, 0, 5, 1, 4, 128, rp(16, 5), 320, rp(16, 5)},
+    {90, 0, 0, 9, 1, 2, 128, rp(10, 9), 192, rp(10, 9)},
     {96, 0, 0, 16, 1, 4, 128, rp(16, 6), 384, rp(16, 6)},
     {96, 0, 1, 16, 1, 8, 128, rp(16, 6), 768, rp(16, 6)},
     {96, 0, 3, 6, 2, 4, 192, rp(16, 6), 384, rp(16, 6)},

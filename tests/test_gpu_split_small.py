@@ -1,0 +1,75 @@
+"""Complex64 below N = 96 on the split-x2 schedule: the bits of the plane schedule.
+
+The x2 factors of these sizes are those of the plane pass, and chunks start and end with plane passes,
+so every state goes through the same operations in the same order.
+"""
+import numpy as np
+import pytest
+
+import synthetic as S
+
+pytestmark = pytest.mark.gpu
+
+SMALL = (32, 36, 40, 48, 50, 54, 60, 64, 72, 80, 90)
+
+
+def problem(N, kind, vkind, k, K, scheme=S.SCHEME_SPLIT):
+    a = 0.05
+    m = 1.5
+    vp = (0.4, 0.2, a / 2) if vkind == S.V_CORNELL else (1.0,)
+    dt = a / 8
+    if scheme == S.SCHEME_AB:
+        dt = 0.9 * 2 / (np.sqrt(12 / a ** 2 + m * m) - m) if kind == S.K_REL else m * a * a / 8
+    return S.Problem(N=N, a=a, m=m, kinetic=kind, vkind=vkind, vparams=vp, k=k, scheme=scheme,
+                     vgrid_seed=1031 if vkind == S.V_CORNELL else None, precision=S.PREC_C64, dt=dt,
+                     steps=7, measure_every=K, seed=N)
+
+
+def run(p, init, **kw):
+    from paper_2211_10185_amd.solver import Solver
+    s = Solver.from_problem(p, **kw)
+    s.enable_kernel_timing(1)
+    s.set_states(init)
+    s.evolve(p.steps, p.dt)
+    out = s.states()
+    ran = [s.kernel_stats(c)[0] for c in range(7)]
+    s.close()
+    return out, ran
+
+
+@pytest.mark.parametrize("N,kind,vkind,k,K", [(N, (S.K_REL, S.K_NR_P2, S.K_NR_SIN2)[i % 3],
+                                               (S.V_CORNELL, S.V_HARMONIC)[i % 2], 1 + i % 3, (3, 1, 5)[i % 3])
+                                              for i, N in enumerate(SMALL)])
+def test_small_split_schedule_has_the_bits_of_the_plane_schedule(N, kind, vkind, k, K):
+    # real and complex factors, one to three states, chunks of one step (both pencil edges in one pass),
+    # of 3 and 1, and of 5 and 2
+    p = problem(N, kind, vkind, k, K)
+    init = p.init_states()
+    print("small split, N", N, "kind", kind, "k", k, "K", K, flush=True)
+    (E, psi), ran = run(p, init, split=True, groups=1)
+    (Ep, psip), ranp = run(p, init, split=False, rowcol=False, groups=1)
+    assert ran[6] > 0 and ranp[6] == 0 and (K == 1 or ran[5] > 0), (ran, ranp)
+    assert np.array_equal(E, Ep) and np.array_equal(psi, psip)
+
+
+def test_small_split_batch_groups_and_graphs_keep_the_bits():
+    from paper_2211_10185_amd.solver import Solver, batch_evolve
+    probs = [problem(64, S.K_NR_SIN2, S.V_HARMONIC, 3, 3), problem(48, S.K_REL, S.V_CORNELL, 1, 5),
+             problem(64, S.K_NR_P2, S.V_CORNELL, 2, 2)]
+    print("small split: batch, state groups, graph replays", flush=True)
+    alone = [run(p, p.init_states(), split=False, rowcol=False, groups=1)[0] for p in probs]
+    for g in (2, 3):
+        s = Solver.from_problem(probs[0], split=True, groups=g)
+        s.set_states(probs[0].init_states())
+        for n in (3, 3, 1):
+            s.evolve(n, probs[0].dt)
+        assert np.array_equal(s.states()[1], alone[0][1])
+        s.close()
+    ss = [Solver.from_problem(p, split=True) for p in probs]
+    for s, p in zip(ss, probs):
+        s.set_states(p.init_states())
+    batch_evolve(ss, [p.steps for p in probs], [p.dt for p in probs])
+    for s, (Ea, psia) in zip(ss, alone):
+        E, psi = s.states()
+        s.close()
+        assert np.array_equal(E, Ea) and np.array_equal(psi, psia)
