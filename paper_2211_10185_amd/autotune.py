@@ -77,6 +77,29 @@ def schedule_for(N: int, kinetic: int, precision: int, k: int) -> dict:
             "split_variant": int(e.get("split_variant", 0))}
 
 
+def ab_schedule(N: int, precision: int, k: int) -> Optional[dict]:
+    """Split-x2 schedule of the A/B update of an FFT kinetic term, None where the other schedules stay.
+
+    Measured (us per step, best plane or row/column schedule against split-x2; one state / three):
+    complex64 32: 16.0 -> 12.9 / 16.4 -> 13.3, 64: 20.9 -> 16.2 / 25.7 -> 21.9, 90: 41.9 -> 29.9 /
+    58.6 -> 46.0, 128: 45.1 -> 34.4 / 91.4 -> 69.4 (above 128 the row/column passes stay: the split-x2
+    factors would change the FP32 results); complex128 64: 24.7 -> 17.3 / 34.8 -> 29.8, 128: 71.0 ->
+    45.7 / 187 -> 108, 160: 137 -> 104 / 413 -> 318, 240: 549 -> 477 / 1741 -> 1342, 256: 606 -> 584 /
+    1869 -> 1615, but 216: 366 -> 368 and 250: 616 -> 636 with one state.  Groups of states on their own
+    streams win where a pass of one state does not fill the chip but its launches are long enough."""
+    if precision == 0:
+        if N not in SPLIT_SMALL_SIZES + (96, 100, 108, 120, 128):
+            return None
+        groups = 1 if N < 80 or N == 108 else min(k, 3)
+        variant = 0
+    else:
+        if N not in SPLIT_C128_SIZES or (k == 1 and N in (216, 250)):
+            return None
+        groups = min(k, 3) if N in (90, 96, 100, 108, 120, 128, 160) else 1
+        variant = 1 if N in (162, 192) else 0
+    return {"rowcol": False, "single_stream": groups == 1, "groups": groups, "split": True, "split_variant": variant}
+
+
 def candidates(N: int, precision: int, k: int):
     out = []
     plane_ok = N <= PLANE_LIMIT[precision]

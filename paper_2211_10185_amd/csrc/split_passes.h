@@ -546,31 +546,47 @@ struct SplitDef {
 };
 constexpr SplitDef SPLIT_DEFS[] = {
     {32, 0, 0, 4, 1, 4, 64, rp(8, 4), 128, rp(8, 4)},
+    {32, 0, 4, 4, 1, 4, 64, rp(8, 4), 128, rp(8, 4)},
     {36, 0, 0, 9, 1, 4, 64, rp(4, 9), 192, rp(4, 9)},
+    {36, 0, 4, 9, 1, 4, 64, rp(4, 9), 192, rp(4, 9)},
     {40, 0, 0, 5, 1, 2, 64, rp(8, 5), 128, rp(8, 5)},
+    {40, 0, 4, 5, 1, 2, 64, rp(8, 5), 128, rp(8, 5)},
     {48, 0, 0, 3, 1, 2, 64, rp(16, 3), 128, rp(16, 3)},
+    {48, 0, 4, 3, 1, 2, 64, rp(16, 3), 128, rp(16, 3)},
     {50, 0, 0, 5, 1, 2, 64, rp(10, 5), 128, rp(10, 5)},
+    {50, 0, 4, 5, 1, 2, 64, rp(10, 5), 128, rp(10, 5)},
     {54, 0, 0, 9, 1, 2, 64, rp(6, 9), 128, rp(6, 9)},
+    {54, 0, 4, 9, 1, 2, 64, rp(6, 9), 128, rp(6, 9)},
     {60, 0, 0, 10, 1, 4, 64, rp(6, 10), 256, rp(6, 10)},
+    {60, 0, 4, 10, 1, 4, 64, rp(6, 10), 256, rp(6, 10)},
     {64, 0, 0, 8, 1, 8, 64, rp(8, 8), 512, rp(8, 8)},
+    {64, 0, 4, 8, 1, 8, 64, rp(8, 8), 512, rp(8, 8)},
     {72, 0, 0, 9, 1, 8, 128, rp(8, 9), 576, rp(8, 9)},
+    {72, 0, 4, 9, 1, 8, 128, rp(8, 9), 576, rp(8, 9)},
     {80, 0, 0, 5, 1, 4, 128, rp(16, 5), 320, rp(16, 5)},
+    {80, 0, 4, 5, 1, 4, 128, rp(16, 5), 320, rp(16, 5)},
     {90, 0, 0, 9, 1, 2, 128, rp(10, 9), 192, rp(10, 9)},
+    {90, 0, 4, 9, 1, 2, 128, rp(10, 9), 192, rp(10, 9)},
     {96, 0, 0, 16, 1, 4, 128, rp(16, 6), 384, rp(16, 6)},
     {96, 0, 1, 16, 1, 8, 128, rp(16, 6), 768, rp(16, 6)},
     {96, 0, 3, 6, 2, 4, 192, rp(16, 6), 384, rp(16, 6)},
+    {96, 0, 4, 6, 1, 4, 128, rp(16, 6), 384, rp(16, 6)},
     {100, 0, 0, 10, 1, 4, 128, rp(10, 10), 448, rp(10, 10)},
     {100, 0, 1, 10, 2, 4, 256, rp(10, 10), 448, rp(10, 10)},
+    {100, 0, 4, 10, 1, 4, 128, rp(10, 10), 448, rp(10, 10)},
     {108, 0, 0, 12, 1, 4, 192, rp(12, 9), 448, rp(12, 9)},
     {108, 0, 1, 12, 2, 2, 320, rp(12, 9), 256, rp(12, 9)},
     {108, 0, 3, 9, 2, 4, 256, rp(12, 9), 448, rp(12, 9)},
+    {108, 0, 4, 9, 1, 4, 128, rp(12, 9), 448, rp(12, 9)},
     {120, 0, 0, 12, 1, 4, 128, rp(8, 15), 512, rp(8, 15)},
     {120, 0, 1, 12, 2, 4, 256, rp(8, 15), 512, rp(8, 15)},
     {120, 0, 3, 10, 2, 4, 256, rp(8, 15), 512, rp(8, 15)},
+    {120, 0, 4, 15, 1, 4, 128, rp(8, 15), 512, rp(8, 15)},
     {128, 0, 0, 16, 2, 4, 256, rp(16, 8), 512, rp(16, 8)},
     {128, 0, 1, 16, 1, 4, 128, rp(16, 8), 512, rp(16, 8)},
     {128, 0, 2, 16, 2, 8, 256, rp(16, 8), 1024, rp(16, 8)},
     {128, 0, 3, 8, 2, 4, 256, rp(16, 8), 512, rp(16, 8)},
+    {128, 0, 4, 8, 1, 4, 128, rp(16, 8), 512, rp(16, 8)},
     {144, 0, 0, 16, 1, 4, 256, rp(16, 9), 576, rp(16, 9)},
     {144, 0, 1, 16, 2, 2, 512, rp(16, 9), 320, rp(16, 9)},
     {144, 0, 3, 9, 2, 2, 192, rp(16, 9), 320, rp(16, 9)},

@@ -73,3 +73,24 @@ def test_small_split_batch_groups_and_graphs_keep_the_bits():
         E, psi = s.states()
         s.close()
         assert np.array_equal(E, Ea) and np.array_equal(psi, psia)
+
+
+@pytest.mark.parametrize("N,kind,vkind,k,K", [(N, (S.K_NR_SIN2, S.K_REL, S.K_NR_P2)[i % 3],
+                                               (S.V_HARMONIC, S.V_CORNELL)[i % 2], 1 + i % 3, (5, 3, 1)[i % 3])
+                                              for i, N in enumerate((32, 50, 64, 90, 96, 100, 108, 120, 128))])
+def test_ab_split_schedule_has_the_bits_of_the_plane_schedule(N, kind, vkind, k, K):
+    p = problem(N, kind, vkind, k, K, S.SCHEME_AB)
+    init = p.init_states()
+    print("A/B split, N", N, "kind", kind, "k", k, "K", K, flush=True)
+    (Ep, psip), ranp = run(p, init, split=False, rowcol=False, groups=1)
+    for g in range(1, k + 1):
+        (E, psi), ran = run(p, init, split=True, groups=g)
+        assert ran[6] > 0 and ranp[6] == 0 and (K == 1 or ran[5] > 0), (ran, ranp)
+        assert np.array_equal(E, Ep) and np.array_equal(psi, psip)
+    # state groups on their own streams (launch timing keeps them on one)
+    from paper_2211_10185_amd.solver import Solver
+    s = Solver.from_problem(p, split=True, groups=k)
+    s.set_states(init)
+    s.evolve(p.steps, p.dt)
+    assert np.array_equal(s.states()[1], psip)
+    s.close()
