@@ -519,8 +519,9 @@ __global__ void __launch_bounds__(RED_THREADS) k_parity(const LaunchList L) {
 
 // ------------------------------------------------------------- reductions
 
+// the block's sums of NV values per thread, value q to out[q stride]
 template <int NV>
-__device__ __forceinline__ void block_reduce_store(double (&acc)[NV], double *out) {
+__device__ __forceinline__ void block_reduce_store(double (&acc)[NV], double *out, size_t stride) {
   __shared__ double red[RED_THREADS / 64][NV > 0 ? NV : 1];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
 #pragma unroll
@@ -535,12 +536,12 @@ __device__ __forceinline__ void block_reduce_store(double (&acc)[NV], double *ou
     double v = 0.0;
 #pragma unroll
     for (int ww = 0; ww < RED_THREADS / 64; ++ww) v += red[ww][q];
-    out[q] = v;
+    out[(size_t)q * stride] = v;
   }
 }
 
 // Gram partials G_ij = sum conj(psi_i) psi_j, i <= j, over block blk's range of the N3 sites
-// (nblk blocks), written to out[0 .. 2 NP).
+// (nblk blocks), sum q of the 2 NP written to out[q nblk].
 template <typename T, int KS>
 __device__ __forceinline__ void gram_partials(const C<T> *src, size_t N3, int nblk, int blk, double *out) {
   constexpr int NP = KS * (KS + 1) / 2;
@@ -549,6 +550,7 @@ __device__ __forceinline__ void gram_partials(const C<T> *src, size_t N3, int nb
   double acc[2 * NP];
 #pragma unroll
   for (int q = 0; q < 2 * NP; ++q) acc[q] = 0.0;
+#pragma unroll 2
   for (size_t x = lo + threadIdx.x; x < hi; x += RED_THREADS) {
     double2 v[KS];
 #pragma unroll
@@ -565,7 +567,7 @@ __device__ __forceinline__ void gram_partials(const C<T> *src, size_t N3, int nb
         acc[2 * p + 1] += v[i].x * v[j].y - v[i].y * v[j].x;
       }
   }
-  block_reduce_store<2 * NP>(acc, out);
+  block_reduce_store<2 * NP>(acc, out, nblk);
 }
 
 template <typename T, int KS>
@@ -576,64 +578,61 @@ __global__ void __launch_bounds__(RED_THREADS) k_gram(const LaunchList L) {
   const int blk = blockIdx.x - L.tile_start[e];
   const size_t N3 = (size_t)d.N * d.N * d.N;
   const C<T> *src = (const C<T> *)((mode & M_SWAP) ? d.alt : d.psi);
-  gram_partials<T, KS>(src, N3, d.nblk_red, blk, d.partials + (size_t)blk * (2 * MAX_PAIRS));
+  gram_partials<T, KS>(src, N3, d.nblk_red, blk, d.partials + blk);
 }
 
 // The same partials for k states given by a plain pointer ([k][n] interleaved complex).
 template <typename T, int KS>
 __global__ void __launch_bounds__(RED_THREADS) k_gram_flat(const C<T> *psi, size_t n, int nblk, double *partials) {
-  gram_partials<T, KS>(psi, n, nblk, blockIdx.x, partials + (size_t)blockIdx.x * (2 * MAX_PAIRS));
+  gram_partials<T, KS>(psi, n, nblk, blockIdx.x, partials + blockIdx.x);
 }
 
 __device__ __forceinline__ int pair_index(int i, int j, int KS) { return i * KS - i * (i - 1) / 2 + (j - i); }
 
-// Sums of columns q0 .. q0 + nq - 1 (nq <= SUMQ) of a [nb][2*MAX_PAIRS] partials array over its
-// nb rows, all at once, with all threads of the block: thread t adds rows t, t + RED_THREADS,
-// ... in order, then a fixed-shape tree halves the thread sums.  The order of additions of a
-// column never changes (and does not depend on nq or q0); the loads of all the columns are in
-// flight together.  Thread j < nq writes the sum of column q0 + j to out[j].
-constexpr int SUMQ = 12;
-__device__ void block_sum_columns(const double *part, int nb, int q0, int nq, double *out) {
-  __shared__ double red[SUMQ][RED_THREADS];
-  double s[SUMQ];
+// Sums of the nq rows of nb partials (row q at part + q nb) into out[q], with all waves of the block: wave
+// w takes rows w, w + waves, ..., each lane adds elements lane, lane + 64, ... in order (eight loads in
+// flight), then a fixed shuffle tree.  The order of a row's additions never changes (and does not
+// depend on nq).  Bound by the latency of the loads: a row per wave, coalesced and several in flight (with
+// the sums of a block next to each other and all threads on every sum, the final energies of 128^3 x 3
+// states took 26 us instead of 4).
+constexpr int FIN_THREADS = 1024;
+__device__ __forceinline__ double row_sum(const double *row, int nb) {
+  const int lane = threadIdx.x & 63;
+  double v = 0.0;
+  for (int b0 = 0; b0 < nb; b0 += 512) {
+    double x[8];
 #pragma unroll
-  for (int j = 0; j < SUMQ; ++j) s[j] = 0.0;
-  for (int b = threadIdx.x; b < nb; b += RED_THREADS) {
-    const double *row = part + (size_t)b * (2 * MAX_PAIRS) + q0;
-#pragma unroll
-    for (int j = 0; j < SUMQ; ++j)
-      if (j < nq) s[j] += row[j];
-  }
-#pragma unroll
-  for (int j = 0; j < SUMQ; ++j)
-    if (j < nq) red[j][threadIdx.x] = s[j];
-  __syncthreads();
-  for (int w = RED_THREADS / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) {
-#pragma unroll
-      for (int j = 0; j < SUMQ; ++j)
-        if (j < nq) red[j][threadIdx.x] += red[j][threadIdx.x + w];
+    for (int u = 0; u < 8; ++u) {
+      const int b = b0 + u * 64 + lane;
+      x[u] = b < nb ? row[b] : 0.0;
     }
-    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v += x[u];
   }
-  if ((int)threadIdx.x < nq) out[threadIdx.x] = red[threadIdx.x][0];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+__device__ void block_sum_rows(const double *part, int nb, int nq, double *out) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  for (int q = w; q < nq; q += (int)blockDim.x / 64) {
+    const double v = row_sum(part + (size_t)q * nb, nb);
+    if (lane == 0) out[q] = v;
+  }
   __syncthreads();
 }
 
 // The Gram matrix itself: fixed-order sums of the partials into out[nq] (one block).
-__global__ void __launch_bounds__(RED_THREADS) k_gram_sum(const double *partials, int nb, int nq, double *out) {
-  for (int q0 = 0; q0 < nq; q0 += SUMQ)
-    block_sum_columns(partials, nb, q0, nq - q0 < SUMQ ? nq - q0 : SUMQ, out + q0);
+__global__ void __launch_bounds__(FIN_THREADS) k_gram_sum(const double *partials, int nb, int nq, double *out) {
+  block_sum_rows(partials, nb, nq, out);
 }
 
-// The k x k Gram matrix from nb rows of partials: the pair sums in the fixed order of
+// The k x k Gram matrix from the partials of nb blocks: the pair sums in the fixed order of
 // k_gram_sum, then the Hermitian matrix G[i][j] = (re, im), row-major, as qfdtd_gram_matrix
 // returns it.
-__global__ void __launch_bounds__(RED_THREADS) k_gram_full(const double *partials, int nb, int KS, double *G) {
+__global__ void __launch_bounds__(FIN_THREADS) k_gram_full(const double *partials, int nb, int KS, double *G) {
   __shared__ double Gs[MAX_PAIRS * 2];
-  const int NP = KS * (KS + 1) / 2;
-  for (int q0 = 0; q0 < 2 * NP; q0 += SUMQ)
-    block_sum_columns(partials, nb, q0, 2 * NP - q0 < SUMQ ? 2 * NP - q0 : SUMQ, Gs + q0);
+  block_sum_rows(partials, nb, KS * (KS + 1), Gs);
   for (int t = threadIdx.x; t < KS * KS; t += blockDim.x) {
     const int i = t / KS, j = t - (t / KS) * KS;
     const int p = i <= j ? pair_index(i, j, KS) : pair_index(j, i, KS);
@@ -642,67 +641,57 @@ __global__ void __launch_bounds__(RED_THREADS) k_gram_full(const double *partial
   }
 }
 
-// Sum the partials (fixed order), Cholesky G = R^H R per sector, coef = R^{-1}.
-__global__ void __launch_bounds__(RED_THREADS) k_gram_finalize(const LaunchList L) {
+// Sum the partials (fixed order), Cholesky G = R^H R per sector, coef = R^{-1}.  One thread does the
+// factorisation, so what it touches by run-time index (states of a sector) is in LDS: scratch memory
+// costs a trip to the caches per access.  With the sums above: 22 -> 7 us at 128^3 x 3 states.
+__global__ void __launch_bounds__(FIN_THREADS) k_gram_finalize(const LaunchList L) {
   const int e = blockIdx.x;
   const PassDesc &d = *(const PassDesc *)L.descp[e];
   const int KS = d.k;
-  const int NP = KS * (KS + 1) / 2;
   __shared__ double G[MAX_PAIRS * 2];
-  for (int q0 = 0; q0 < 2 * NP; q0 += SUMQ)
-    block_sum_columns(d.partials, d.nblk_red, q0, 2 * NP - q0 < SUMQ ? 2 * NP - q0 : SUMQ, G + q0);
-  // the factor and its inverse in LDS: one thread works on them with indices known only at run
-  // time (the states of each sector), which would otherwise put them in scratch memory
   __shared__ double Rr[MAX_STATES][MAX_STATES], Ri[MAX_STATES][MAX_STATES];
   __shared__ double Xr[MAX_STATES][MAX_STATES], Xi[MAX_STATES][MAX_STATES];
-  if (threadIdx.x != 0) return;
-  for (int i = 0; i < MAX_STATES; ++i)
-    for (int j = 0; j < MAX_STATES; ++j) { Rr[i][j] = Ri[i][j] = Xr[i][j] = Xi[i][j] = 0.0; }
-  int bad = 0;
+  __shared__ double rdiag[MAX_STATES];
+  __shared__ int sec[MAX_STATES];
+  const int z = (int)threadIdx.x - (FIN_THREADS - MAX_STATES * MAX_STATES);
+  if (z >= 0) {
+    const int i = z / MAX_STATES, j = z % MAX_STATES;
+    Rr[i][j] = Ri[i][j] = Xr[i][j] = Xi[i][j] = 0.0;
+    if (i == 0) sec[j] = d.sector[j];
+  }
+  block_sum_rows(d.partials, d.nblk_red, KS * (KS + 1), G);
   const bool residuals = L.aux[e] == 1;   // only report the diagonal of R (see below)
-  double rdiag[MAX_STATES] = {0, 0, 0, 0, 0, 0, 0, 0};
-  bool done[MAX_STATES] = {false, false, false, false, false, false, false, false};
-  for (int first = 0; first < KS; ++first) {
-    if (done[first]) continue;
-    int idx[MAX_STATES], n = 0;
-    for (int s = first; s < KS; ++s)
-      if (d.sector[s] == d.sector[first]) { idx[n++] = s; done[s] = true; }
-    for (int jj = 0; jj < n; ++jj) {
-      const int j = idx[jj];
-      for (int ii = 0; ii < jj; ++ii) {
-        const int i = idx[ii];
+  if (threadIdx.x == 0) {
+    int bad = 0;
+    // column j of R and of X = R^{-1} (upper triangular within the states of a sector)
+    for (int j = 0; j < KS; ++j) {
+      const int sj = sec[j];
+      double dd = G[2 * pair_index(j, j, KS)];
+      const double gjj = dd;
+      for (int i = 0; i < j; ++i) {
+        if (sec[i] != sj) continue;
         const int p = pair_index(i, j, KS);
         double sr = G[2 * p], si = G[2 * p + 1];
-        for (int ll = 0; ll < ii; ++ll) {
-          const int l = idx[ll];
+        for (int l = 0; l < i; ++l) {
+          if (sec[l] != sj) continue;
           // conj(R_li) R_lj
           sr -= Rr[l][i] * Rr[l][j] + Ri[l][i] * Ri[l][j];
           si -= Rr[l][i] * Ri[l][j] - Ri[l][i] * Rr[l][j];
         }
         Rr[i][j] = sr / Rr[i][i];
         Ri[i][j] = si / Rr[i][i];
-      }
-      const int p = pair_index(j, j, KS);
-      double dd = G[2 * p];
-      const double gjj = dd;
-      for (int ll = 0; ll < jj; ++ll) {
-        const int l = idx[ll];
-        dd -= Rr[l][j] * Rr[l][j] + Ri[l][j] * Ri[l][j];
+        dd -= Rr[i][j] * Rr[i][j] + Ri[i][j] * Ri[i][j];
       }
       rdiag[j] = (dd > 0.0 && isfinite(dd)) ? sqrt(dd) : 0.0;
       if (!(gjj > 0.0) || !isfinite(gjj) || !(dd > 1e-24 * gjj) || !isfinite(dd)) { bad = 1; dd = 1.0; }
       Rr[j][j] = sqrt(dd);
       Ri[j][j] = 0.0;
-    }
-    // X = R^{-1} (upper triangular within the sector)
-    for (int jj = 0; jj < n; ++jj) {
-      const int j = idx[jj];
       Xr[j][j] = 1.0 / Rr[j][j];
-      for (int ii = jj - 1; ii >= 0; --ii) {
-        const int i = idx[ii];
+      for (int i = j - 1; i >= 0; --i) {
+        if (sec[i] != sj) continue;
         double sr = 0.0, si = 0.0;
-        for (int ll = ii + 1; ll <= jj; ++ll) {
-          const int l = idx[ll];
+        for (int l = i + 1; l <= j; ++l) {
+          if (sec[l] != sj) continue;
           sr += Rr[i][l] * Xr[l][j] - Ri[i][l] * Xi[l][j];
           si += Rr[i][l] * Xi[l][j] + Ri[i][l] * Xr[l][j];
         }
@@ -710,19 +699,20 @@ __global__ void __launch_bounds__(RED_THREADS) k_gram_finalize(const LaunchList 
         Xi[i][j] = -si / Rr[i][i];
       }
     }
+    if (bad && !residuals) d.energy[2 * MAX_STATES] = 1.0;
   }
+  __syncthreads();
+  const int i = (int)threadIdx.x / MAX_STATES, j = (int)threadIdx.x % MAX_STATES;
   if (residuals) {
     // R_jj = the norm of state j after projection against the earlier states of its sector
     // (G = R^H R per sector); qfdtd_gram_residuals reads it, nothing else changes
-    for (int j = 0; j < KS; ++j) d.energy[ENERGY_RDIAG + j] = rdiag[j];
+    if (i == 0 && j < KS) d.energy[ENERGY_RDIAG + j] = d.h_energy[3 * MAX_STATES + j] = rdiag[j];
     return;
   }
-  for (int i = 0; i < KS; ++i)
-    for (int j = 0; j < KS; ++j) {
-      d.coef[(i * MAX_STATES + j) * 2] = Xr[i][j];
-      d.coef[(i * MAX_STATES + j) * 2 + 1] = Xi[i][j];
-    }
-  if (bad) d.energy[2 * MAX_STATES] = 1.0;
+  if (i < KS && j < KS) {
+    d.coef[(i * MAX_STATES + j) * 2] = Xr[i][j];
+    d.coef[(i * MAX_STATES + j) * 2 + 1] = Xi[i][j];
+  }
 }
 
 // psi_j <- sum_{i <= j} src_i coef_ij  (in place when src is psi)
@@ -760,55 +750,73 @@ __global__ void __launch_bounds__(RED_THREADS) k_apply(const LaunchList L) {
 
 // ------------------------------------------------------------- energies
 
-// per state: |psi|^2, V |psi|^2 (re, im) and, for H_K^(0), conj(psi) H_K psi (re, im)
-template <typename T, int KS>
-__global__ void __launch_bounds__(RED_THREADS) k_energy_partials(const LaunchList L) {
-  const int e = find_entry(L, blockIdx.x);
-  const PassDesc &d = *(const PassDesc *)L.descp[e];
-  const int blk = blockIdx.x - L.tile_start[e];
-  const int N = d.N;
-  const size_t N3 = (size_t)N * N * N;
-  const C<T> *src = (const C<T> *)d.psi;
-  const size_t chunk = (N3 + d.nblk_red - 1) / d.nblk_red;
-  const size_t lo = blk * chunk, hi = (lo + chunk < N3) ? lo + chunk : N3;
-  const bool fdtd = d.kin == KIN_FDTD;
+// Sums over sites of one state per block: |psi|^2, V |psi|^2 (re, im) and, for H_K^(0) (NQ = 5),
+// conj(psi) H_K psi (re, im).  Block t of a member: state t mod k, range t / k of the sites.  Logical blocks go
+// to the XCDs in one contiguous run each, so that the states of a range (which share V) and the planes
+// above and below it meet in one L2.  H_K^(0), bound by the latency of its loads, three complex64 states:
+// 57 -> 38 us at 128^3 (one state per block, neighbour loads without branches), 50 -> 11 us at 64^3
+// (four times the blocks).
+template <typename T, int NQ>
+__device__ __forceinline__ void energy_sums(const PassDesc &d, int t) {
+  const int blk = t / d.k, s = t - blk * d.k;
+  // site indices in 32 bits: N^3 <= 512^3 = 2^27
+  const uint32_t N = (uint32_t)d.N, N2 = N * N, N3 = N2 * N;
+  const C<T> *__restrict__ sp = (const C<T> *)d.psi + (size_t)s * N3;
+  const uint32_t chunk = (N3 + d.en_nb - 1) / d.en_nb;
+  const uint32_t lo = blk * chunk, hi = lo + chunk < N3 ? lo + chunk : N3;
   const double kc = 1.0 / (2.0 * d.m * d.a * d.a);
-  double acc[5 * KS];
+  const bool vc = d.vcomplex != 0;
+  double acc[NQ];
 #pragma unroll
-  for (int q = 0; q < 5 * KS; ++q) acc[q] = 0.0;
-  for (size_t x = lo + threadIdx.x; x < hi; x += RED_THREADS) {
+  for (int q = 0; q < NQ; ++q) acc[q] = 0.0;
+#pragma unroll 2
+  for (uint32_t x = lo + threadIdx.x; x < hi; x += RED_THREADS) {
     double vr, vi = 0.0;
-    if (d.vcomplex) { vr = d.v64[2 * x]; vi = d.v64[2 * x + 1]; }
+    if (vc) { vr = d.v64[2 * (size_t)x]; vi = d.v64[2 * (size_t)x + 1]; }
     else vr = d.v64[x];
-    const int i3 = (int)(x % N), i2 = (int)((x / N) % N), i1 = (int)(x / ((size_t)N * N));
+    const C<T> u = sp[x];
+    const double ur = u.x, ui = u.y;
+    const double n2 = ur * ur + ui * ui;
+    acc[0] += n2;
+    acc[1] += vr * n2;
+    acc[2] += vi * n2;
+    if constexpr (NQ == 5) {
+      const uint32_t r = x / N, i3 = x - r * N, i1 = r / N, i2 = r - i1 * N;
+      // neighbours outside the lattice are zero; their loads take the site itself, so that all six are
+      // issued without a branch
+      const bool in[6] = {i3 > 0, i3 < N - 1, i2 > 0, i2 < N - 1, i1 > 0, i1 < N - 1};
+      C<T> w[6];
+      w[0] = sp[in[0] ? x - 1 : x];
+      w[1] = sp[in[1] ? x + 1 : x];
+      w[2] = sp[in[2] ? x - N : x];
+      w[3] = sp[in[3] ? x + N : x];
+      w[4] = sp[in[4] ? x - N2 : x];
+      w[5] = sp[in[5] ? x + N2 : x];
+      double lr = -6.0 * ur, li = -6.0 * ui;
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      const C<T> *sp = src + (size_t)s * N3;
-      const C<T> u = sp[x];
-      const double ur = u.x, ui = u.y;
-      const double n2 = ur * ur + ui * ui;
-      acc[5 * s] += n2;
-      acc[5 * s + 1] += vr * n2;
-      acc[5 * s + 2] += vi * n2;
-      if (fdtd) {
-        double lr = -6.0 * ur, li = -6.0 * ui;
-        C<T> w;
-        if (i3 > 0) { w = sp[x - 1]; lr += w.x; li += w.y; }
-        if (i3 < N - 1) { w = sp[x + 1]; lr += w.x; li += w.y; }
-        if (i2 > 0) { w = sp[x - N]; lr += w.x; li += w.y; }
-        if (i2 < N - 1) { w = sp[x + N]; lr += w.x; li += w.y; }
-        if (i1 > 0) { w = sp[x - (size_t)N * N]; lr += w.x; li += w.y; }
-        if (i1 < N - 1) { w = sp[x + (size_t)N * N]; lr += w.x; li += w.y; }
-        // conj(u) * (-L u) / (2 m a^2)
-        acc[5 * s + 3] += -kc * (ur * lr + ui * li);
-        acc[5 * s + 4] += -kc * (ur * li - ui * lr);
+      for (int q = 0; q < 6; ++q) {
+        lr += in[q] ? (double)w[q].x : 0.0;
+        li += in[q] ? (double)w[q].y : 0.0;
       }
+      // conj(u) * (-L u) / (2 m a^2)
+      acc[3] += -kc * (ur * lr + ui * li);
+      acc[4] += -kc * (ur * li - ui * lr);
     }
   }
-  block_reduce_store<5 * KS>(acc, d.partials + (size_t)blk * (2 * MAX_PAIRS));
+  block_reduce_store<NQ>(acc, d.partials + (size_t)s * NQ * d.en_nb + blk, d.en_nb);
+}
+template <typename T>
+__global__ void __launch_bounds__(RED_THREADS) k_energy_partials(const LaunchList L) {
+  const int b = xcd_block(blockIdx.x, gridDim.x);
+  const int e = find_entry(L, b);
+  const PassDesc &d = *(const PassDesc *)L.descp[e];
+  const int t = b - L.tile_start[e];
+  if (d.en_nq == 5) energy_sums<T, 5>(d, t);
+  else energy_sums<T, 3>(d, t);
 }
 
-// state precision -> FP64 copy of all states (input of the FP64 energy transform)
+// state precision -> FP64 copy of all states (input of the FP64 energy transform of the sizes without
+// split-x2 kernels)
 template <typename T>
 __global__ void __launch_bounds__(RED_THREADS) k_to64(const LaunchList L) {
   const int e = find_entry(L, blockIdx.x);
@@ -825,64 +833,67 @@ __global__ void __launch_bounds__(RED_THREADS) k_to64(const LaunchList L) {
   }
 }
 
-// sum_k T(k) |psi^(k)|^2 / N^3 per state, from the FP64 forward transform in scratch64
-template <int KS>
+// sum_k T(k) |psi^(k)|^2 of one state per block, from the FP64 forward transform in scratch64
 __global__ void __launch_bounds__(RED_THREADS) k_kin_partials(const LaunchList L) {
   const int e = find_entry(L, blockIdx.x);
   const PassDesc &d = *(const PassDesc *)L.descp[e];
-  const int blk = blockIdx.x - L.tile_start[e];
-  const int N = d.N;
-  const size_t N3 = (size_t)N * N * N;
-  const size_t chunk = (N3 + d.nblk_red - 1) / d.nblk_red;
-  const size_t lo = blk * chunk, hi = (lo + chunk < N3) ? lo + chunk : N3;
+  const int t = blockIdx.x - L.tile_start[e];
+  const int s = t / d.en_nbk, blk = t - s * d.en_nbk;
+  const uint32_t N = (uint32_t)d.N, N3 = N * N * N;
+  const uint32_t chunk = (N3 + d.en_nbk - 1) / d.en_nbk;
+  const uint32_t lo = blk * chunk, hi = lo + chunk < N3 ? lo + chunk : N3;
   const double m = d.m;
-  double acc[KS];
-#pragma unroll
-  for (int s = 0; s < KS; ++s) acc[s] = 0.0;
-  for (size_t x = lo + threadIdx.x; x < hi; x += RED_THREADS) {
-    const int i3 = (int)(x % N), i2 = (int)((x / N) % N), i1 = (int)(x / ((size_t)N * N));
+  double acc[1] = {0.0};
+  for (uint32_t x = lo + threadIdx.x; x < hi; x += RED_THREADS) {
+    const uint32_t r = x / N, i3 = x - r * N, i1 = r / N, i2 = r - i1 * N;
     const double ks = d.ksym64[i1] + d.ksym64[i2] + d.ksym64[i3];
     const double tk = (d.kin == KIN_REL) ? ks / (sqrt(ks + m * m) + m) : ks;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      const double2 u = d.scratch64[(size_t)s * N3 + x];
-      acc[s] += tk * (u.x * u.x + u.y * u.y);
-    }
+    const double2 u = d.scratch64[(size_t)s * N3 + x];
+    acc[0] += tk * (u.x * u.x + u.y * u.y);
   }
-  block_reduce_store<KS>(acc, d.partials + (size_t)(d.nblk_red + blk) * (2 * MAX_PAIRS));
+  block_reduce_store<1>(acc, d.partials + (size_t)d.k * d.en_nq * d.en_nb + (size_t)s * d.en_nbk + blk, 1);
 }
 
-// E_s = (<V> + <H_K>)/<psi|psi>; aux = trace slot (or -1)
-__global__ void __launch_bounds__(RED_THREADS) k_energy_finalize(const LaunchList L) {
-  const int e = blockIdx.x;
+// E_s = (<V> + <H_K>)/<psi|psi> of one state per block, to device and pinned host memory; aux = trace
+// slot (or -1)
+__global__ void __launch_bounds__(FIN_THREADS) k_energy_finalize(const LaunchList L) {
+  const int e = find_entry(L, blockIdx.x);
   const PassDesc &d = *(const PassDesc *)L.descp[e];
-  const int KS = d.k;
-  const bool fdtd = d.kin == KIN_FDTD;
-  __shared__ double S[6 * MAX_STATES];
-  for (int q0 = 0; q0 < 5 * KS; q0 += SUMQ)
-    block_sum_columns(d.partials, d.nblk_red, q0, 5 * KS - q0 < SUMQ ? 5 * KS - q0 : SUMQ, S + q0);
-  if (!fdtd) {
-    for (int q0 = 0; q0 < KS; q0 += SUMQ)
-      block_sum_columns(d.partials + (size_t)d.nblk_red * (2 * MAX_PAIRS), d.nblk_red, q0,
-                        KS - q0 < SUMQ ? KS - q0 : SUMQ, S + 5 * KS + q0);
+  const int s = blockIdx.x - L.tile_start[e];
+  const int KS = d.k, nq = d.en_nq, nb = d.en_nb, nbk = d.en_nbk;
+  // a row of partials by two waves (the halves in order); the k-space row by the waves after them
+  __shared__ double H[FIN_THREADS / 64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int half = (nb + 1) / 2, halfk = (nbk + 1) / 2;
+  double v = 0.0;
+  if (w < 2 * nq) {
+    const double *row = d.partials + ((size_t)s * nq + w / 2) * nb;
+    v = (w & 1) ? row_sum(row + half, nb - half) : row_sum(row, half);
+  } else if (w < 2 * nq + 2) {
+    const double *row = d.partials + (size_t)KS * nq * nb + (size_t)s * nbk;
+    v = (w & 1) ? row_sum(row + halfk, nbk - halfk) : row_sum(row, halfk);
   }
+  if (lane == 0) H[w] = v;
+  __syncthreads();
   if (threadIdx.x != 0) return;
   const int slot = L.aux[e];
-  for (int s = 0; s < KS; ++s) {
-    const double nrm = S[5 * s];
-    double er = S[5 * s + 1], ei = S[5 * s + 2];
-    if (fdtd) { er += S[5 * s + 3]; ei += S[5 * s + 4]; }
-    else er += S[5 * KS + s] * d.inv_n3;
-    er /= nrm;
-    ei /= nrm;
-    d.energy[2 * s] = er;
-    d.energy[2 * s + 1] = ei;
-    if (slot >= 0 && d.trace) {
-      d.trace[((size_t)slot * KS + s) * 2] = er;
-      d.trace[((size_t)slot * KS + s) * 2 + 1] = ei;
-    }
-    if (!isfinite(er) || !isfinite(ei) || !(nrm > 0.0)) d.energy[2 * MAX_STATES] = 1.0;
+  const double nrm = H[0] + H[1];
+  double er = H[2] + H[3], ei = H[4] + H[5];
+  if (nq == 5) { er += H[6] + H[7]; ei += H[8] + H[9]; }
+  else er += (H[6] + H[7]) * d.inv_n3;
+  er /= nrm;
+  ei /= nrm;
+  d.energy[2 * s] = er;
+  d.energy[2 * s + 1] = ei;
+  if (slot >= 0 && d.trace) {
+    d.trace[((size_t)slot * KS + s) * 2] = er;
+    d.trace[((size_t)slot * KS + s) * 2 + 1] = ei;
   }
+  const bool bad = !isfinite(er) || !isfinite(ei) || !(nrm > 0.0);
+  if (bad) d.energy[2 * MAX_STATES] = 1.0;
+  d.h_energy[2 * s] = er;
+  d.h_energy[2 * s + 1] = ei;
+  d.h_energy[2 * MAX_STATES + s] = bad ? 1.0 : d.energy[2 * MAX_STATES];
 }
 
 // host <-> state conversions through an FP64 staging buffer
@@ -1017,26 +1028,21 @@ void launch_apply(const LaunchList &L, int total, int KS, bool dbl, hipStream_t 
   QF_KS_SWITCH(KS, A_)
 #undef A_
 }
-void launch_energy_partials(const LaunchList &L, int total, int KS, bool dbl, hipStream_t st) {
-#define E_(K)                                                                                             \
-  if (dbl) hipLaunchKernelGGL((k_energy_partials<double, K>), dim3(total), dim3(RED_THREADS), 0, st, L); \
-  else hipLaunchKernelGGL((k_energy_partials<float, K>), dim3(total), dim3(RED_THREADS), 0, st, L);
-  QF_KS_SWITCH(KS, E_)
-#undef E_
+void launch_energy_partials(const LaunchList &L, int total, bool dbl, hipStream_t st) {
+  if (dbl) hipLaunchKernelGGL(k_energy_partials<double>, dim3(total), dim3(RED_THREADS), 0, st, L);
+  else hipLaunchKernelGGL(k_energy_partials<float>, dim3(total), dim3(RED_THREADS), 0, st, L);
 }
-void launch_kin_partials(const LaunchList &L, int total, int KS, hipStream_t st) {
-#define K_(K) hipLaunchKernelGGL((k_kin_partials<K>), dim3(total), dim3(RED_THREADS), 0, st, L);
-  QF_KS_SWITCH(KS, K_)
-#undef K_
+void launch_kin_partials(const LaunchList &L, int total, hipStream_t st) {
+  hipLaunchKernelGGL(k_kin_partials, dim3(total), dim3(RED_THREADS), 0, st, L);
 }
 void launch_gram_sum(const double *partials, int nb, int nq, double *out, hipStream_t st) {
-  hipLaunchKernelGGL(k_gram_sum, dim3(1), dim3(RED_THREADS), 0, st, partials, nb, nq, out);
+  hipLaunchKernelGGL(k_gram_sum, dim3(1), dim3(FIN_THREADS), 0, st, partials, nb, nq, out);
 }
 void launch_gram_finalize(const LaunchList &L, hipStream_t st) {
-  hipLaunchKernelGGL(k_gram_finalize, dim3(L.n), dim3(RED_THREADS), 0, st, L);
+  hipLaunchKernelGGL(k_gram_finalize, dim3(L.n), dim3(FIN_THREADS), 0, st, L);
 }
-void launch_energy_finalize(const LaunchList &L, hipStream_t st) {
-  hipLaunchKernelGGL(k_energy_finalize, dim3(L.n), dim3(RED_THREADS), 0, st, L);
+void launch_energy_finalize(const LaunchList &L, int total, hipStream_t st) {
+  hipLaunchKernelGGL(k_energy_finalize, dim3(total), dim3(FIN_THREADS), 0, st, L);
 }
 
 // ------------------------------------------------ Gram matrix without allocation
@@ -1115,7 +1121,7 @@ extern "C" qfdtd_status qfdtd_gram_matrix_noalloc(const void *psi, int64_t n_sit
   else hipLaunchKernelGGL((k_gram_flat<float, K>), dim3(nb), dim3(RED_THREADS), 0, s, (const float2 *)psi, n, nb, part);
   QF_KS_SWITCH(k, GF_)
 #undef GF_
-  hipLaunchKernelGGL(k_gram_full, dim3(1), dim3(RED_THREADS), 0, s, (const double *)part, nb, (int)k, G);
+  hipLaunchKernelGGL(k_gram_full, dim3(1), dim3(FIN_THREADS), 0, s, (const double *)part, nb, (int)k, G);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     g_create_error = std::string("qfdtd_gram_matrix_noalloc: kernel launch: ") + hipGetErrorString(e);

@@ -105,6 +105,15 @@ constexpr int MAX_PAIRS = MAX_STATES * (MAX_STATES + 1) / 2;
 constexpr int MAX_LAUNCH = 64;       // members per launch list
 constexpr int ENERGY_RDIAG = 2 * MAX_STATES + 8;           // offset of the Cholesky diagonal
 constexpr int ENERGY_WORDS = ENERGY_RDIAG + MAX_STATES;    // doubles in PassDesc::energy
+constexpr int HOST_WORDS = 4 * MAX_STATES + 1;             // doubles in PassDesc::h_energy, then the evolve status
+
+// Blocks of the FP64 energy sums over n sites of H_K^(0) and of sizes without split-x2 kernels: one
+// per 512 sites, so that small lattices fill the chip, at most MAX_EN_BLOCKS.
+constexpr int MAX_EN_BLOCKS = 2048;
+__host__ __device__ inline int energy_blocks(size_t n) {
+  const size_t b = (n + 511) / 512;
+  return b > (size_t)MAX_EN_BLOCKS ? MAX_EN_BLOCKS : (int)b;
+}
 
 // Blocks of an FP64 reduction sweep over n sites: one per 2048 sites, at most MAX_RED_BLOCKS.
 // The grid, and with it the order of every FP64 sum, depends only on the site count.
@@ -155,7 +164,8 @@ struct PassDesc {
   const double *ksym64;   // [N] t(k_j) (HK1/HK2) or 4 sin^2(k_j/2)/a^2 (HK3), FP64
   const double *v64;      // [N^3] V in FP64, real or (re, im) interleaved
   double2 *scratch64;     // [k][N^3] FP64 copy for the energy transform
-  double *partials;       // [2][nblk_red][MAX_PAIRS][2] FP64 reduction partials
+  double *partials;       // FP64 partial sums: Gram [2 pairs][nblk_red]; energies [k][en_nq][en_nb] and
+                          // (FFT kinds) [k][en_nbk]
   double *coef;           // [MAX_STATES][MAX_STATES][2] FP64 orthonormalisation coefficients
   double *energy;         // [MAX_STATES][2] last energies; [2*MAX_STATES] status word;
                           // [ENERGY_RDIAG + j] Gram-Cholesky diagonal of state j (residual mode)
@@ -165,6 +175,10 @@ struct PassDesc {
   int32_t radix[MAX_STAGES];
   int32_t sector[MAX_STATES];
   int32_t nblk_red;       // reduction blocks per state sweep
+  int32_t en_nq, en_nb;   // energy sums over sites: quantities and blocks
+  int32_t en_nbk;         // blocks of the kinetic sum in k space
+  double *h_energy;       // pinned host: [2 MAX_STATES] energies, [MAX_STATES] their status words,
+                          // [MAX_STATES] Gram-Cholesky diagonal (residual mode)
   int32_t scheme;         // SCHEME_SPLIT or SCHEME_AB (FFT kinetic terms)
   double a, m, dt;
   double stencil_c;       // dt / (2 m a^2)
@@ -227,6 +241,15 @@ struct SplitKernels {
   bool plane_edges;
 };
 
+// Kernels of the FP64 energy measurement of one lattice size (slab: by state precision); pencil is null
+// where the size has none.  tps, pps: tiles of one state.
+struct MeasKernels {
+  const void *slab[2];
+  const void *pencil;
+  size_t slab_lds, pencil_lds;
+  int slab_nt, pencil_nt, tps, pps;
+};
+
 // Transform-pass kernels instantiated for one lattice size (index 0: complex64,
 // 1: complex128); plane entries are null where an N^2 plane does not fit LDS.
 struct FftKernels {
@@ -236,6 +259,7 @@ struct FftKernels {
   size_t plane_lds[2], row_lds[2], col_lds[2];
   int plane_nt;
   SplitKernels split[2][SPLIT_VARIANTS];   // two-pass split-x2 schedule: precision, variant
+  MeasKernels meas;
 };
 
 // Multi-size transform-pass kernels of one size group (see fft_inst.hip).

@@ -55,11 +55,11 @@ void launch_parity(const LaunchList &L, int total, bool dbl, hipStream_t st);
 void launch_to64(const LaunchList &L, int total, bool dbl, hipStream_t st);
 void launch_gram(const LaunchList &L, int total, int KS, bool dbl, hipStream_t st);
 void launch_apply(const LaunchList &L, int total, int KS, bool dbl, hipStream_t st);
-void launch_energy_partials(const LaunchList &L, int total, int KS, bool dbl, hipStream_t st);
-void launch_kin_partials(const LaunchList &L, int total, int KS, hipStream_t st);
+void launch_energy_partials(const LaunchList &L, int total, bool dbl, hipStream_t st);
+void launch_kin_partials(const LaunchList &L, int total, hipStream_t st);
 void launch_gram_finalize(const LaunchList &L, hipStream_t st);
 void launch_gram_sum(const double *partials, int nb, int nq, double *out, hipStream_t st);
-void launch_energy_finalize(const LaunchList &L, hipStream_t st);
+void launch_energy_finalize(const LaunchList &L, int total, hipStream_t st);
 }  // namespace qf
 
 using namespace qf;
@@ -250,7 +250,7 @@ struct qfdtd_ctx {
   bool stencil2 = false;        // H_K^(0), complex64: two fused steps per stencil pass
   int trace_on = 0;
   int64_t trace_cap = 0, trace_n = 0;
-  double *h_status = nullptr;   // pinned
+  double *h_words = nullptr;    // pinned: PassDesc::h_energy and, at 4 MAX_STATES, the evolve status
   hipEvent_t status_ev = nullptr;
   bool status_pending = false;
   Timer timer;
@@ -368,7 +368,7 @@ struct Entry {
 
 // F_SLAB: slab passes of any mode (split below into one launch per kernel kind, F_SLAB_KIND + kind)
 enum Fam { F_PLANE, F_ROW, F_COL, F_STENCIL, F_STENCIL2, F_PARITY, F_TO64, F_GRAM, F_APPLY, F_EPART, F_KPART, F_GFIN, F_EFIN,
-           F_SLAB, F_PENCIL, F_SLAB_KIND };   // F_SLAB_KIND last
+           F_MSLAB, F_MPENCIL, F_SLAB, F_PENCIL, F_SLAB_KIND };   // F_SLAB_KIND last
 
 // Kernel kind of a slab pass: the steady passes with a real or complex factor and of the A/B update,
 // and every other mode
@@ -398,6 +398,8 @@ double entry_bytes(const Entry &e, Fam f) {
       return n * 2 * s + ((e.mode & (M_PRE | M_MID | M_POST)) ? n3 * fsz : 0.0);
     case F_COL:
     case F_PENCIL: return n * 2 * s;
+    case F_MSLAB: return n * (s + 16.0) + n3 * (c->vcomplex ? 16.0 : 8.0);
+    case F_MPENCIL: return n * 16.0;
     case F_STENCIL: return n * 2 * s + n3 * fsz;
     case F_STENCIL2: return 2 * (n * 2 * s + n3 * fsz);    // two steps per launch
     default: return n * 2 * s;
@@ -475,6 +477,8 @@ qfdtd_status run_family(Fam f, std::vector<Entry> &es, bool dbl, int KS, hipStre
       else if (f == F_COL) l = K.col_lds[dbl];
       else if (f >= F_SLAB_KIND) l = split_of(e.c).slab_lds;
       else if (f == F_PENCIL) l = split_of(e.c).pencil_lds;
+      else if (f == F_MSLAB) l = K.meas.slab_lds;
+      else if (f == F_MPENCIL) l = K.meas.pencil_lds;
       if (l > lds) lds = l;
       if (grp >= 0 && (f == F_PLANE || f == F_ROW || f == F_COL))
         lds = g_grp_lds[grp][f == F_PLANE ? 0 : (f == F_ROW ? 1 : 2)][dbl];
@@ -492,6 +496,7 @@ qfdtd_status run_family(Fam f, std::vector<Entry> &es, bool dbl, int KS, hipStre
     else if (f == F_STENCIL || f == F_STENCIL2) cls = TC_STENCIL;
     else if (f >= F_SLAB_KIND) cls = TC_SLAB;
     else if (f == F_PENCIL) cls = TC_PENCIL;
+    else if (f == F_MSLAB || f == F_MPENCIL) cls = TC_MEAS;
     const int tix = cls >= 0 ? tbegin(c0, cls, bytes, st) : -1;
     const FftKernels &K = g_fft[es[base].c->N];
     void *kargs[] = {(void *)&L};
@@ -519,10 +524,12 @@ qfdtd_status run_family(Fam f, std::vector<Entry> &es, bool dbl, int KS, hipStre
       case F_TO64: launch_to64(L, total, dbl, st); break;
       case F_GRAM: launch_gram(L, total, KS, dbl, st); break;
       case F_APPLY: launch_apply(L, total, KS, dbl, st); break;
-      case F_EPART: launch_energy_partials(L, total, KS, dbl, st); break;
-      case F_KPART: launch_kin_partials(L, total, KS, st); break;
+      case F_MSLAB: go(K.meas.slab[dbl], K.meas.slab_nt, lds); break;
+      case F_MPENCIL: go(K.meas.pencil, K.meas.pencil_nt, lds); break;
+      case F_EPART: launch_energy_partials(L, total, dbl, st); break;
+      case F_KPART: launch_kin_partials(L, total, st); break;
       case F_GFIN: launch_gram_finalize(L, st); break;
-      case F_EFIN: launch_energy_finalize(L, st); break;
+      case F_EFIN: launch_energy_finalize(L, total, st); break;
       default: break;
     }
     QF_LAUNCHED(c0);
@@ -542,10 +549,11 @@ qfdtd_status run_by_k(Fam f, std::vector<Entry> &es, bool dbl) {
   return QFDTD_OK;
 }
 
-// run a single-size kernel family once per distinct N and split variant (split-x2 passes)
+// run a single-size kernel family once per distinct N (and split variant: split-x2 passes of a step)
 qfdtd_status run_by_size(Fam f, std::vector<Entry> &es, bool dbl, hipStream_t sto) {
   std::vector<int> keys;
-  auto key_of = [&](const Entry &e) { return e.c->N * 8 + e.c->split_v; };
+  const bool meas = f == F_MSLAB || f == F_MPENCIL;
+  auto key_of = [&](const Entry &e) { return e.c->N * 8 + (meas ? 0 : e.c->split_v); };
   for (auto &e : es)
     if (std::find(keys.begin(), keys.end(), key_of(e)) == keys.end()) keys.push_back(key_of(e));
   for (int kk : keys) {
@@ -584,8 +592,8 @@ qfdtd_status orthonormalise(std::vector<qfdtd_ctx *> &ms) {
   return QFDTD_OK;
 }
 
-// FP64 forward transform of the scratch copy (FFT members)
-qfdtd_status fwd64(std::vector<qfdtd_ctx *> &ms) {
+// FP64 forward transform of the scratch copy (FFT members without split-x2 kernels)
+qfdtd_status fwd64(std::vector<qfdtd_ctx *> &ms, hipStream_t st) {
   std::vector<Entry> pl, rw, c2, c1;
   for (auto *c : ms) {
     if (c->plane64) pl.push_back({c, 1, M_FWD, plane_tiles(c->N, c->k), 0});
@@ -595,35 +603,37 @@ qfdtd_status fwd64(std::vector<qfdtd_ctx *> &ms) {
     }
     c1.push_back({c, 1, M_FWD | M_AXIS1, col_tiles(c->N, c->k, true), 0});
   }
-  QF_TRY(run_family(F_PLANE, pl, true));
-  QF_TRY(run_family(F_ROW, rw, true));
-  QF_TRY(run_family(F_COL, c2, true));
-  QF_TRY(run_family(F_COL, c1, true));
+  QF_TRY(run_family(F_PLANE, pl, true, 0, st));
+  QF_TRY(run_family(F_ROW, rw, true, 0, st));
+  QF_TRY(run_family(F_COL, c2, true, 0, st));
+  QF_TRY(run_family(F_COL, c1, true, 0, st));
   return QFDTD_OK;
 }
 
-// E_i = <psi_i|H|psi_i>/<psi_i|psi_i> in FP64; `slot` >= 0 also records a trace row
-qfdtd_status energies(std::vector<qfdtd_ctx *> &ms, bool with_trace) {
-  if (ms.empty()) return QFDTD_OK;
+// The sums of the energies of the members (any N, kind), on stream `st`
+qfdtd_status energy_passes(std::vector<qfdtd_ctx *> &ms, hipStream_t st) {
   const bool dbl = ms[0]->dbl;
-  std::vector<Entry> ep, to, kp, fin;
-  std::vector<qfdtd_ctx *> ffts;
+  std::vector<Entry> ep, to, kp, sl, pe;
+  std::vector<qfdtd_ctx *> plain;
   for (auto *c : ms) {
-    ep.push_back({c, 0, 0u, c->nblk_red, 0});
-    if (c->fft()) {
-      to.push_back({c, 0, 0u, ew_tiles_host((long long)c->k * c->n3()), 0});
-      kp.push_back({c, 1, 0u, c->nblk_red, 0});
-      ffts.push_back(c);
+    const MeasKernels &m = g_fft[c->fft() ? c->N : 0].meas;
+    if (m.pencil) {
+      sl.push_back({c, 0, 0u, c->k * m.tps, 0});
+      pe.push_back({c, 0, 0u, c->k * m.pps, 0});
+      continue;
     }
-    int slot = -1;
-    if (with_trace && c->trace_on && c->trace_n < c->trace_cap) slot = (int)c->trace_n++;
-    fin.push_back({c, 0, 0u, 1, slot});
+    ep.push_back({c, 0, 0u, c->k * c->hd[0].en_nb, 0});
+    if (!c->fft()) continue;
+    to.push_back({c, 0, 0u, ew_tiles_host((long long)c->k * c->n3()), 0});
+    kp.push_back({c, 1, 0u, c->k * c->hd[0].en_nbk, 0});
+    plain.push_back(c);
   }
-  QF_TRY(run_by_k(F_EPART, ep, dbl));
-  QF_TRY(run_family(F_TO64, to, dbl));
-  QF_TRY(fwd64(ffts));
-  QF_TRY(run_by_k(F_KPART, kp, true));
-  QF_TRY(run_family(F_EFIN, fin, dbl));
+  QF_TRY(run_by_size(F_MSLAB, sl, dbl, st));
+  QF_TRY(run_by_size(F_MPENCIL, pe, dbl, st));
+  QF_TRY(run_family(F_EPART, ep, dbl, 0, st));
+  QF_TRY(run_family(F_TO64, to, dbl, 0, st));
+  QF_TRY(fwd64(plain, st));
+  QF_TRY(run_family(F_KPART, kp, true, 0, st));
   return QFDTD_OK;
 }
 
@@ -773,20 +783,15 @@ int lane_key(const qfdtd_ctx *c) {
   return c->split ? c->N * 8 + c->split_v : 8192 + 2 * size_group(c->N) + (c->plane ? 1 : 0);
 }
 
-// A chunk of one or several members.  The pass chains of a batch's members do not depend on each
-// other, so members are dealt to LANES streams (those that share launches to the same one, the
-// costliest first to the least loaded), forked from and joined to the common stream: the small sizes'
-// launches, which leave most of the chip idle, run beside the large ones'.  Measured on 16 uneven
-// one-state solves from 32^3 to 240^3 and on 12 three-state solves from 48^3 to 160^3, ms per 50 steps:
-// one stream 43.6 and 27.4, two 35.3 and 23.2, three 32.5 and 21.7, four (the hardware queues of a
-// process) 31.8 and 21.0.
-// While launches are timed everything runs on one stream, so that every timed launch has the device
-// to itself (as under a profiler) and its duration is the kernel's own.
-qfdtd_status run_chunk(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n, qfdtd_ctx *lead) {
-  if (ms.empty()) return QFDTD_OK;
-  bool timed = false;
-  for (auto *c : ms) timed = timed || c->timer.every > 0;
-  if (ms.size() == 1 && ms[0]->ngroups >= 2 && n[0] > 0 && !timed) return run_chunk_grouped(ms[0], n[0]);
+// Work of a batch's members that do not depend on each other (a chunk's pass chains, the energy sums):
+// members are dealt to LANES streams (those that share launches to the same one, the costliest first
+// to the least loaded), forked from and joined to the common stream: the small sizes' launches, which
+// leave most of the chip idle, run beside the large ones'.  Measured on 16 uneven one-state solves
+// from 32^3 to 240^3 and on 12 three-state solves from 48^3 to 160^3, ms per 50 steps: one stream
+// 43.6 and 27.4, two 35.3 and 23.2, three 32.5 and 21.7, four (the hardware queues of a process) 31.8
+// and 21.0.  run(members, steps, stream) does the work; n[j]: member j's steps (0: it has none).
+template <class Run>
+qfdtd_status on_lanes(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n, qfdtd_ctx *lead, Run run) {
   struct Share { int key; double cost; };
   std::vector<Share> shares;
   for (size_t j = 0; j < ms.size(); ++j) {
@@ -798,7 +803,7 @@ qfdtd_status run_chunk(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n, qfdtd_
     if (it == shares.end()) { shares.push_back({key, 8e-6}); it = shares.end() - 1; }
     it->cost += 4.0 * (double)c->k * (double)c->n3() * (double)c->csz() / 5e12 * (c->fft() && !c->plane && !c->split ? 2 : 1);
   }
-  if (timed || shares.size() < 2 || !lead || !lead->lane_fork) return run_chunk_on(ms, n, ms[0]->st);
+  if (shares.size() < 2 || !lead || !lead->lane_fork) return run(ms, n, ms[0]->st);
   std::sort(shares.begin(), shares.end(), [](const Share &x, const Share &y) {
     return x.cost != y.cost ? x.cost > y.cost : x.key < y.key;
   });
@@ -816,13 +821,42 @@ qfdtd_status run_chunk(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n, qfdtd_
   for (int l = 1; l < LANES; ++l) {
     if (lm[l].empty()) continue;
     QF_HIP(ms[0], hipStreamWaitEvent(lead->lane_st[l - 1], lead->lane_fork, 0));
-    QF_TRY(run_chunk_on(lm[l], ln[l], lead->lane_st[l - 1]));
+    QF_TRY(run(lm[l], ln[l], lead->lane_st[l - 1]));
     QF_HIP(ms[0], hipEventRecord(lead->lane_join[l - 1], lead->lane_st[l - 1]));
   }
-  QF_TRY(run_chunk_on(lm[0], ln[0], st));
+  QF_TRY(run(lm[0], ln[0], st));
   for (int l = 1; l < LANES; ++l)
     if (!lm[l].empty()) QF_HIP(ms[0], hipStreamWaitEvent(st, lead->lane_join[l - 1], 0));
   return QFDTD_OK;
+}
+
+// A chunk of one or several members.  While launches are timed everything runs on one stream, so that
+// every timed launch has the device to itself (as under a profiler) and its duration is the kernel's
+// own.
+qfdtd_status run_chunk(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n, qfdtd_ctx *lead) {
+  if (ms.empty()) return QFDTD_OK;
+  bool timed = false;
+  for (auto *c : ms) timed = timed || c->timer.every > 0;
+  if (timed) return run_chunk_on(ms, n, ms[0]->st);
+  if (ms.size() == 1 && ms[0]->ngroups >= 2 && n[0] > 0) return run_chunk_grouped(ms[0], n[0]);
+  return on_lanes(ms, n, lead, run_chunk_on);
+}
+
+// E_i = <psi_i|H|psi_i>/<psi_i|psi_i> in FP64, to device and pinned host memory; with_trace also records a
+// trace row where the member keeps one
+qfdtd_status energies(std::vector<qfdtd_ctx *> &ms, bool with_trace, qfdtd_ctx *lead) {
+  if (ms.empty()) return QFDTD_OK;
+  std::vector<int> one(ms.size(), 1);
+  QF_TRY(on_lanes(ms, one, lead, [](std::vector<qfdtd_ctx *> &m, std::vector<int> &, hipStream_t st) {
+    return energy_passes(m, st);
+  }));
+  std::vector<Entry> fin;
+  for (auto *c : ms) {
+    int slot = -1;
+    if (with_trace && c->trace_on && c->trace_n < c->trace_cap) slot = (int)c->trace_n++;
+    fin.push_back({c, 0, 0u, c->k, slot});
+  }
+  return run_family(F_EFIN, fin, ms[0]->dbl);
 }
 
 // Streams and events of the lanes of batches that this context leads (its first member), made on first
@@ -865,7 +899,7 @@ qfdtd_status check_status(qfdtd_ctx *c, bool wait) {
   if (wait) QF_HIP(c, hipEventSynchronize(c->status_ev));
   else if (hipEventQuery(c->status_ev) != hipSuccess) return QFDTD_OK;
   c->status_pending = false;
-  if (*c->h_status != 0.0) {
+  if (c->h_words[4 * MAX_STATES] != 0.0) {
     c->poisoned = true;
     c->set_mask = 0;
     return fail(c, QFDTD_E_NUMERIC, "non-finite value or collapsed norm during orthonormalisation");
@@ -874,7 +908,8 @@ qfdtd_status check_status(qfdtd_ctx *c, bool wait) {
 }
 
 qfdtd_status post_status(qfdtd_ctx *c) {
-  QF_HIP(c, hipMemcpyAsync(c->h_status, c->energy + 2 * MAX_STATES, sizeof(double), hipMemcpyDeviceToHost, c->st));
+  QF_HIP(c, hipMemcpyAsync(c->h_words + 4 * MAX_STATES, c->energy + 2 * MAX_STATES, sizeof(double),
+                           hipMemcpyDeviceToHost, c->st));
   QF_HIP(c, hipEventRecord(c->status_ev, c->st));
   c->status_pending = true;
   return QFDTD_OK;
@@ -1046,7 +1081,7 @@ qfdtd_status batch_evolve_impl(qfdtd_ctx *const *members, int32_t n, const int64
     std::vector<qfdtd_ctx *> tr;
     for (auto *c : act)
       if (c->trace_on) tr.push_back(c);
-    QF_TRY(energies(tr, true));
+    QF_TRY(energies(tr, true, nullptr));
     size_t q = 0;
     for (size_t j = 0; j < ms.size(); ++j)
       if (rem[j] > 0) rem[j] -= cn[q++];
@@ -1152,7 +1187,7 @@ qfdtd_status qfdtd_create(qfdtd_ctx **out, int32_t N, double a, double m, int32_
     }
     if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
     free_all(c);
-    if (c->h_status) (void)hipHostFree(c->h_status);
+    if (c->h_words) (void)hipHostFree(c->h_words);
     if (c->status_ev) (void)hipEventDestroy(c->status_ev);
     delete c;
     return fail(nullptr, s, msg);
@@ -1170,7 +1205,11 @@ qfdtd_status qfdtd_create(qfdtd_ctx **out, int32_t N, double a, double m, int32_
   c->tw64 = (double2 *)dalloc(c, N * 16);
   c->ksym64 = (double *)dalloc(c, N * 8);
   c->scratch64 = (double2 *)dalloc(c, c->k * n3 * 16);
-  c->partials = (double *)dalloc(c, 2 * (size_t)c->nblk_red * MAX_PAIRS * 2 * 8);
+  const MeasKernels &mk = g_fft[c->fft() ? N : 0].meas;
+  const int en_nq = c->fft() ? 3 : 5, en_nb = mk.pencil ? mk.tps : energy_blocks(n3);
+  const int en_nbk = mk.pencil ? mk.pps : c->fft() ? energy_blocks(n3) : 0;
+  c->partials = (double *)dalloc(c, 8 * std::max((size_t)c->nblk_red * MAX_PAIRS * 2,
+                                                 (size_t)c->k * ((size_t)en_nq * en_nb + en_nbk)));
   c->coef = (double *)dalloc(c, MAX_STATES * MAX_STATES * 2 * 8);
   c->energy = (double *)dalloc(c, ENERGY_WORDS * 8);
   if (c->trace_on) c->trace = (double *)dalloc(c, (size_t)c->trace_cap * c->k * 2 * 8);
@@ -1180,8 +1219,9 @@ qfdtd_status qfdtd_create(qfdtd_ctx **out, int32_t N, double a, double m, int32_
             (!c->fft() || ab || (c->hfac && c->h2fac)) &&
             (!c->any_parity || c->alt) && (!c->trace_on || c->trace);
   if (!ok) return bail(QFDTD_E_NOMEM, "device allocation failed");
-  if (hipHostMalloc((void **)&c->h_status, sizeof(double)) != hipSuccess) return bail(QFDTD_E_NOMEM, "pinned allocation failed");
-  *c->h_status = 0.0;
+  if (hipHostMalloc((void **)&c->h_words, HOST_WORDS * sizeof(double)) != hipSuccess)
+    return bail(QFDTD_E_NOMEM, "pinned allocation failed");
+  std::memset(c->h_words, 0, HOST_WORDS * sizeof(double));
   if (hipEventCreateWithFlags(&c->status_ev, hipEventDisableTiming) != hipSuccess)
     return bail(QFDTD_E_DEVICE, "event creation failed");
 
@@ -1251,6 +1291,10 @@ qfdtd_status qfdtd_create(qfdtd_ctx **out, int32_t N, double a, double m, int32_
     d.nst = make_plan(N, d.radix);
     for (int i = 0; i < c->k; ++i) d.sector[i] = c->sectors[i];
     d.nblk_red = c->nblk_red;
+    d.en_nq = en_nq;
+    d.en_nb = en_nb;
+    d.en_nbk = en_nbk;
+    d.h_energy = c->h_words;
     d.scheme = c->scheme;
     d.a = a; d.m = m; d.dt = 0.0; d.stencil_c = 0.0;
     d.inv_n3 = 1.0 / (double)n3;
@@ -1346,25 +1390,32 @@ qfdtd_status qfdtd_batch_evolve(qfdtd_ctx *const *members, int32_t n, const int6
   return batch_evolve_impl(members, n, steps, dt);
 }
 
+// status of the energies in the pinned words (after a synchronisation)
+static qfdtd_status energy_status(qfdtd_ctx *c, const char *msg) {
+  for (int i = 0; i < c->k; ++i)
+    if (c->h_words[2 * MAX_STATES + i] != 0.0) {
+      c->poisoned = true;
+      c->set_mask = 0;
+      return fail(c, QFDTD_E_NUMERIC, msg);
+    }
+  return QFDTD_OK;
+}
+
 static qfdtd_status measure_host(qfdtd_ctx *c) {
   QF_TRY(check_status(c, true));
   QF_TRY(validate_common(c));
   std::vector<qfdtd_ctx *> one{c};
   if (c->fresh) QF_TRY(orthonormalise(one));
-  QF_TRY(energies(one, false));
-  QF_TRY(post_status(c));
-  QF_TRY(check_status(c, true));
-  return QFDTD_OK;
+  QF_TRY(energies(one, false, nullptr));
+  QF_HIP(c, hipStreamSynchronize(c->st));
+  return energy_status(c, "non-finite value or collapsed norm during orthonormalisation");
 }
 
 qfdtd_status qfdtd_states(qfdtd_ctx *c, int32_t k, double *en, double *psi) {
   if (!c) return fail(nullptr, QFDTD_E_INVALID, "ctx is NULL");
   if (k < 1 || k > c->k) return fail(c, QFDTD_E_INVALID, "k out of range");
   QF_TRY(measure_host(c));
-  std::vector<double> e(2 * MAX_STATES);
-  QF_HIP(c, hipMemcpyAsync(e.data(), c->energy, 2 * MAX_STATES * 8, hipMemcpyDeviceToHost, c->st));
-  QF_HIP(c, hipStreamSynchronize(c->st));
-  if (en) std::memcpy(en, e.data(), (size_t)2 * k * 8);
+  if (en) std::memcpy(en, c->h_words, (size_t)2 * k * 8);
   if (psi) {
     const size_t n3 = c->n3();
     for (int i = 0; i < k; ++i) {
@@ -1386,12 +1437,7 @@ qfdtd_status qfdtd_states_device(qfdtd_ctx *c, int32_t k, double *en, void *psi_
   if (!c) return fail(nullptr, QFDTD_E_INVALID, "ctx is NULL");
   if (k < 1 || k > c->k) return fail(c, QFDTD_E_INVALID, "k out of range");
   QF_TRY(measure_host(c));
-  if (en) {
-    std::vector<double> e(2 * MAX_STATES);
-    QF_HIP(c, hipMemcpyAsync(e.data(), c->energy, 2 * MAX_STATES * 8, hipMemcpyDeviceToHost, c->st));
-    QF_HIP(c, hipStreamSynchronize(c->st));
-    std::memcpy(en, e.data(), (size_t)2 * k * 8);
-  }
+  if (en) std::memcpy(en, c->h_words, (size_t)2 * k * 8);
   if (psi_dev) QF_HIP(c, hipMemcpyAsync(psi_dev, c->psi, (size_t)k * c->n3() * c->csz(), hipMemcpyDeviceToDevice, c->st));
   return QFDTD_OK;
 }
@@ -1431,10 +1477,8 @@ qfdtd_status qfdtd_gram_residuals(qfdtd_ctx *c, double *r) {
   // coefficients and the status word alone
   std::vector<Entry> fin{{c, 0, 0u, 1, 1}};
   QF_TRY(run_family(F_GFIN, fin, c->dbl));
-  std::vector<double> d(MAX_STATES);
-  QF_HIP(c, hipMemcpyAsync(d.data(), c->energy + ENERGY_RDIAG, MAX_STATES * 8, hipMemcpyDeviceToHost, c->st));
   QF_HIP(c, hipStreamSynchronize(c->st));
-  std::memcpy(r, d.data(), (size_t)c->k * 8);
+  std::memcpy(r, c->h_words + 3 * MAX_STATES, (size_t)c->k * 8);
   return QFDTD_OK;
 }
 
@@ -1454,17 +1498,13 @@ qfdtd_status qfdtd_batch_energies(qfdtd_ctx *const *members, int32_t n, double *
     kmax = c->k > kmax ? c->k : kmax;
   }
   QF_TRY(orthonormalise(fr));
-  QF_TRY(energies(ms, false));
-  std::vector<double> e(2 * MAX_STATES + 8);
+  if (n > 1) make_lanes(ms[0]);
+  QF_TRY(energies(ms, false, ms[0]));
+  QF_HIP(ms[0], hipStreamSynchronize(ms[0]->st));
   for (int j = 0; j < n; ++j) {
     qfdtd_ctx *c = ms[j];
-    QF_HIP(c, hipMemcpyAsync(e.data(), c->energy, (2 * MAX_STATES + 1) * 8, hipMemcpyDeviceToHost, c->st));
-    QF_HIP(c, hipStreamSynchronize(c->st));
-    if (e[2 * MAX_STATES] != 0.0) {
-      c->poisoned = true;
-      c->set_mask = 0;
-      return fail(c, QFDTD_E_NUMERIC, "non-finite energy or collapsed norm");
-    }
+    QF_TRY(energy_status(c, "non-finite energy or collapsed norm"));
+    const double *e = c->h_words;
     for (int i = 0; i < kmax; ++i) {
       en[2 * ((size_t)j * kmax + i)] = i < c->k ? e[2 * i] : 0.0;
       en[2 * ((size_t)j * kmax + i) + 1] = i < c->k ? e[2 * i + 1] : 0.0;
@@ -1565,7 +1605,7 @@ void qfdtd_destroy(qfdtd_ctx *c) {
   }
   if (c->lane_fork) (void)hipEventDestroy(c->lane_fork);
   free_all(c);
-  if (c->h_status) (void)hipHostFree(c->h_status);
+  if (c->h_words) (void)hipHostFree(c->h_words);
   if (c->status_ev) (void)hipEventDestroy(c->status_ev);
   delete c;
 }

@@ -33,7 +33,9 @@
 
 namespace qf {
 
-#define REG_SPLIT(n) register_split<QF_T, n>(t);
+#define REG_SPLIT(n)          \
+  register_split<QF_T, n>(t); \
+  if constexpr (sizeof(QF_T) == 8) register_meas<n>(t);
 void QF_CAT(register_split_part, QF_SPLIT_PART)(FftKernels *t) { QF_SIZES(REG_SPLIT) }
 
 }  // namespace qf

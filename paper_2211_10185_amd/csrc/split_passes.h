@@ -516,6 +516,181 @@ __device__ __forceinline__ void pencil_body(const LaunchList &L, int e, int t, u
   }
 }
 
+// FP64 energy measurement in two passes over the states.  The kinetic energy is sum_k T(k) |psi^(k)|^2 / N^3,
+// so the transform's last stage feeds the sum and its output is never written; the slab pass reads the
+// state as it is stored (complex64 or complex128), adds up |psi|^2 and V |psi|^2 on the way, and leaves
+// x3 and the slab part of x2 transformed in scratch64.  40 B per site and state (complex64) instead of
+// the 152 B of a copy, three transform passes and two sums.  128^3 x 3 states: slab pass 44 us, pencil
+// pass 25 us, with the final sums 73 us for a readout that took 203; 256^3 x 3 states with complex V: 438
+// and 555 us of 1.68 ms before.  Bound by the slab pass's natural-order loads and by HBM.
+
+// Fixed-order block sums of NV values per thread: wave shuffles, then the waves in order.  Thread 0
+// returns with the sums in acc.
+template <int NV, int NT> __device__ __forceinline__ void block_sums(double (&acc)[NV]) {
+  constexpr int NW = (NT + 63) / 64;
+  __shared__ double red[NW][NV];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+  for (int q = 0; q < NV; ++q) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) acc[q] += __shfl_xor(acc[q], off, 64);
+    if (lane == 0) red[w][q] = acc[q];
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+      double v = 0.0;
+      for (int ww = 0; ww < NW; ++ww) v += red[ww][q];
+      acc[q] = v;
+    }
+  }
+}
+
+// Slab pass of the measurement on tile (state s, plane group p, fast x2 digit b): the state's natural rows
+// to LDS in FP64 with the sums over the tile's sites, forward x3, A to scratch64 in split order.
+template <typename TI, int N, int N1, int NT, int XI, int PK>
+__device__ __forceinline__ void slab_meas_body(const PassDesc &d, int t, unsigned char *smem) {
+  using V2 = C<double>;
+  constexpr int N2 = N / N1, P = padded_len(N), NR = XI * N1, NH = N / XI, NP = XI * N;
+  constexpr int CQ = (NP + NT - 1) / NT, TPS = (N / XI) * N2;
+  using Rows = SlabGeo<NR, P, N1, XI>;
+  static_assert(NT % 64 == 0, "whole waves");
+  const int s = t / TPS, tile = t - s * TPS;
+  const int p = tile / N2, b = tile - p * N2;
+  V2 *tw = (V2 *)smem;
+  V2 *buf = tw + tw_total<PK, N>();
+  constexpr size_t N3 = (size_t)N * N * N;
+  const size_t voff = (size_t)XI * p * N * N;
+  auto site = [&](int j, int a, int n) -> size_t { return ((size_t)j * N + N2 * a + b) * N + n; };
+  const C<TI> *g = (const C<TI> *)d.psi + (size_t)s * N3 + voff;
+  const bool vc = d.vcomplex != 0;
+  double acc[3] = {0.0, 0.0, 0.0};
+  constexpr int NE = NR * N, EPT = (NE + NT - 1) / NT, UB = EPT < 8 ? EPT : 8;
+#pragma unroll 1
+  for (int it0 = 0; it0 < EPT; it0 += UB) {
+    C<TI> v[UB];
+    double vr[UB], vi[UB];
+#pragma unroll
+    for (int u = 0; u < UB; ++u) {
+      const int idx = (int)threadIdx.x + (it0 + u) * NT;
+      vr[u] = vi[u] = 0.0;
+      if (it0 + u < EPT && (NE % NT == 0 || idx < NE)) {
+        const int bl = idx / N, n = idx - bl * N, pl = bl / N1, a = bl - pl * N1;
+        const size_t o = site(pl, a, n);
+        v[u] = g[o];
+        if (vc) { const V2 w = ((const V2 *)d.v64)[voff + o]; vr[u] = w.x; vi[u] = w.y; }
+        else vr[u] = d.v64[voff + o];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < UB; ++u) {
+      const int idx = (int)threadIdx.x + (it0 + u) * NT;
+      if (it0 + u < EPT && (NE % NT == 0 || idx < NE)) {
+        const int bl = idx / N, n = idx - bl * N;
+        const double ur = v[u].x, ui = v[u].y;
+        const double n2 = ur * ur + ui * ui;
+        acc[0] += n2;
+        acc[1] += vr[u] * n2;
+        acc[2] += vi[u] * n2;
+        buf[Rows::at(bl, n)] = mkc<double>(ur, ui);
+      }
+    }
+  }
+  fill_twiddles<double, PK, N, NT>(tw, (const V2 *)d.tw64);
+  block_sums<3, NT>(acc);
+  if (threadIdx.x == 0)
+    for (int q = 0; q < 3; ++q) d.partials[(size_t)(s * 3 + q) * TPS + tile] = acc[q];
+  __syncthreads();
+  fft_lines_t<double, PK, N, false, Rows, NT>(buf, tw);
+  const StateBuf<double, true> sb((V2 *)d.scratch64 + (size_t)s * N3 + voff);
+#pragma unroll
+  for (int q = 0; q < CQ; ++q) {
+    const int pos = (int)threadIdx.x + q * NT;
+    if (NP % NT == 0 || pos < NP) {
+      const int j = pos / N, w = pos - (pos / N) * N;
+      const int pl = w % XI, col = j * NH + w / XI;
+      V2 v[N1];
+#pragma unroll
+      for (int a = 0; a < N1; ++a) v[a] = buf[Rows::at(pl * N1 + a, col)];
+      Dft<N1, false, V2>::run(v);
+#pragma unroll
+      for (int k1 = 1; k1 < N1; ++k1) v[k1] = cmul(v[k1], uniform(((const V2 *)d.tw64)[(b * k1) % N]));
+      const uint32_t vo = (uint32_t)(site(j, 0, w) * sizeof(V2));
+#pragma unroll
+      for (int k1 = 0; k1 < N1; ++k1) sb.store(v[k1], vo, (uint32_t)(k1 * N2 * N * sizeof(V2)));
+    }
+  }
+}
+
+// Pencil pass of the measurement on tile (state s, slow x2 frequency k1, TT x3 columns): B and forward x1 of
+// scratch64; the last stage's outputs are weighted with T(k) and summed.
+template <int N, int N2, int TT, int NT, int XI, int PK>
+__device__ __forceinline__ void pencil_meas_body(const PassDesc &d, int t, unsigned char *smem) {
+  using V2 = C<double>;
+  constexpr int N1 = N / N2, NH = N / XI, NL = N2 * TT, PC = pencil_pitch<N2, TT>(), NCB = N / TT;
+  constexpr int PPT = (N * TT + NT - 1) / NT, PPS = N1 * NCB;
+  constexpr int M = stages_of<PK, N, false>().n - 1;
+  using Geo = TileGeo<NL, PC>;
+  const int s = t / PPS, tile = t - s * PPS;
+  const int k1 = tile / NCB, c0 = (tile - k1 * NCB) * TT;
+  V2 *tw = (V2 *)smem;
+  double *ktl = (double *)(tw + tw_total<PK, N>());
+  V2 *buf = (V2 *)(ktl + N);
+  const StateBuf<double> sb((V2 *)d.scratch64 + (size_t)s * N * N * N);
+  auto at = [&](int i1, int c) -> uint32_t {
+    const int col = c0 + c, j = col / NH, w = XI * (col - j * NH) + i1 % XI;
+    return (uint32_t)((((size_t)(i1 - i1 % XI + j) * N + (size_t)(N2 * k1)) * N + w) * sizeof(V2));
+  };
+#pragma unroll
+  for (int q = 0; q < PPT; ++q) {
+    const int pos = (int)threadIdx.x + q * NT;
+    const int i1 = pos / TT, c = pos - (pos / TT) * TT;
+    const bool in = (N * TT) % NT == 0 || pos < N * TT;
+    V2 v[N2];
+    if (in) {
+#pragma unroll
+      for (int bb = 0; bb < N2; ++bb) v[bb] = sb.load(at(i1, c), (uint32_t)(bb * N * sizeof(V2)));
+    }
+    if (q == 0) {
+      // the first position's loads are in flight while the tables are filled
+      fill_twiddles<double, PK, N, NT>(tw, (const V2 *)d.tw64);
+      for (int i = threadIdx.x; i < N; i += NT) ktl[i] = d.ksym64[i];
+    }
+    if (in) {
+      Dft<N2, false, V2>::run(v);
+#pragma unroll
+      for (int k2 = 0; k2 < N2; ++k2) buf[Geo::at(k2 * TT + c, i1)] = v[k2];
+    }
+  }
+  __syncthreads();
+  lds_stages<double, PK, N, false, false, Geo, NT, 0, M>(buf, tw);
+  constexpr int R = StageOf<PK, N, false, M>::R;
+  using SS = SG<Geo, N, R, NT>;
+  V2 v[SS::CAPQ][R];
+  stage_read<double, PK, N, false, M, false, Geo, NT>(v, tw, [&](int l, int n) { return buf[Geo::at(l, n)]; });
+  double acc[1] = {0.0};
+  const bool rel = d.kin == KIN_REL;
+  const double mm = d.m;
+#pragma unroll
+  for (int q = 0; q < SS::CAPQ; ++q) {
+    if (SS::active(q)) {
+      int j, l;
+      SS::jb(q, j, l);
+      const int k2 = l / TT, c = l - (l / TT) * TT;
+      const double k23 = ktl[k1 + N1 * k2] + ktl[c0 + c];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const double ks = ktl[j + r * SS::NR] + k23;
+        const double tk = rel ? ks / (sqrt(ks + mm * mm) + mm) : ks;
+        acc[0] += tk * (v[q][r].x * v[q][r].x + v[q][r].y * v[q][r].y);
+      }
+    }
+  }
+  block_sums<1, NT>(acc);
+  if (threadIdx.x == 0) d.partials[(size_t)d.k * 3 * d.en_nb + (size_t)s * PPS + tile] = acc[0];
+}
+
 // Tile shapes of the split-x2 passes per size, precision and variant: x2 = N1 x N2 (N1 stride rows
 // per slab tile, N2 consecutive rows per pencil tile; both have register butterflies), plane groups
 // of XI, TT x3 columns per pencil tile, and per pass its threads and the radix plan of its line
@@ -731,6 +906,38 @@ template <typename T, int N> void register_split(FftKernels *tab) {
   register_split_variant<T, N, 2>(tab);
   register_split_variant<T, N, 3>(tab);
   register_split_variant<T, N, 4>(tab);
+}
+
+// Measurement kernels: the shapes of complex128 variant 0.
+template <typename TI, int N>
+__global__ void __launch_bounds__((split_def(N, 1, 0).slab_nt)) k_slab_meas_t(const LaunchList L) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr SplitDef D = split_def(N, 1, 0);
+  const int e = find_entry(L, blockIdx.x);
+  slab_meas_body<TI, N, D.N1, D.slab_nt, D.XI, D.slab_plan>(*(const PassDesc *)L.descp[e],
+                                                            blockIdx.x - L.tile_start[e], smem);
+}
+template <int N>
+__global__ void __launch_bounds__((split_def(N, 1, 0).pencil_nt)) k_pencil_meas_t(const LaunchList L) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr SplitDef D = split_def(N, 1, 0);
+  const int blk = xcd_block_chunked(blockIdx.x, gridDim.x, PENCIL_XCD_RUN);
+  const int e = find_entry(L, blk);
+  pencil_meas_body<N, N / D.N1, D.TT, D.pencil_nt, D.XI, D.pencil_plan>(*(const PassDesc *)L.descp[e],
+                                                                        blk - L.tile_start[e], smem);
+}
+template <int N> void register_meas(FftKernels *tab) {
+  constexpr SplitDef D = split_def(N, 1, 0);
+  MeasKernels &k = tab[N].meas;
+  k.slab[0] = (const void *)k_slab_meas_t<float, N>;
+  k.slab[1] = (const void *)k_slab_meas_t<double, N>;
+  k.pencil = (const void *)k_pencil_meas_t<N>;
+  k.slab_lds = slab_lds_t<double, N, D.N1, D.XI, D.slab_plan>();
+  k.pencil_lds = pencil_lds_t<double, N, N / D.N1, D.TT, D.pencil_plan>();
+  k.slab_nt = D.slab_nt;
+  k.pencil_nt = D.pencil_nt;
+  k.tps = N / D.XI * (N / D.N1);
+  k.pps = D.N1 * (N / D.TT);
 }
 
 }  // namespace qf
