@@ -129,7 +129,7 @@ typedef struct {
                                      a chunk into a HIP graph once and replaying it */
 #define QFDTD_F_THREE_GROUPS 16u  /* FFT kinds, k >= 3: split the states into three groups on three
                                      internal streams instead of two (schedule autotuning) */
-#define QFDTD_F_STENCIL_1STEP 32u /* H_K^(0) with complex64 states: one step per stencil pass.
+#define QFDTD_F_STENCIL_1STEP 32u /* H_K^(0): one step per stencil pass.
                                      By default a pass advances two steps at once (eq. HK0
                                      applied twice in one sweep, the same operations per site,
                                      so the results are bit-identical) and halves the memory

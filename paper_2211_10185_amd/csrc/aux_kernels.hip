@@ -4,7 +4,7 @@
 //  k_potential    FP64 V(r) on the lattice (harmonic, Cornell, Coulomb, radial spline, grid)
 //  k_dt_tables    e^{-dt V/2}, e^{-dt V}, e^{-dt t(k_j)} for the current dt (FP64, stored
 //                 in the state precision)
-//  k_stencil      H_K^(0) step psi' = A psi + B dt/(2 M a^2) L psi            (Sec. 2, eq. HK0)
+//  k_stencil(2)   H_K^(0) step, one or two at a time: psi' = A psi + B dt/(2 M a^2) L psi            (Sec. 2, eq. HK0)
 //  k_parity       P^+, P^-, P^-_{p_k} over reflection orbits                  (Sec. 3, Fig. 1 text)
 //  k_gram ...     FP64 Gram matrix, Cholesky, Psi <- Psi R^{-1}              (Sec. 1: orthogonal projection)
 //  k_energy_*     FP64 <psi|V|psi>, <psi|H_K|psi>, <psi|psi>                (Sec. 2, general solution)
@@ -122,17 +122,25 @@ __global__ void k_dt_tables(const double *v64, int vcomplex, size_t N3, double d
 // psi' = A psi + B c (sum of 6 neighbours - 6 psi), c = dt/(2 m a^2),
 // A = (1 - dt V/2)/(1 + dt V/2), B = 1/(1 + dt V/2); walls are ghost zeros.
 //
-// Tile = 64 (x3) x 16 (x2) columns of one state over ST_CZ planes along x1.
+// Tile = 64 (x3) x 16 (x2) columns of one state over some planes along x1 (stencil_cz).
 // Each wave owns 4 consecutive x2 rows, one x3 column per lane, and marches
 // along x1 keeping psi at i1-1, i1, i1+1 of its 4 sites in registers.  x2
 // neighbours come from the thread's own rows (memory only for the rows just
 // outside its 4), x3 neighbours from the adjacent lanes by wavefront shifts
 // (memory only at the tile's x3 edges), so each site is read from memory about
 // once per sweep.  Loads of ST_ZU planes are issued together.
-constexpr int ST_TX = 64, ST_RPT = 4, ST_TY = (RED_THREADS / 64) * ST_RPT, ST_CZ = 8, ST_ZU = 2;
+constexpr int ST_TX = 64, ST_RPT = 4, ST_TY = (RED_THREADS / 64) * ST_RPT, ST_ZU = 2;
 
-__host__ __device__ inline int stencil_tiles(int N, int k) {
-  return k * ((N + ST_TX - 1) / ST_TX) * ((N + ST_TY - 1) / ST_TY) * ((N + ST_CZ - 1) / ST_CZ);
+// Planes per tile: 8 (4 and 16 are slower at 128^3), down to 2 where the tiles would not fill the chip
+// (64^3 x 3 states: 96 tiles of 8 planes 14.4 us, 384 of 2 planes 11.6).
+inline int stencil_cz(int N, int k) {
+  const long long cols = (long long)k * ((N + ST_TX - 1) / ST_TX) * ((N + ST_TY - 1) / ST_TY);
+  int cz = 8;
+  while (cz > 2 && cols * ((N + cz - 1) / cz) < 384) cz /= 2;
+  return cz;
+}
+inline int stencil_tiles(int N, int k, int cz) {
+  return k * ((N + ST_TX - 1) / ST_TX) * ((N + ST_TY - 1) / ST_TY) * ((N + cz - 1) / cz);
 }
 
 // value of lane l-1 (DPP wave shift right by one; lane 0 gets 0)
@@ -276,19 +284,19 @@ __global__ void __launch_bounds__(RED_THREADS) k_stencil(const LaunchList L) {
   const C<T> *sp = (const C<T> *)((mode & M_SWAP) ? d.alt : d.psi) + (size_t)s * N3;
   C<T> *dp = (C<T> *)((mode & M_SWAP) ? d.psi : d.alt) + (size_t)s * N3;
   const T c = (T)d.stencil_c, hdt = (T)(0.5 * d.dt);
-  const int z0 = bz * ST_CZ;
-  const int z1 = (z0 + ST_CZ < N) ? z0 + ST_CZ : N;
+  const int cz = L.aux[e];
+  const int z0 = bz * cz;
+  const int z1 = (z0 + cz < N) ? z0 + cz : N;
   // every lane of the wave takes part (the lane shifts need the whole wave),
   // lanes and rows outside the lattice neither load nor store
   if (d.vcomplex) stencil_tile<T, true>(sp, dp, d.vtab, N, y0, i3, lane, z0, z1, c, hdt);
   else stencil_tile<T, false>(sp, dp, d.vtab, N, y0, i3, lane, z0, z1, c, hdt);
 }
 
-// ------------------------------------------------ two fused stencil steps (complex64)
+// ------------------------------------------------ two fused stencil steps
 //
-// psi'' = S(S(psi)) for the H_K^(0) step S above, in one sweep.  A block owns an output tile
-// of S2_TX (x3) x S2_TY (x2) sites over S2_CZ planes along x1 and marches along x1.  At plane
-// zp it
+// psi'' = S(S(psi)) for the H_K^(0) step S above, in one sweep.  A block owns an output tile of TX (x3) x
+// TY (x2) sites over CZ planes along x1 and marches along x1.  At plane zp it
 //   - writes psi(zp) over the tile and a frame of width 2 in x2 and x3 to LDS;
 //   - computes psi'(zp) over the tile and a frame of width 1 (x1 neighbours from registers,
 //     x2 and x3 neighbours from LDS);
@@ -297,156 +305,245 @@ __global__ void __launch_bounds__(RED_THREADS) k_stencil(const LaunchList L) {
 // Every site is updated with the operations of S in the same order, so the fused pass gives
 // the bits of two single passes.  psi' is zero outside the lattice (the walls).  Per step the
 // lattice is read and written half as often as by single passes.
-constexpr int S2_TX = 64, S2_TY = 16, S2_CZ = 8;   // S2_THREADS: common.h
-constexpr int S2_PX = S2_TX + 4, S2_PY = S2_TY + 4;                // psi plane in LDS
-constexpr int S2_QX = S2_TX + 2, S2_QY = S2_TY + 2;                // psi' plane in LDS
-constexpr int S2_QN = S2_QX * S2_QY;
-constexpr int S2_OWN = (S2_QN + S2_THREADS - 1) / S2_THREADS;      // psi' sites per thread
-constexpr int S2_RING = S2_PX * S2_PY - S2_QN;                     // psi sites outside the psi' tile
-static_assert(S2_RING <= S2_THREADS, "one frame site per thread");
+//
+// Bound by the vector ALUs and by the latency of one plane's chain (loads, LDS, two updates).  So: the
+// update's coefficients (an IEEE division) are computed once per site and kept for its second step;
+// psi and psi' planes alternate between two LDS buffers, which leaves one barrier per plane; the next
+// plane's loads are issued in the middle of a plane, into the registers whose values are done, without
+// branches (a load outside the lattice takes another site and is masked); six planes are unrolled, the
+// common period of the register roles, so that nothing is moved between them.
+//
+// Tile: 32 x 13 sites, whose psi' tile (34 x 15) is two sites for each of 256 threads, so that a thread needs
+// 90 (complex64) or 140 (complex128) registers and a compute unit holds five or three blocks.  us per step
+// on an MI355X, complex64 128^3 x 3 states / 150^3 x 2 / 256^3 x 3, complex128 150^3 x 2 / 256^3 x 2:
+//   64 x 16, 256 threads, 5 sites each (198 registers)  17.6 / 24.1 / 143, -
+//   32 x 16, 320 threads                                15.0 / 19.9 / 147, 41.3 / 195
+//   64 x 5,  256 threads                                15.5 / 20.5 / 139, -
+//   32 x 13, 256 threads                                15.0 / 15.9 / 138, 27.2 / 151
+// against 18.4 / 29.2 / 161 for the earlier 64 x 16 kernel with two barriers per plane, and 60.3 / 285 for
+// single steps in complex128.
+template <typename T> struct S2 {
+  static constexpr int TX = 32, TY = 13, NT = 256;
+  static constexpr int PX = TX + 4, PY = TY + 4;                // psi plane in LDS
+  static constexpr int QX = TX + 2, QY = TY + 2, QN = QX * QY;  // psi' plane in LDS
+  static constexpr int OWN = (QN + NT - 1) / NT;                // psi' sites per thread
+  static constexpr int RING = PX * PY - QN;                     // psi sites outside the psi' tile
+  static_assert(RING <= NT, "one frame site per thread");
+};
 
-__host__ __device__ inline int stencil2_tiles(int N, int k) {
-  return k * ((N + S2_TX - 1) / S2_TX) * ((N + S2_TY - 1) / S2_TY) * ((N + S2_CZ - 1) / S2_CZ);
+// Planes per tile.  A tile of CZ planes computes psi' on CZ + 2, so long marches do less work, and short ones
+// fill the chip and are a shorter chain: 32 planes while that leaves four blocks per compute unit, 16
+// while it leaves one and a half, else less.  us per step, complex64: 64^3 x 3 states 8 planes 12.5 (the
+// earlier kernel), 2 planes 5.3; 128^3 x 3 states 8 / 16 / 32 planes 18.3 / 15.0 / 16.1; 256^3 x 3
+// states 16 / 32 planes 138 / 135.
+__host__ __device__ inline int stencil2_cz(int N, int k) {
+  const long long cols = (long long)k * ((N + S2<float>::TX - 1) / S2<float>::TX) * ((N + S2<float>::TY - 1) / S2<float>::TY);
+  int cz = 32;
+  while (cz > 2 && cols * ((N + cz - 1) / cz) < (cz == 32 ? 1024 : 384)) cz /= 2;
+  return cz;
+}
+int stencil2_cz_host(int N, int k) { return stencil2_cz(N, k); }
+int stencil2_tiles_host(int N, int k, int cz) {
+  return k * ((N + S2<float>::TX - 1) / S2<float>::TX) * ((N + S2<float>::TY - 1) / S2<float>::TY) * ((N + cz - 1) / cz);
 }
 
-// psi-plane coordinates of frame site j: rows 0 and S2_PY - 1, then columns 0 and S2_PX - 1
-// of the rows in between
+// psi-plane coordinates of frame site j: rows 0 and PY - 1, then columns 0 and PX - 1 of the rows in
+// between
+template <typename T>
 __device__ __forceinline__ void s2_frame_site(int j, int &py, int &px) {
-  if (j < S2_PX) { py = 0; px = j; }
-  else if (j < 2 * S2_PX) { py = S2_PY - 1; px = j - S2_PX; }
-  else { const int jj = j - 2 * S2_PX; py = 1 + (jj >> 1); px = (jj & 1) ? S2_PX - 1 : 0; }
+  constexpr int PX = S2<T>::PX, PY = S2<T>::PY;
+  if (j < PX) { py = 0; px = j; }
+  else if (j < 2 * PX) { py = PY - 1; px = j - PX; }
+  else { const int jj = j - 2 * PX; py = 1 + (jj >> 1); px = (jj & 1) ? PX - 1 : 0; }
 }
 
-template <bool VC>
-__device__ __forceinline__ void stencil2_tile(const float2 *__restrict__ sp, float2 *__restrict__ dp,
+// the update's coefficients at one site, and the update with them (the operations of fdtd_update)
+template <typename T, bool VC> struct FdtdCoef;
+template <typename T> struct FdtdCoef<T, false> {
+  T A, Bc;
+  __device__ __forceinline__ void set(T V, T c, T hdt) {
+    const T B = (T)1 / fmaT(hdt, V, (T)1);
+    A = fmaT(-hdt, V, (T)1) * B;
+    Bc = B * c;
+  }
+  __device__ __forceinline__ C<T> step(C<T> cur, C<T> acc, T) const {
+    return mkc<T>(fmaT(A, cur.x, Bc * acc.x), fmaT(A, cur.y, Bc * acc.y));
+  }
+};
+template <typename T> struct FdtdCoef<T, true> {
+  C<T> A, B;
+  __device__ __forceinline__ void set(C<T> V, T c, T hdt) {
+    const T dr = fmaT(hdt, V.x, (T)1), di = hdt * V.y;
+    const T den = (T)1 / fmaT(dr, dr, di * di);
+    B = mkc<T>(dr * den, -di * den);
+    A = cmul(mkc<T>(fmaT(-hdt, V.x, (T)1), -hdt * V.y), B);
+  }
+  __device__ __forceinline__ C<T> step(C<T> cur, C<T> acc, T c) const {
+    return cadd(cmul(A, cur), cmul(B, cscale(acc, c)));
+  }
+};
+
+template <typename T, bool VC>
+__device__ __forceinline__ void stencil2_tile(const C<T> *__restrict__ sp, C<T> *__restrict__ dp,
                                               const void *__restrict__ vtab, int N, int x0, int y0, int z0,
-                                              int z1, float c, float hdt, float2 *P, float2 *Q) {
-  using VT = typename VType<float, VC>::type;
+                                              int z1, T c, T hdt, C<T> *P, C<T> *Q) {
+  using VT = typename VType<T, VC>::type;
+  constexpr int PX = S2<T>::PX, QX = S2<T>::QX, OWN = S2<T>::OWN, NT = S2<T>::NT, QN = S2<T>::QN;
+  constexpr int PN = PX * S2<T>::PY;
   const int N2 = N * N;
-  const float2 zero = make_float2(0.f, 0.f);
-  VT vzero;
-  if constexpr (VC) vzero = zero; else vzero = 0.f;
+  const C<T> zero = mkc<T>(0, 0);
   const int t = threadIdx.x;
-  // psi' sites of this thread: i = t + q S2_THREADS over the (S2_QY x S2_QX) tile
-  int qoff[S2_OWN], pa[S2_OWN], qa[S2_OWN];
-  bool own[S2_OWN], lat[S2_OWN], out[S2_OWN];
+  // psi' sites of this thread: i = t + q NT over the QY x QX tile
+  int qoff[OWN], pa[OWN], qa[OWN];
+  bool own[OWN], lat[OWN], out[OWN];
 #pragma unroll
-  for (int q = 0; q < S2_OWN; ++q) {
-    const int i = t + q * S2_THREADS;
-    own[q] = i < S2_QN;
-    const int qy = own[q] ? i / S2_QX : 0, qx = own[q] ? i - (i / S2_QX) * S2_QX : 0;
+  for (int q = 0; q < OWN; ++q) {
+    const int i = t + q * NT;
+    own[q] = i < QN;
+    const int qy = own[q] ? i / QX : 0, qx = own[q] ? i - (i / QX) * QX : 0;
     const int y = y0 - 1 + qy, x = x0 - 1 + qx;
     lat[q] = own[q] && y >= 0 && y < N && x >= 0 && x < N;
-    out[q] = lat[q] && qy >= 1 && qy <= S2_TY && qx >= 1 && qx <= S2_TX;
+    out[q] = lat[q] && qy >= 1 && qy <= S2<T>::TY && qx >= 1 && qx <= S2<T>::TX;
     qoff[q] = lat[q] ? y * N + x : 0;
-    pa[q] = (qy + 1) * S2_PX + qx + 1;     // its psi-plane address
-    qa[q] = qy * S2_QX + qx;               // its psi'-plane address
+    pa[q] = (qy + 1) * PX + qx + 1;     // its psi-plane address
+    qa[q] = qy * QX + qx;               // its psi'-plane address
   }
   // frame site of this thread (psi only)
+  const bool ring = t < S2<T>::RING;
   int fa = 0, foff = 0;
   bool flat = false;
-  if (t < S2_RING) {
+  if (ring) {
     int py, px;
-    s2_frame_site(t, py, px);
+    s2_frame_site<T>(t, py, px);
     const int y = y0 - 2 + py, x = x0 - 2 + px;
     flat = y >= 0 && y < N && x >= 0 && x < N;
     foff = flat ? y * N + x : 0;
-    fa = py * S2_PX + px;
+    fa = py * PX + px;
   }
-  auto ld = [&](int z, int off, bool ok) -> float2 {
-    return (ok && z >= 0 && z < N) ? sp[z * N2 + off] : zero;
+  // a plane's values, zero outside the lattice
+  auto plane = [&](int z) -> const C<T> * { return sp + (size_t)(z < 0 ? 0 : z >= N ? N - 1 : z) * N2; };
+  auto load = [&](C<T> (&v)[OWN], int z) {
+    const C<T> *g = plane(z);
+    const bool zin = z >= 0 && z < N;
+#pragma unroll
+    for (int q = 0; q < OWN; ++q) v[q] = g[qoff[q]];
+#pragma unroll
+    for (int q = 0; q < OWN; ++q)
+      if (!(zin && lat[q])) v[q] = zero;
   };
-  // registers per psi' site: psi at zp - 1 and zp, psi' at zp - 2 and zp - 1, V at zp - 1
-  float2 pp[S2_OWN], pc[S2_OWN], qm2[S2_OWN], qm1[S2_OWN];
-  VT vm1[S2_OWN];
+  auto load_pot = [&](VT (&v)[OWN], int z) {
+    const VT *g = (const VT *)vtab + (size_t)(z < 0 ? 0 : z >= N ? N - 1 : z) * N2;
 #pragma unroll
-  for (int q = 0; q < S2_OWN; ++q) {
-    pp[q] = ld(z0 - 2, qoff[q], lat[q]);
-    pc[q] = ld(z0 - 1, qoff[q], lat[q]);
-    qm2[q] = zero;
-    qm1[q] = zero;
-    vm1[q] = vzero;
-  }
-  for (int zp = z0 - 1; zp <= z1; ++zp) {
+    for (int q = 0; q < OWN; ++q) v[q] = g[qoff[q]];
+  };
+  auto load_frame = [&](int z) -> C<T> {
+    const C<T> v = plane(z)[foff];
+    return flat && z >= 0 && z < N ? v : zero;
+  };
+  using Coef = FdtdCoef<T, VC>;
+  // registers per psi' site: psi at three planes, psi' at three, V of the next plane, coefficients of two
+  C<T> a0[OWN], a1[OWN], a2[OWN], b0[OWN], b1[OWN], b2[OWN], fv;
+  VT v[OWN];
+  Coef k0[OWN], k1[OWN];
+  load(a0, z0 - 2);
+  load(a1, z0 - 1);
+  load(a2, z0);
+  load_pot(v, z0 - 1);
+  fv = load_frame(z0 - 1);
+#pragma unroll
+  for (int q = 0; q < OWN; ++q) b0[q] = b1[q] = zero;
+  // Plane zp: pp, pc, pn are psi at zp - 1, zp, zp + 1, qm2, qm1 psi' at zp - 2, zp - 1, q0 becomes psi'
+  // at zp, km the coefficients at zp - 1 and kc those of zp; pp takes psi at zp + 2.  S: LDS buffers of
+  // this plane (0, 1).
+  auto step = [&](int zp, int S, C<T> (&pp)[OWN], C<T> (&pc)[OWN], C<T> (&pn)[OWN], C<T> (&qm2)[OWN],
+                  C<T> (&qm1)[OWN], C<T> (&q0)[OWN], Coef (&km)[OWN], Coef (&kc)[OWN]) {
+    C<T> *Pb = P + S * PN, *Qb = Q + S * QN;
+    const C<T> *Qo = Q + (1 - S) * QN;
     const bool zin = zp >= 0 && zp < N;
-    float2 pn[S2_OWN];
-    VT v0[S2_OWN];
-#pragma unroll
-    for (int q = 0; q < S2_OWN; ++q) {
-      pn[q] = ld(zp + 1, qoff[q], lat[q]);
-      v0[q] = (lat[q] && zin) ? load_v<float, VC>(vtab, zp * N2 + qoff[q]) : vzero;
-    }
-    const float2 fv = t < S2_RING ? ld(zp, foff, flat) : zero;
     // psi(zp) over the tile and its frame of width 2
 #pragma unroll
-    for (int q = 0; q < S2_OWN; ++q)
-      if (own[q]) P[pa[q]] = pc[q];
-    if (t < S2_RING) P[fa] = fv;
+    for (int q = 0; q < OWN; ++q)
+      if (QN % NT == 0 || q < OWN - 1 || own[q]) Pb[pa[q]] = pc[q];
+    if (ring) Pb[fa] = fv;
+#pragma unroll
+    for (int q = 0; q < OWN; ++q) kc[q].set(v[q], c, hdt);
+    load_pot(v, zp + 1);
+    fv = load_frame(zp + 1);
     __syncthreads();
     // psi'(zp) over the tile and its frame of width 1
-    float2 q0[S2_OWN];
 #pragma unroll
-    for (int q = 0; q < S2_OWN; ++q) {
-      q0[q] = zero;
-      if (lat[q] && zin) {
-        const int a = pa[q];
-        const float2 l = P[a - 1], rr = P[a + 1], yu = P[a - S2_PX], yd = P[a + S2_PX];
-        float2 acc = csub(cadd(pp[q], pn[q]), cscale(pc[q], 6.f));
-        acc = cadd(acc, cadd(cadd(l, rr), cadd(yu, yd)));
-        q0[q] = fdtd_update<float, VC>(pc[q], acc, v0[q], c, hdt);
-      }
+    for (int q = 0; q < OWN; ++q) {
+      const int a = pa[q];
+      const C<T> l = Pb[a - 1], rr = Pb[a + 1], yu = Pb[a - PX], yd = Pb[a + PX];
+      C<T> acc = csub(cadd(pp[q], pn[q]), cscale(pc[q], (T)6));
+      acc = cadd(acc, cadd(cadd(l, rr), cadd(yu, yd)));
+      const C<T> r = kc[q].step(pc[q], acc, c);
+      q0[q] = zin && lat[q] ? r : zero;
     }
-    // psi''(zp - 1) over the tile; the psi' plane in LDS holds psi'(zp - 1)
+    load(pp, zp + 2);
+    // psi''(zp - 1) over the tile
     const int zo = zp - 1;
     if (zo >= z0) {
 #pragma unroll
-      for (int q = 0; q < S2_OWN; ++q) {
-        if (out[q]) {
-          const int a = qa[q];
-          const float2 l = Q[a - 1], rr = Q[a + 1], yu = Q[a - S2_QX], yd = Q[a + S2_QX];
-          float2 acc = csub(cadd(qm2[q], q0[q]), cscale(qm1[q], 6.f));
-          acc = cadd(acc, cadd(cadd(l, rr), cadd(yu, yd)));
-          dp[zo * N2 + qoff[q]] = fdtd_update<float, VC>(qm1[q], acc, vm1[q], c, hdt);
-        }
+      for (int q = 0; q < OWN; ++q) {
+        const int a = qa[q];
+        // sites on the rim of the psi' tile have no output; their neighbours' addresses stay in the
+        // buffers (Q has a row of slack on both sides)
+        const C<T> l = Qo[a - 1], rr = Qo[a + 1], yu = Qo[a - QX], yd = Qo[a + QX];
+        C<T> acc = csub(cadd(qm2[q], q0[q]), cscale(qm1[q], (T)6));
+        acc = cadd(acc, cadd(cadd(l, rr), cadd(yu, yd)));
+        const C<T> r = km[q].step(qm1[q], acc, c);
+        if (out[q]) dp[(size_t)zo * N2 + qoff[q]] = r;
       }
     }
-    __syncthreads();
 #pragma unroll
-    for (int q = 0; q < S2_OWN; ++q) {
-      if (own[q]) Q[qa[q]] = q0[q];
-      pp[q] = pc[q];
-      pc[q] = pn[q];
-      qm2[q] = qm1[q];
-      qm1[q] = q0[q];
-      vm1[q] = v0[q];
-    }
+    for (int q = 0; q < OWN; ++q)
+      if (QN % NT == 0 || q < OWN - 1 || own[q]) Qb[qa[q]] = q0[q];
+  };
+  for (int zp = z0 - 1;;) {
+    step(zp, 0, a0, a1, a2, b0, b1, b2, k0, k1);
+    if (++zp > z1) break;
+    step(zp, 1, a1, a2, a0, b1, b2, b0, k1, k0);
+    if (++zp > z1) break;
+    step(zp, 0, a2, a0, a1, b2, b0, b1, k0, k1);
+    if (++zp > z1) break;
+    step(zp, 1, a0, a1, a2, b0, b1, b2, k1, k0);
+    if (++zp > z1) break;
+    step(zp, 0, a1, a2, a0, b1, b2, b0, k0, k1);
+    if (++zp > z1) break;
+    step(zp, 1, a2, a0, a1, b2, b0, b1, k1, k0);
+    if (++zp > z1) break;
   }
 }
 
-__global__ void __launch_bounds__(S2_THREADS) k_stencil2(const LaunchList L) {
-  __shared__ float2 P[S2_PX * S2_PY];
-  __shared__ float2 Q[S2_QN];
+// VC: complex potentials (kernels of their own: twice the coefficients in registers)
+template <typename T, bool VC>
+__global__ void __launch_bounds__(S2<T>::NT) k_stencil2(const LaunchList L) {
+  using H = S2<T>;
+  // psi' rim sites read a row beyond their plane: slack before and after the two planes
+  __shared__ C<T> P[2 * H::PX * H::PY];
+  __shared__ C<T> Qs[2 * H::QN + 2 * (H::QX + 1)];
   // tiles are ordered as those of the single-step stencil (states of a tile adjacent, runs of
   // 48 tiles per XCD)
   const int blk = xcd_block_chunked(blockIdx.x, gridDim.x, 48);
   const int e = find_entry(L, blk);
   const PassDesc &d = *(const PassDesc *)L.descp[e];
   const uint32_t mode = L.mode[e];
-  const int N = d.N;
-  const int ntx = (N + S2_TX - 1) / S2_TX, nty = (N + S2_TY - 1) / S2_TY;
+  const int N = d.N, cz = L.aux[e];
+  const int ntx = (N + H::TX - 1) / H::TX, nty = (N + H::TY - 1) / H::TY;
   int t = blk - L.tile_start[e];
   const int s = t % d.k; t /= d.k;
   const int bx = t % ntx; t /= ntx;
   const int by = t % nty; t /= nty;
   const int bz = t;
   const size_t N3 = (size_t)N * N * N;
-  const float2 *sp = (const float2 *)((mode & M_SWAP) ? d.alt : d.psi) + (size_t)s * N3;
-  float2 *dp = (float2 *)((mode & M_SWAP) ? d.psi : d.alt) + (size_t)s * N3;
-  const float c = (float)d.stencil_c, hdt = (float)(0.5 * d.dt);
-  const int z0 = bz * S2_CZ;
-  const int z1 = (z0 + S2_CZ < N) ? z0 + S2_CZ : N;
-  if (d.vcomplex) stencil2_tile<true>(sp, dp, d.vtab, N, bx * S2_TX, by * S2_TY, z0, z1, c, hdt, P, Q);
-  else stencil2_tile<false>(sp, dp, d.vtab, N, bx * S2_TX, by * S2_TY, z0, z1, c, hdt, P, Q);
+  const C<T> *sp = (const C<T> *)((mode & M_SWAP) ? d.alt : d.psi) + (size_t)s * N3;
+  C<T> *dp = (C<T> *)((mode & M_SWAP) ? d.psi : d.alt) + (size_t)s * N3;
+  const T c = (T)d.stencil_c, hdt = (T)(0.5 * d.dt);
+  const int z0 = bz * cz;
+  const int z1 = (z0 + cz < N) ? z0 + cz : N;
+  C<T> *Q = Qs + H::QX + 1;
+  stencil2_tile<T, VC>(sp, dp, d.vtab, N, bx * H::TX, by * H::TY, z0, z1, c, hdt, P, Q);
 }
 
 // ---------------------------------------------------------------- parity
@@ -986,9 +1083,13 @@ void launch_to64_slot(bool dbl, double2 *dst, const void *src, size_t n, hipStre
 }
 
 int ew_tiles_host(long long n) { return ew_tiles(n); }
-int stencil_tiles_host(int N, int k) { return stencil_tiles(N, k); }
-int stencil2_tiles_host(int N, int k) { return stencil2_tiles(N, k); }
-const void *stencil2_kernel() { return (const void *)k_stencil2; }
+int stencil_cz_host(int N, int k) { return stencil_cz(N, k); }
+int stencil_tiles_host(int N, int k, int cz) { return stencil_tiles(N, k, cz); }
+const void *stencil2_kernel(bool dbl, bool vc) {
+  if (dbl) return vc ? (const void *)k_stencil2<double, true> : (const void *)k_stencil2<double, false>;
+  return vc ? (const void *)k_stencil2<float, true> : (const void *)k_stencil2<float, false>;
+}
+int stencil2_threads() { return S2<float>::NT; }
 
 const void *stencil_kernel(bool dbl) {
   return dbl ? (const void *)k_stencil<double> : (const void *)k_stencil<float>;

@@ -278,7 +278,6 @@ __host__ __device__ inline int size_group(int N) {
 // Threads per block of each kernel family.
 constexpr int LINE_THREADS = 256;
 constexpr int RED_THREADS = 256;
-constexpr int S2_THREADS = 256;      // block of the two-step stencil
 
 // Rows of N sites per row-pass block, and x3 columns per column-pass tile; the kernels and the
 // host's grid sizes use these same functions.  A row block holds enough rows that the largest

@@ -47,9 +47,12 @@ void launch_from64_slot(bool dbl, void *dst, const double2 *src, size_t n, hipSt
 void launch_noise(bool dbl, void *dst, size_t n, uint64_t seed, int slot, hipStream_t st);
 void launch_to64_slot(bool dbl, double2 *dst, const void *src, size_t n, hipStream_t st);
 int ew_tiles_host(long long n);
-int stencil_tiles_host(int N, int k);
-int stencil2_tiles_host(int N, int k);
-const void *stencil2_kernel();
+int stencil_cz_host(int N, int k);
+int stencil_tiles_host(int N, int k, int cz);
+int stencil2_cz_host(int N, int k);
+int stencil2_tiles_host(int N, int k, int cz);
+const void *stencil2_kernel(bool dbl, bool vc);
+int stencil2_threads();
 const void *stencil_kernel(bool dbl);
 void launch_parity(const LaunchList &L, int total, bool dbl, hipStream_t st);
 void launch_to64(const LaunchList &L, int total, bool dbl, hipStream_t st);
@@ -247,7 +250,7 @@ struct qfdtd_ctx {
   uint32_t set_mask = 0;
   bool poisoned = false;
   int cur = 0;                  // H_K^(0): 1 when the state sits in alt
-  bool stencil2 = false;        // H_K^(0), complex64: two fused steps per stencil pass
+  bool stencil2 = false;        // H_K^(0): two fused steps per stencil pass
   int trace_on = 0;
   int64_t trace_cap = 0, trace_n = 0;
   double *h_words = nullptr;    // pinned: PassDesc::h_energy and, at 4 MAX_STATES, the evolve status
@@ -519,7 +522,7 @@ qfdtd_status run_family(Fam f, std::vector<Entry> &es, bool dbl, int KS, hipStre
       case F_COL: go(fcol, LINE_THREADS, lds); break;
       case F_PENCIL: go(split_of(c0).pencil, split_of(c0).pencil_nt, lds); break;
       case F_STENCIL: go(stencil_kernel(dbl), RED_THREADS, 0); break;
-      case F_STENCIL2: go(stencil2_kernel(), S2_THREADS, 0); break;
+      case F_STENCIL2: go(stencil2_kernel(dbl, c0->vcomplex), stencil2_threads(), 0); break;
       case F_PARITY: launch_parity(L, total, dbl, st); break;
       case F_TO64: launch_to64(L, total, dbl, st); break;
       case F_GRAM: launch_gram(L, total, KS, dbl, st); break;
@@ -707,7 +710,7 @@ qfdtd_status run_chunk_on(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n, hip
   const bool dbl = ms[0]->dbl;
   int maxn = 0;
   for (int v : n) maxn = v > maxn ? v : maxn;
-  std::vector<Entry> pl, rw, c2, c1, sten, sten2, sl, pen;
+  std::vector<Entry> pl, rw, c2, c1, sten, sten2[2], sl, pen;     // sten2: real and complex V
   // chunk start: h then forward transforms along x3 (and x2)
   for (size_t j = 0; j < ms.size(); ++j) {
     qfdtd_ctx *c = ms[j];
@@ -730,7 +733,7 @@ qfdtd_status run_chunk_on(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n, hip
   QF_TRY(run_family(F_ROW, rw, dbl, 0, st));
   QF_TRY(run_family(F_COL, c2, dbl, 0, st));
   for (int s = 0; s < maxn; ++s) {
-    c1.clear(); c2.clear(); pl.clear(); rw.clear(); sten.clear(); sten2.clear(); sl.clear(); pen.clear();
+    c1.clear(); c2.clear(); pl.clear(); rw.clear(); sten.clear(); sten2[0].clear(); sten2[1].clear(); sl.clear(); pen.clear();
     std::vector<Entry> c2f;
     for (size_t j = 0; j < ms.size(); ++j) {
       qfdtd_ctx *c = ms[j];
@@ -740,8 +743,14 @@ qfdtd_status run_chunk_on(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n, hip
         // one single step
         const uint32_t sw = c->cur ? (uint32_t)M_SWAP : 0u;
         if (c->stencil2 && (s & 1)) continue;                // advanced by the pass at s - 1
-        if (c->stencil2 && s + 1 < n[j]) sten2.push_back({c, 0, sw, stencil2_tiles_host(c->N, c->k), 0});
-        else sten.push_back({c, 0, sw, stencil_tiles_host(c->N, c->k), 0});
+        if (c->stencil2 && s + 1 < n[j]) {
+          const int cz = stencil2_cz_host(c->N, c->k);
+          sten2[c->vcomplex].push_back({c, 0, sw, stencil2_tiles_host(c->N, c->k, cz), cz});
+        }
+        else {
+          const int cz = stencil_cz_host(c->N, c->k);
+          sten.push_back({c, 0, sw, stencil_tiles_host(c->N, c->k, cz), cz});
+        }
         c->cur ^= 1;
         continue;
       }
@@ -770,7 +779,8 @@ qfdtd_status run_chunk_on(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n, hip
     QF_TRY(run_family(F_PLANE, pl, dbl, 0, st));
     QF_TRY(run_family(F_ROW, rw, dbl, 0, st));
     QF_TRY(run_family(F_COL, c2f, dbl, 0, st));
-    QF_TRY(run_family(F_STENCIL2, sten2, dbl, 0, st));
+    QF_TRY(run_family(F_STENCIL2, sten2[0], dbl, 0, st));
+    QF_TRY(run_family(F_STENCIL2, sten2[1], dbl, 0, st));
     QF_TRY(run_family(F_STENCIL, sten, dbl, 0, st));
   }
   return QFDTD_OK;
@@ -1176,7 +1186,7 @@ qfdtd_status qfdtd_create(qfdtd_ctx **out, int32_t N, double a, double m, int32_
   c->nblk_red = red_blocks(n3);
   c->trace_on = o.trace_energies ? 1 : 0;
   c->graphs = !(o.flags & QFDTD_F_NO_GRAPH);
-  c->stencil2 = !c->fft() && !c->dbl && !(o.flags & QFDTD_F_STENCIL_1STEP);
+  c->stencil2 = !c->fft() && !(o.flags & QFDTD_F_STENCIL_1STEP);
   c->serial = g_next_serial.fetch_add(1);
   c->trace_cap = c->trace_on ? 4096 : 0;
 
