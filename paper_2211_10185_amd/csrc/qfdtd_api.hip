@@ -674,43 +674,40 @@ qfdtd_status run_chunk_grouped(qfdtd_ctx *c, int n) {
   const bool dbl = c->dbl;
   QF_HIP(c, hipEventRecord(c->ev_fork, c->st));
   for (int g = 0; g < c->ngroups; ++g) QF_HIP(c, hipStreamWaitEvent(c->gst[g], c->ev_fork, 0));
-  for (int g = 0; g < c->ngroups; ++g) {
-    const int which = 2 + g, kg = c->gk[g];
-    hipStream_t st = c->gst[g];
-    if (c->split) {
-      for (int s = 0; s <= n; ++s) {
-        std::vector<Entry> pe, sl, pl;
+  // step by step over the groups, so that every group starts at once (a launch costs the host about
+  // 4 us, directly or as a node of a graph: a whole chunk of one group first left the others idle for
+  // its 100 launches)
+  for (int s = 0; s <= n; ++s) {
+    for (int g = 0; g < c->ngroups; ++g) {
+      const int which = 2 + g, kg = c->gk[g];
+      hipStream_t st = c->gst[g];
+      std::vector<Entry> pe, c1, sl, pl;
+      if (c->split) {
         if (s > 0) pe.push_back(split_pencil(c, which, kg, s - 1, n));
         split_real(c, which, kg, s, n, sl, pl);
-        QF_TRY(run_family(F_PENCIL, pe, dbl, 0, st));
-        QF_TRY(run_family(F_SLAB, sl, dbl, 0, st));
-        QF_TRY(run_family(F_PLANE, pl, dbl, 0, st));
+      } else {
+        if (s > 0) c1.push_back({c, which, M_FWD | M_KIN | M_INV | M_AXIS1, col_tiles(c->N, kg, dbl), 0});
+        const uint32_t mode = s == 0 ? M_PRE | M_FWD : s == n ? M_INV | M_POST : M_INV | M_MID | M_FWD;
+        pl.push_back({c, which, mode, plane_tiles(c->N, kg), 0});
       }
-      QF_HIP(c, hipEventRecord(c->ev_join[g], st));
-      continue;
-    }
-    std::vector<Entry> pl{{c, which, M_PRE | M_FWD, plane_tiles(c->N, kg), 0}};
-    QF_TRY(run_family(F_PLANE, pl, dbl, 0, st));
-    for (int s = 0; s < n; ++s) {
-      std::vector<Entry> c1{{c, which, M_FWD | M_KIN | M_INV | M_AXIS1, col_tiles(c->N, kg, dbl), 0}};
-      const uint32_t rs = (s == n - 1) ? (M_INV | M_POST) : (M_INV | M_MID | M_FWD);
-      std::vector<Entry> p2{{c, which, rs, plane_tiles(c->N, kg), 0}};
+      QF_TRY(run_family(F_PENCIL, pe, dbl, 0, st));
       QF_TRY(run_family(F_COL, c1, dbl, 0, st));
-      QF_TRY(run_family(F_PLANE, p2, dbl, 0, st));
+      QF_TRY(run_family(F_SLAB, sl, dbl, 0, st));
+      QF_TRY(run_family(F_PLANE, pl, dbl, 0, st));
     }
-    QF_HIP(c, hipEventRecord(c->ev_join[g], st));
   }
-  for (int g = 0; g < c->ngroups; ++g) QF_HIP(c, hipStreamWaitEvent(c->st, c->ev_join[g], 0));
+  for (int g = 0; g < c->ngroups; ++g) {
+    QF_HIP(c, hipEventRecord(c->ev_join[g], c->gst[g]));
+    QF_HIP(c, hipStreamWaitEvent(c->st, c->ev_join[g], 0));
+  }
   return QFDTD_OK;
 }
 
 // The passes of one chunk of the members (n[j] steps each), one launch per pass kind and size, on
-// stream `st`.
-qfdtd_status run_chunk_on(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n, hipStream_t st) {
+// stream `st`: its start (s = -1) or its step s.
+qfdtd_status chunk_start(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n, hipStream_t st) {
   const bool dbl = ms[0]->dbl;
-  int maxn = 0;
-  for (int v : n) maxn = v > maxn ? v : maxn;
-  std::vector<Entry> pl, rw, c2, c1, sten, sten2[2], sl, pen;     // sten2: real and complex V
+  std::vector<Entry> pl, rw, c2, sl;
   // chunk start: h then forward transforms along x3 (and x2)
   for (size_t j = 0; j < ms.size(); ++j) {
     qfdtd_ctx *c = ms[j];
@@ -731,59 +728,59 @@ qfdtd_status run_chunk_on(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n, hip
   QF_TRY(run_by_size(F_SLAB, sl, dbl, st));
   QF_TRY(run_family(F_PLANE, pl, dbl, 0, st));
   QF_TRY(run_family(F_ROW, rw, dbl, 0, st));
-  QF_TRY(run_family(F_COL, c2, dbl, 0, st));
-  for (int s = 0; s < maxn; ++s) {
-    c1.clear(); c2.clear(); pl.clear(); rw.clear(); sten.clear(); sten2[0].clear(); sten2[1].clear(); sl.clear(); pen.clear();
-    std::vector<Entry> c2f;
-    for (size_t j = 0; j < ms.size(); ++j) {
-      qfdtd_ctx *c = ms[j];
-      if (s >= n[j]) continue;
-      if (!c->fft()) {
-        // two fused steps at even s while two steps remain; a chunk of odd length ends with
-        // one single step
-        const uint32_t sw = c->cur ? (uint32_t)M_SWAP : 0u;
-        if (c->stencil2 && (s & 1)) continue;                // advanced by the pass at s - 1
-        if (c->stencil2 && s + 1 < n[j]) {
-          const int cz = stencil2_cz_host(c->N, c->k);
-          sten2[c->vcomplex].push_back({c, 0, sw, stencil2_tiles_host(c->N, c->k, cz), cz});
-        }
-        else {
-          const int cz = stencil_cz_host(c->N, c->k);
-          sten.push_back({c, 0, sw, stencil_tiles_host(c->N, c->k, cz), cz});
-        }
-        c->cur ^= 1;
-        continue;
+  return run_family(F_COL, c2, dbl, 0, st);
+}
+qfdtd_status chunk_step(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n, int s, hipStream_t st) {
+  if (s < 0) return chunk_start(ms, n, st);
+  const bool dbl = ms[0]->dbl;
+  std::vector<Entry> pl, rw, c2, c2f, c1, sten, sten2[2], sl, pen;     // sten2: real and complex V
+  for (size_t j = 0; j < ms.size(); ++j) {
+    qfdtd_ctx *c = ms[j];
+    if (s >= n[j]) continue;
+    if (!c->fft()) {
+      // two fused steps at even s while two steps remain; a chunk of odd length ends with
+      // one single step
+      const uint32_t sw = c->cur ? (uint32_t)M_SWAP : 0u;
+      if (c->stencil2 && (s & 1)) continue;                // advanced by the pass at s - 1
+      if (c->stencil2 && s + 1 < n[j]) {
+        const int cz = stencil2_cz_host(c->N, c->k);
+        sten2[c->vcomplex].push_back({c, 0, sw, stencil2_tiles_host(c->N, c->k, cz), cz});
       }
-      const bool last = (s == n[j] - 1);
-      if (c->split) {
-        pen.push_back(split_pencil(c, 0, c->k, s, n[j]));
-        split_real(c, 0, c->k, s + 1, n[j], sl, pl);
-        continue;
-      }
-      const bool ab = c->scheme == SCHEME_AB;
-      const uint32_t onalt = ab ? (uint32_t)M_ALT : 0u;
-      uint32_t rs = last ? (M_INV | M_POST) : (M_INV | M_MID | M_FWD);
-      if (ab) rs = last ? (uint32_t)(M_INV | M_COMB) : (uint32_t)(M_INV | M_COMB | M_FWD | M_ALT);
-      c1.push_back({c, 0, M_FWD | M_KIN | M_INV | M_AXIS1 | onalt, col_tiles(c->N, c->k, dbl), 0});
-      if (c->plane) pl.push_back({c, 0, rs, plane_tiles(c->N, c->k), 0});
       else {
-        c2.push_back({c, 0, M_INV | onalt, col_tiles(c->N, c->k, dbl), 0});
-        rw.push_back({c, 0, rs, row_tiles(c->N, c->k, dbl), 0});
-        if (!last) c2f.push_back({c, 0, M_FWD | onalt, col_tiles(c->N, c->k, dbl), 0});
+        const int cz = stencil_cz_host(c->N, c->k);
+        sten.push_back({c, 0, sw, stencil_tiles_host(c->N, c->k, cz), cz});
       }
+      c->cur ^= 1;
+      continue;
     }
-    QF_TRY(run_family(F_COL, c1, dbl, 0, st));
-    QF_TRY(run_family(F_COL, c2, dbl, 0, st));
-    QF_TRY(run_by_size(F_PENCIL, pen, dbl, st));
-    QF_TRY(run_by_size(F_SLAB, sl, dbl, st));
-    QF_TRY(run_family(F_PLANE, pl, dbl, 0, st));
-    QF_TRY(run_family(F_ROW, rw, dbl, 0, st));
-    QF_TRY(run_family(F_COL, c2f, dbl, 0, st));
-    QF_TRY(run_family(F_STENCIL2, sten2[0], dbl, 0, st));
-    QF_TRY(run_family(F_STENCIL2, sten2[1], dbl, 0, st));
-    QF_TRY(run_family(F_STENCIL, sten, dbl, 0, st));
+    const bool last = (s == n[j] - 1);
+    if (c->split) {
+      pen.push_back(split_pencil(c, 0, c->k, s, n[j]));
+      split_real(c, 0, c->k, s + 1, n[j], sl, pl);
+      continue;
+    }
+    const bool ab = c->scheme == SCHEME_AB;
+    const uint32_t onalt = ab ? (uint32_t)M_ALT : 0u;
+    uint32_t rs = last ? (M_INV | M_POST) : (M_INV | M_MID | M_FWD);
+    if (ab) rs = last ? (uint32_t)(M_INV | M_COMB) : (uint32_t)(M_INV | M_COMB | M_FWD | M_ALT);
+    c1.push_back({c, 0, M_FWD | M_KIN | M_INV | M_AXIS1 | onalt, col_tiles(c->N, c->k, dbl), 0});
+    if (c->plane) pl.push_back({c, 0, rs, plane_tiles(c->N, c->k), 0});
+    else {
+      c2.push_back({c, 0, M_INV | onalt, col_tiles(c->N, c->k, dbl), 0});
+      rw.push_back({c, 0, rs, row_tiles(c->N, c->k, dbl), 0});
+      if (!last) c2f.push_back({c, 0, M_FWD | onalt, col_tiles(c->N, c->k, dbl), 0});
+    }
   }
-  return QFDTD_OK;
+  QF_TRY(run_family(F_COL, c1, dbl, 0, st));
+  QF_TRY(run_family(F_COL, c2, dbl, 0, st));
+  QF_TRY(run_by_size(F_PENCIL, pen, dbl, st));
+  QF_TRY(run_by_size(F_SLAB, sl, dbl, st));
+  QF_TRY(run_family(F_PLANE, pl, dbl, 0, st));
+  QF_TRY(run_family(F_ROW, rw, dbl, 0, st));
+  QF_TRY(run_family(F_COL, c2f, dbl, 0, st));
+  QF_TRY(run_family(F_STENCIL2, sten2[0], dbl, 0, st));
+  QF_TRY(run_family(F_STENCIL2, sten2[1], dbl, 0, st));
+  return run_family(F_STENCIL, sten, dbl, 0, st);
 }
 
 // Launches of a member that no other member of the batch can share: its size and split-x2 shape, its
@@ -799,9 +796,11 @@ int lane_key(const qfdtd_ctx *c) {
 // leave most of the chip idle, run beside the large ones'.  Measured on 16 uneven one-state solves
 // from 32^3 to 240^3 and on 12 three-state solves from 48^3 to 160^3, ms per 50 steps: one stream
 // 43.6 and 27.4, two 35.3 and 23.2, three 32.5 and 21.7, four (the hardware queues of a process) 31.8
-// and 21.0.  run(members, steps, stream) does the work; n[j]: member j's steps (0: it has none).
+// and 21.0.  run(members, steps, round, stream) does the work in rounds r0 .. r1 - 1; n[j]: member j's steps
+// (0: it has none).  A stream's rounds are launched together: taken round by round over the streams
+// (as the state groups of one solve are) the batch of 12 took 22.2 instead of 19.7 ms.
 template <class Run>
-qfdtd_status on_lanes(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n, qfdtd_ctx *lead, Run run) {
+qfdtd_status on_lanes(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n, int r0, int r1, qfdtd_ctx *lead, Run run) {
   struct Share { int key; double cost; };
   std::vector<Share> shares;
   for (size_t j = 0; j < ms.size(); ++j) {
@@ -813,7 +812,10 @@ qfdtd_status on_lanes(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n, qfdtd_c
     if (it == shares.end()) { shares.push_back({key, 8e-6}); it = shares.end() - 1; }
     it->cost += 4.0 * (double)c->k * (double)c->n3() * (double)c->csz() / 5e12 * (c->fft() && !c->plane && !c->split ? 2 : 1);
   }
-  if (shares.size() < 2 || !lead || !lead->lane_fork) return run(ms, n, ms[0]->st);
+  if (shares.size() < 2 || !lead || !lead->lane_fork) {
+    for (int r = r0; r < r1; ++r) QF_TRY(run(ms, n, r, ms[0]->st));
+    return QFDTD_OK;
+  }
   std::sort(shares.begin(), shares.end(), [](const Share &x, const Share &y) {
     return x.cost != y.cost ? x.cost > y.cost : x.key < y.key;
   });
@@ -828,13 +830,14 @@ qfdtd_status on_lanes(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n, qfdtd_c
   }
   hipStream_t st = ms[0]->st;
   QF_HIP(ms[0], hipEventRecord(lead->lane_fork, st));
-  for (int l = 1; l < LANES; ++l) {
+  for (int l = 1; l < LANES; ++l)
+    if (!lm[l].empty()) QF_HIP(ms[0], hipStreamWaitEvent(lead->lane_st[l - 1], lead->lane_fork, 0));
+  for (int q = 1; q <= LANES; ++q) {
+    const int l = q % LANES;      // the common stream, with the costliest members, last
     if (lm[l].empty()) continue;
-    QF_HIP(ms[0], hipStreamWaitEvent(lead->lane_st[l - 1], lead->lane_fork, 0));
-    QF_TRY(run(lm[l], ln[l], lead->lane_st[l - 1]));
-    QF_HIP(ms[0], hipEventRecord(lead->lane_join[l - 1], lead->lane_st[l - 1]));
+    for (int r = r0; r < r1; ++r) QF_TRY(run(lm[l], ln[l], r, l ? lead->lane_st[l - 1] : st));
+    if (l) QF_HIP(ms[0], hipEventRecord(lead->lane_join[l - 1], lead->lane_st[l - 1]));
   }
-  QF_TRY(run(lm[0], ln[0], st));
   for (int l = 1; l < LANES; ++l)
     if (!lm[l].empty()) QF_HIP(ms[0], hipStreamWaitEvent(st, lead->lane_join[l - 1], 0));
   return QFDTD_OK;
@@ -847,9 +850,8 @@ qfdtd_status run_chunk(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n, qfdtd_
   if (ms.empty()) return QFDTD_OK;
   bool timed = false;
   for (auto *c : ms) timed = timed || c->timer.every > 0;
-  if (timed) return run_chunk_on(ms, n, ms[0]->st);
-  if (ms.size() == 1 && ms[0]->ngroups >= 2 && n[0] > 0) return run_chunk_grouped(ms[0], n[0]);
-  return on_lanes(ms, n, lead, run_chunk_on);
+  if (!timed && ms.size() == 1 && ms[0]->ngroups >= 2 && n[0] > 0) return run_chunk_grouped(ms[0], n[0]);
+  return on_lanes(ms, n, -1, *std::max_element(n.begin(), n.end()), timed ? nullptr : lead, chunk_step);
 }
 
 // E_i = <psi_i|H|psi_i>/<psi_i|psi_i> in FP64, to device and pinned host memory; with_trace also records a
@@ -857,7 +859,7 @@ qfdtd_status run_chunk(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n, qfdtd_
 qfdtd_status energies(std::vector<qfdtd_ctx *> &ms, bool with_trace, qfdtd_ctx *lead) {
   if (ms.empty()) return QFDTD_OK;
   std::vector<int> one(ms.size(), 1);
-  QF_TRY(on_lanes(ms, one, lead, [](std::vector<qfdtd_ctx *> &m, std::vector<int> &, hipStream_t st) {
+  QF_TRY(on_lanes(ms, one, 0, 1, lead, [](std::vector<qfdtd_ctx *> &m, std::vector<int> &, int, hipStream_t st) {
     return energy_passes(m, st);
   }));
   std::vector<Entry> fin;
