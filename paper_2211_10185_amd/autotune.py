@@ -35,7 +35,7 @@ SPLIT_SWAPPED_SIZES = {0: (96, 108, 120, 128, 144, 150, 160, 162, 180, 192, 200,
 SPLIT_C128_SIZES = (32, 36, 40, 48, 50, 54, 60, 64, 72, 80, 90, 96, 100, 108, 120, 128, 144, 150, 160, 162, 180, 192,
                     200, 216, 240, 250, 256)
 SPLIT_SMALL_SIZES = (32, 36, 40, 48, 50, 54, 60, 64, 72, 80, 90)     # complex64, one tile shape
-SPLIT_C128_SECOND = (40, 48, 72, 80, 96, 108, 120, 150, 162, 192, 216)
+SPLIT_C128_SECOND = (40, 48, 72, 80, 96, 108, 120, 150, 160, 162, 192, 216, 250)
 _cache: Optional[Dict[str, dict]] = None
 
 
@@ -82,10 +82,11 @@ def ab_schedule(N: int, precision: int, k: int) -> Optional[dict]:
 
     Measured (us per step, best plane or row/column schedule against split-x2; one state / three):
     complex64 32: 16.0 -> 12.9 / 16.4 -> 13.3, 64: 20.9 -> 16.2 / 25.7 -> 21.9, 90: 41.9 -> 29.9 /
-    58.6 -> 46.0, 128: 45.1 -> 34.4 / 91.4 -> 69.4 (above 128 the row/column passes stay: the split-x2
+    58.4 -> 43.6, 128: 45.1 -> 34.4 / 90.9 -> 66.3 (above 128 the row/column passes stay: the split-x2
     factors would change the FP32 results); complex128 64: 24.7 -> 17.3 / 34.8 -> 29.8, 128: 71.0 ->
-    45.7 / 187 -> 108, 160: 137 -> 104 / 413 -> 318, 240: 549 -> 477 / 1741 -> 1342, 256: 606 -> 584 /
-    1869 -> 1615, but 216: 366 -> 368 and 250: 616 -> 636 with one state.  Groups of states on their own
+    45.7 / 187 -> 108, 160: 137 -> 104 / 413 -> 318, 240: 549 -> 477 / 1741 -> 1342, 256: 606 -> 513 /
+    1848 -> 1418, but 216: 366 -> 368 and 250: 616 -> 636 with one state.  At 160 and 250 the other shape
+    is the better one for this update (three states: 318 against 365 and 2250).  Groups of states on their own
     streams win where a pass of one state does not fill the chip but its launches are long enough."""
     if precision == 0:
         if N not in SPLIT_SMALL_SIZES + (96, 100, 108, 120, 128):
@@ -96,7 +97,7 @@ def ab_schedule(N: int, precision: int, k: int) -> Optional[dict]:
         if N not in SPLIT_C128_SIZES or (k == 1 and N in (216, 250)):
             return None
         groups = min(k, 3) if N in (90, 96, 100, 108, 120, 128, 160) else 1
-        variant = 1 if N in (162, 192) else 0
+        variant = 1 if N in (160, 162, 192, 250) else 0
     return {"rowcol": False, "single_stream": groups == 1, "groups": groups, "split": True, "split_variant": variant}
 
 

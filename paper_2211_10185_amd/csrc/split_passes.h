@@ -709,11 +709,13 @@ __device__ __forceinline__ void pencil_meas_body(const PassDesc &d, int t, unsig
 //     slab pass 86 -> 62 us, pencil pass 89 -> 77 us;
 //   - the passes are bound by latency, so registers decide: at most 128 leave four waves per SIMD;
 //   - pencil pieces of 32 bytes and more (XI TT >= 4 in complex64, >= 2 in complex128): the L1 is
-//     bound by requests below that;
+//     bound by requests below that; 64 bytes where the LDS holds the tile (256^3, complex128, one / three
+//     states: 420 / 1169 -> 330 / 925 us per step; one pencil tile of 157 KB per CU);
 //   - at small N more, smaller tiles: one per (plane, row digit) with 64 to 256 threads.
 // Variants:
 //   0: the fastest for three states;  1: complex64 from 96 up: the fastest other shape of the same
-//   factors (complex128: the fastest for one state, where that is another);  2: 8 consecutive rows per
+//   factors (complex128: the fastest for one state or for the A/B
+//   update, where that is another);  2: 8 consecutive rows per
 //   pencil tile and 8 columns;  3: the factors swapped;  4 (not selectable by flags): the A/B update
 //   of complex64 up to N = 128, with the factors of the plane pass.
 struct SplitDef {
@@ -821,18 +823,20 @@ constexpr SplitDef SPLIT_DEFS[] = {
     {144, 1, 0, 12, 1, 2, 192, rp(16, 9), 320, rp(12, 12)},
     {150, 1, 0, 15, 1, 2, 256, rp(15, 10), 320, rp(15, 10)},
     {150, 1, 1, 15, 1, 2, 256, rp(10, 15), 320, rp(15, 10)},
-    {160, 1, 0, 16, 1, 4, 256, rp(16, 10), 640, rp(10, 16)},
+    {160, 1, 0, 16, 1, 2, 256, rp(16, 10), 320, rp(16, 10)},
+    {160, 1, 1, 16, 1, 4, 256, rp(16, 10), 640, rp(10, 16)},
     {162, 1, 0, 9, 2, 1, 384, rp(18, 9), 192, rp(9, 18)},
     {162, 1, 1, 9, 1, 2, 192, rp(2, 9, 9), 384, rp(9, 18)},
     {180, 1, 0, 10, 2, 1, 384, rp(18, 10), 192, rp(10, 18)},
-    {192, 1, 0, 12, 2, 1, 384, rp(12, 16), 192, rp(16, 12)},
+    {192, 1, 0, 12, 2, 1, 384, rp(12, 16), 192, rp(12, 16)},
     {192, 1, 1, 12, 1, 2, 192, rp(16, 12), 384, rp(12, 16)},
-    {200, 1, 0, 10, 1, 2, 256, rp(5, 8, 5), 448, rp(8, 5, 5)},
+    {200, 1, 0, 10, 1, 2, 256, rp(5, 8, 5), 448, rp(10, 20)},
     {216, 1, 0, 12, 2, 2, 448, rp(18, 12), 448, rp(12, 18)},
     {216, 1, 1, 12, 1, 2, 256, rp(12, 18), 448, rp(12, 18)},
     {240, 1, 0, 15, 1, 2, 256, rp(15, 16), 512, rp(15, 16)},
-    {250, 1, 0, 10, 2, 1, 512, rp(5, 10, 5), 256, rp(5, 10, 5)},
-    {256, 1, 0, 16, 2, 1, 512, rp(16, 16), 256, rp(16, 16)},
+    {250, 1, 0, 25, 1, 2, 256, rp(25, 10), 512, rp(25, 10)},
+    {250, 1, 1, 10, 2, 1, 512, rp(5, 10, 5), 256, rp(5, 10, 5)},
+    {256, 1, 0, 16, 2, 2, 512, rp(16, 16), 512, rp(16, 16)},
 };
 __host__ __device__ constexpr SplitDef split_def(int N, int dbl, int v) {
   for (const SplitDef &s : SPLIT_DEFS)

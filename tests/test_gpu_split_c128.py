@@ -16,7 +16,9 @@ CASES = [(32, S.K_REL, S.V_CORNELL, 3, False, 0), (36, S.K_NR_P2, S.V_HARMONIC, 
          (100, S.K_NR_SIN2, S.V_CORNELL, 3, False, 0), (128, S.K_NR_P2, S.V_HARMONIC, 2, True, 0),
          (144, S.K_REL, S.V_CORNELL, 1, False, 0), (150, S.K_NR_SIN2, S.V_HARMONIC, 2, False, 1),
          (160, S.K_REL, S.V_CORNELL, 2, False, 0), (162, S.K_NR_P2, S.V_CORNELL, 1, True, 1),
-         (200, S.K_NR_SIN2, S.V_HARMONIC, 1, False, 0), (250, S.K_REL, S.V_CORNELL, 1, False, 0)]
+         (200, S.K_NR_SIN2, S.V_HARMONIC, 1, False, 0), (250, S.K_REL, S.V_CORNELL, 1, False, 0),
+         (160, S.K_NR_SIN2, S.V_HARMONIC, 1, True, 1), (192, S.K_REL, S.V_HARMONIC, 2, False, 0),
+         (250, S.K_NR_P2, S.V_HARMONIC, 1, True, 1), (256, S.K_NR_P2, S.V_HARMONIC, 1, False, 0)]
 
 
 @pytest.mark.parametrize("N,kind,vkind,k,ab,variant", CASES)
