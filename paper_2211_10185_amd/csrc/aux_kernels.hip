@@ -331,18 +331,31 @@ template <typename T> struct S2 {
   static_assert(RING <= NT, "one frame site per thread");
 };
 
-// Planes per tile.  A tile of CZ planes computes psi' on CZ + 2, so long marches do less work, and short ones
-// fill the chip and are a shorter chain: 32 planes while that leaves four blocks per compute unit, 16
-// while it leaves one and a half, else less.  us per step, complex64: 64^3 x 3 states 8 planes 12.5 (the
-// earlier kernel), 2 planes 5.3; 128^3 x 3 states 8 / 16 / 32 planes 18.3 / 15.0 / 16.1; 256^3 x 3
-// states 16 / 32 planes 138 / 135.
-__host__ __device__ inline int stencil2_cz(int N, int k) {
-  const long long cols = (long long)k * ((N + S2<float>::TX - 1) / S2<float>::TX) * ((N + S2<float>::TY - 1) / S2<float>::TY);
-  int cz = 32;
-  while (cz > 2 && cols * ((N + cz - 1) / cz) < (cz == 32 ? 1024 : 384)) cz /= 2;
-  return cz;
+// Planes per tile.  A tile of CZ planes computes psi' on CZ + 2, so long marches do less work; short ones fill
+// the chip.  What decides is the last round of blocks: 2 to 5 of them fit a compute unit (registers), and tiles
+// that need a round more, or leave compute units with a block less than the others, cost as much as if they
+// were all full.  A round of b blocks per compute unit takes about (CZ + 4) (b + 3) units (start-up of four
+// planes, and a plane's chain of latencies worth three blocks' work); the CZ of the least sum over the rounds
+// is within 1% of the best of all CZ on average (10% at most) over 48 <= N <= 256 and one to three states.
+// us per step against the earlier rule (32, 16, 8, 4 or 2 planes by the number of tiles), complex64: 64^3 x 2
+// states 5.5 -> 5.2, 80^3 x 3 8.9 -> 7.6, 96^3 x 3 12.4 -> 9.0, 112^3 x 2 12.7 -> 9.7, 128^3 x 1 8.9 -> 8.0,
+// 150^3 x 1 13.4 -> 10.6, 180^3 x 3 62.2 -> 51.7, 128^3 and 256^3 x 3 as before (15.3 and 136); complex128: 96^3 x
+// 2 11.7 -> 9.8, 150^3 x 2 29.8 -> 26.7, 192^3 x 3 108 -> 100.
+// load: sites of the launch per site of this solve (> 1 where solves of a batch share it).
+int stencil2_cz_host(bool dbl, bool vc, int N, int k, double load) {
+  constexpr int CUS = 256;
+  const int B = dbl ? (vc ? 2 : 3) : (vc ? 4 : 5);
+  const double cols = load * k * ((N + S2<float>::TX - 1) / S2<float>::TX) * ((N + S2<float>::TY - 1) / S2<float>::TY);
+  int best = 2;
+  double least = 0;
+  for (int cz = 2; cz <= 32; ++cz) {
+    const long long tiles = (long long)(cols * ((N + cz - 1) / cz));
+    const long long full = tiles / (CUS * B), rem = tiles % (CUS * B);
+    const double cost = (cz + 4) * (double)(full * (B + 3) + (rem ? (rem + CUS - 1) / CUS + 3 : 0));
+    if (cz == 2 || cost < least) { least = cost; best = cz; }
+  }
+  return best;
 }
-int stencil2_cz_host(int N, int k) { return stencil2_cz(N, k); }
 int stencil2_tiles_host(int N, int k, int cz) {
   return k * ((N + S2<float>::TX - 1) / S2<float>::TX) * ((N + S2<float>::TY - 1) / S2<float>::TY) * ((N + cz - 1) / cz);
 }

@@ -49,7 +49,7 @@ void launch_to64_slot(bool dbl, double2 *dst, const void *src, size_t n, hipStre
 int ew_tiles_host(long long n);
 int stencil_cz_host(int N, int k);
 int stencil_tiles_host(int N, int k, int cz);
-int stencil2_cz_host(int N, int k);
+int stencil2_cz_host(bool dbl, bool vc, int N, int k, double load);
 int stencil2_tiles_host(int N, int k, int cz);
 const void *stencil2_kernel(bool dbl, bool vc);
 int stencil2_threads();
@@ -734,6 +734,9 @@ qfdtd_status chunk_step(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n, int s
   if (s < 0) return chunk_start(ms, n, st);
   const bool dbl = ms[0]->dbl;
   std::vector<Entry> pl, rw, c2, c2f, c1, sten, sten2[2], sl, pen;     // sten2: real and complex V
+  double sites = 0;            // of the stencil passes together
+  for (size_t j = 0; j < ms.size(); ++j)
+    if (s < n[j] && !ms[j]->fft()) sites += (double)ms[j]->N * ms[j]->N * ms[j]->N * ms[j]->k;
   for (size_t j = 0; j < ms.size(); ++j) {
     qfdtd_ctx *c = ms[j];
     if (s >= n[j]) continue;
@@ -743,7 +746,7 @@ qfdtd_status chunk_step(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n, int s
       const uint32_t sw = c->cur ? (uint32_t)M_SWAP : 0u;
       if (c->stencil2 && (s & 1)) continue;                // advanced by the pass at s - 1
       if (c->stencil2 && s + 1 < n[j]) {
-        const int cz = stencil2_cz_host(c->N, c->k);
+        const int cz = stencil2_cz_host(dbl, c->vcomplex, c->N, c->k, sites / ((double)c->N * c->N * c->N * c->k));
         sten2[c->vcomplex].push_back({c, 0, sw, stencil2_tiles_host(c->N, c->k, cz), cz});
       }
       else {

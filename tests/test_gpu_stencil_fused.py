@@ -7,11 +7,12 @@ import synthetic as S
 
 pytestmark = pytest.mark.gpu
 
-# the smallest lattice, one tile exactly or one site more or less per axis, marches of 2, 4, 8, 16 and 32
-# planes, a last march of one plane, one to eight states, odd chunks
+# the smallest lattice, one tile exactly or one site more or less per axis, marches of 2 to 32 planes
+# with whole and partial last ones, a last march of one plane, one to eight states, odd chunks
 CASES = [(8, 1, 0, False, 2), (10, 8, 1, True, 3), (12, 1, 1, False, 5), (14, 2, 0, True, 4), (26, 1, 0, False, 7),
          (32, 3, 1, False, 4), (34, 2, 0, True, 5), (66, 1, 1, True, 3), (98, 3, 0, False, 4), (130, 1, 0, True, 2),
-         (130, 3, 1, False, 2), (194, 2, 0, False, 2), (226, 4, 0, False, 3)]
+         (130, 3, 1, False, 2), (194, 2, 0, False, 2), (226, 4, 0, False, 3), (80, 3, 0, False, 3), (96, 3, 0, True, 2),
+         (112, 2, 1, False, 3), (88, 5, 1, True, 2)]
 
 
 @pytest.mark.parametrize("N,k,precision,vc,steps", CASES)
