@@ -55,8 +55,8 @@ def parse():
     ap.add_argument("--split", choices=["auto", "on", "off"], default="auto",
                     help="FFT solves: the split-x2 two-pass schedule where it exists (auto: the tuned choice)")
     ap.add_argument("--split-variant", type=int, choices=[0, 1, 2], default=None,
-                    help="split-x2 variant: 0 = 4 x3 columns per pencil tile, 1 = 2, 2 = x2 = 32 x 8 with 8 "
-                         "(default: the tuned choice)")
+                    help="split-x2 variant: 0 and 1 = the size's default factors and two tile shapes, 2 = x2 = 32 x 8 "
+                         "with 8 x3 columns per pencil tile (default: the tuned choice)")
     ap.add_argument("--requests", type=int, default=1000, help="serve: number of requests in the trace")
     ap.add_argument("--rate", type=float, default=200.0, help="serve: arrival rate (1/s)")
     ap.add_argument("--batch-steps", type=int, default=5000, help="batch64: imaginary-time steps")
@@ -280,7 +280,8 @@ def bench_rel256(args):
                                          "3 states in sectors P+,P+,P-_p3, dt=a/8, %d steps, complex64 states, "
                                          "FP64 reductions" % p.steps)
     out["config"]["reductions"] = "f64"
-    split_names = {0: "x2 = 16 x 16, 4-column pencil tiles", 1: "x2 = 16 x 16, 2-column pencil tiles",
+    split_names = {0: "x2 = 16 x 16, 2-column pencil tiles, plane pairs",
+                   1: "x2 = 16 x 16, 4-column pencil tiles, plane pairs",
                    2: "x2 = 32 x 8, 8-column pencil tiles", 3: "x2 factors swapped"}
     out["config"]["schedule"] = ("split-x2 (slab + pencil passes, %s)" % split_names[s.schedule["split_variant"]]
                                  if s.schedule["split"] else "row + three column passes")

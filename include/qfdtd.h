@@ -145,7 +145,8 @@ typedef struct {
                                      rows of a few x3 columns over all x1 and does the other part
                                      of x2 and the x1 transforms around the kinetic factor.  Two
                                      passes over the state per step instead of four (schedule
-                                     autotuning; ignored with QFDTD_F_AB_SCHEME in complex64). */
+                                     autotuning; ignored with QFDTD_F_AB_SCHEME in complex64
+                                     above N = 128). */
 /* Flag bits 7-8: the split-x2 variant (schedule autotuning), read as QFDTD_SPLIT_VARIANT(flags):
  *   0: the size's default factors x2 = N1 x N2 with its fastest tiles;
  *   1 (QFDTD_F_SPLIT_NARROW): the same factors with other tiles (mostly pencil tiles of fewer

@@ -5,10 +5,9 @@ step as
   * the plane schedule (x2-x3 plane pass + x1 column pass: 2 passes per step),
     available where an N^2 plane fits in LDS, or
   * the row/column schedule (x3 row pass + three column passes: 4 passes), or
-  * the split-x2 schedule (slab pass + pencil pass: 2 passes), for the sizes
-    that have split-x2 kernels, with pencil tiles of 4 or 2 x3 columns, and at
-    N = 128 and 256 also with 8-row tiles of 8 columns, and with the two factors
-    of x2 swapped (a radix-plan choice),
+  * the split-x2 schedule (slab pass + pencil pass: 2 passes), in one or two tile
+    shapes, and in complex64 from N = 96 up also with the two factors of x2 swapped
+    (a radix-plan choice) and at 128 and 256 with 8-row tiles of 8 columns,
 and, with k >= 2 states, either carry all states through one stream or split
 them into two (or, with k >= 3, three) groups pipelined on their own streams.  ``tune`` times every candidate
 on the device with the solver's own kernels and records the fastest in a JSON

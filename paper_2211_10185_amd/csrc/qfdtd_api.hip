@@ -8,7 +8,12 @@
 //   FFT kinds, larger N:
 //     row[h, F3] ; col2[F2] ; { col1[...] ; col2[F2^-1] ; row[F3^-1, h^2, F3] ; col2[F2] } x (n-1)
 //                        ; col1[...] ; col2[F2^-1] ; row[F3^-1, h]       -> 4n + 1 passes
-//   H_K^(0): n stencil passes (ping-pong between psi and alt).
+//   FFT kinds, split x2 = N1 x N2 (A the stride-N2 part of F2, B the other; the tuned choice nearly everywhere):
+//     slab[h, F3, A] ; { pencil[B, F1, e^{-dt T}, F1^-1, B^-1] ; slab[A^-1, F3^-1, h^2, F3, A] } x (n-1)
+//                        ; pencil[...] ; slab[A^-1, F3^-1, h]            -> 2n + 1 passes
+//     complex64 up to N = 90 (A/B update: up to 128): plane[h, F23] first and plane[F23^-1, h] last, the
+//     first pencil without B, the last without B^-1, so that the operations are the plane schedule's
+//   H_K^(0): passes of two fused steps, and a single step where n is odd (ping-pong between psi and alt).
 // After every chunk: parity projection (if any sector is set), FP64 Gram
 // matrix, Cholesky per sector, psi <- psi R^{-1}.
 #include <algorithm>
