@@ -627,6 +627,24 @@ template <int PK, int N, bool REV, int S> struct StageOf {
   static constexpr int OFFA = tw_off<PK, N, REV, P.first>();
   static constexpr int OFFB = tw_off<PK, N, REV, P.first + (P.rb > 1 ? 1 : 0)>();
 };
+// the stage's twiddles and butterfly on the inputs v of index j
+template <typename T, int PK, int N, bool REV, int S, bool INV>
+__device__ __forceinline__ void stage_calc(C<T> *v, const C<T> *tw, int j) {
+  using SO = StageOf<PK, N, REV, S>;
+  if constexpr (SO::P.rb == 1) {
+    if constexpr (SO::NS > 1) {
+#pragma unroll
+      for (int r = 1; r < SO::R; ++r) {
+        C<T> w = tw[SO::OFFA + (r - 1) * SO::NS + j % SO::NS];
+        if (INV) w.y = -w.y;
+        v[r] = cmul(v[r], w);
+      }
+    }
+    Dft<SO::R, INV, C<T>>::run(v);
+  } else {
+    fused_dft<T, SO::P.ra, SO::P.rb, SO::NS, INV, SO::OFFA, SO::OFFB>(v, tw, j % SO::NS);
+  }
+}
 // inputs of the stage from src(b, n) and its butterflies
 template <typename T, int PK, int N, bool REV, int S, bool INV, class G, int NT, int CQ, int R, class Src>
 __device__ __forceinline__ void stage_read(C<T> (&v)[CQ][R], const C<T> *tw, Src src) {
@@ -643,7 +661,7 @@ __device__ __forceinline__ void stage_read(C<T> (&v)[CQ][R], const C<T> *tw, Src
         Q::jb(q, j, b);
 #pragma unroll
         for (int r = 0; r < SO::R; ++r) v[q][r] = src(b, j + r * Q::NR);
-        fused_dft<T, SO::P.ra, SO::P.rb, SO::NS, INV, SO::OFFA, SO::OFFB>(v[q], tw, j % SO::NS);
+        stage_calc<T, PK, N, REV, S, INV>(v[q], tw, j);
       }
     }
   }
@@ -680,6 +698,65 @@ __device__ __forceinline__ void lds_stages(C<T> *buf, const C<T> *tw) {
 template <typename T, int PK, int N, bool INV, class G, int NT>
 __device__ __forceinline__ void fft_lines_t(C<T> *buf, const C<T> *tw) {
   lds_stages<T, PK, N, false, INV, G, NT, 0, stages_of<PK, N, false>().n>(buf, tw);
+}
+
+// The same with LDS for one part of each value only: a thread's values stay in registers between the
+// stages, and an exchange moves the real parts and then the imaginary parts through hb.
+template <int P, typename T> __device__ __forceinline__ T &part_of(C<T> &x) {
+  if constexpr (P == 0) return x.x;
+  else return x.y;
+}
+// put(part) writes that part of the values to LDS, get(part) reads it back in the next layout
+template <class Put, class Get> __device__ __forceinline__ void exchange_parts(Put put, Get get) {
+  __syncthreads();
+  put(std::integral_constant<int, 0>());
+  __syncthreads();
+  get(std::integral_constant<int, 0>());
+  __syncthreads();
+  put(std::integral_constant<int, 1>());
+  __syncthreads();
+  get(std::integral_constant<int, 1>());
+}
+// part P of the inputs of stage S, and of its outputs
+template <int P, typename T, int PK, int N, bool REV, int S, class G, int NT, int CQ, int R>
+__device__ __forceinline__ void part_read(C<T> (&v)[CQ][R], const T *hb) {
+  static_assert(R == StageOf<PK, N, REV, S>::R, "the stage's inputs");
+  using Q = SG<G, N, R, NT>;
+#pragma unroll
+  for (int q = 0; q < Q::CAPQ; ++q) {
+    if (Q::active(q)) {
+      int j, b;
+      Q::jb(q, j, b);
+#pragma unroll
+      for (int r = 0; r < R; ++r) part_of<P, T>(v[q][r]) = hb[G::at(b, j + r * Q::NR)];
+    }
+  }
+}
+template <int P, typename T, int PK, int N, bool REV, int S, class G, int NT, int CQ, int R>
+__device__ __forceinline__ void part_write(C<T> (&v)[CQ][R], T *hb) {
+  stage_write<T, PK, N, REV, S, G, NT>(v, [&](int b, int n, C<T> x) { hb[G::at(b, n)] = part_of<P, T>(x); });
+}
+// stages [S, S1) on the inputs v of stage S; fin(x) takes the outputs x of stage S1 - 1
+template <typename T, int PK, int N, bool REV, bool INV, class G, int NT, int S, int S1, int CQ, int R, class Fin>
+__device__ __forceinline__ void part_stages(T *hb, const C<T> *tw, C<T> (&v)[CQ][R], Fin fin) {
+  using Q = SG<G, N, R, NT>;
+#pragma unroll
+  for (int q = 0; q < Q::CAPQ; ++q) {
+    if (Q::active(q)) {
+      int j, b;
+      Q::jb(q, j, b);
+      stage_calc<T, PK, N, REV, S, INV>(v[q], tw, j);
+    }
+  }
+  if constexpr (S + 1 < S1) {
+    constexpr int R2 = StageOf<PK, N, REV, S + 1>::R;
+    C<T> w[SG<G, N, R2, NT>::CAPQ][R2];
+    exchange_parts([&](auto p) { part_write<decltype(p)::value, T, PK, N, REV, S, G, NT>(v, hb); },
+                   [&](auto p) { part_read<decltype(p)::value, T, PK, N, REV, S + 1, G, NT>(w, hb); });
+    part_stages<T, PK, N, REV, INV, G, NT, S + 1, S1>(hb, tw, w, fin);
+  } else {
+    fin(v);
+  }
 }
 
 }  // namespace qf

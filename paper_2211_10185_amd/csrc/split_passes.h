@@ -50,8 +50,8 @@ template <int NL, int P, int N1, int XI> struct SlabGeo {
 template <int N2, int TT> __host__ __device__ constexpr int pencil_pitch() {
   return N2 * TT + 4 + ((N2 * TT + 4) % 32 == 0 ? 4 : 0);
 }
-template <typename T, int N, int N2, int TT, int PK> __host__ __device__ constexpr size_t pencil_lds_t() {
-  return (size_t)(N * pencil_pitch<N2, TT>() + tw_total<PK, N>()) * sizeof(C<T>) + N * sizeof(T);
+template <typename T, int N, int N2, int TT, int PK, bool HX> __host__ __device__ constexpr size_t pencil_lds_t() {
+  return (size_t)N * pencil_pitch<N2, TT>() * sizeof(T) * (HX ? 1 : 2) + tw_total<PK, N>() * sizeof(C<T>) + N * sizeof(T);
 }
 
 // Loads and stores of one state with a block-uniform base and a 32-bit per-lane byte offset.
@@ -246,6 +246,33 @@ __device__ __forceinline__ void slab_body(const LaunchList &L, int e, int t, uns
       }
     }
     fill_twiddles<T, PK, N, NT>(tw, gtw);
+    // psi' or the factor, and the first forward stage, on the outputs of the last inverse one
+    auto middle = [&](auto &v, int s) {
+#pragma unroll
+      for (int q = 0; q < SS::CAPQ; ++q) {
+        if (SS::active(q)) {
+          if constexpr (AB) {
+            C<T> *gp = (C<T> *)d.psi + (size_t)s * N3 + voff;
+            int j, bl;
+            SS::jb(q, j, bl);
+            const int pl = bl / N1, a = bl - (bl / N1) * N1;
+#pragma unroll
+            for (int r = 0; r < RM; ++r) {
+              const size_t o = site(pl, a, j + r * SS::NR);
+              v[q][r] = ab_combine<T>(gp[o], v[q][r], d, voff + o);
+              gp[o] = v[q][r];
+            }
+          } else {
+#pragma unroll
+            for (int r = 0; r < RM; ++r) {
+              if constexpr (KIND == SLAB_COMPLEX) v[q][r] = cmul(v[q][r], hq[q][r]);
+              else v[q][r] = cscale(v[q][r], hq[q][r]);
+            }
+          }
+          stage_first<T, PK, N, true, false>(v[q], tw);
+        }
+      }
+    };
     for (int s = s0; s < s1; ++s) {
       C<T> *g = (C<T> *)(AB ? d.alt : d.psi) + (size_t)s * N3 + voff;
       a_inverse_to_lds(g);
@@ -254,30 +281,7 @@ __device__ __forceinline__ void slab_body(const LaunchList &L, int e, int t, uns
         C<T> v[SS::CAPQ][RM];
         stage_read<T, PK, N, false, M, true, Rows, NT>(v, tw, [&](int bl, int n) { return buf[Rows::at(bl, n)]; });
         __syncthreads();
-#pragma unroll
-        for (int q = 0; q < SS::CAPQ; ++q) {
-          if (SS::active(q)) {
-            if constexpr (AB) {
-              C<T> *gp = (C<T> *)d.psi + (size_t)s * N3 + voff;
-              int j, bl;
-              SS::jb(q, j, bl);
-              const int pl = bl / N1, a = bl - (bl / N1) * N1;
-#pragma unroll
-              for (int r = 0; r < RM; ++r) {
-                const size_t o = site(pl, a, j + r * SS::NR);
-                v[q][r] = ab_combine<T>(gp[o], v[q][r], d, voff + o);
-                gp[o] = v[q][r];
-              }
-            } else {
-#pragma unroll
-              for (int r = 0; r < RM; ++r) {
-                if constexpr (KIND == SLAB_COMPLEX) v[q][r] = cmul(v[q][r], hq[q][r]);
-                else v[q][r] = cscale(v[q][r], hq[q][r]);
-              }
-            }
-            stage_first<T, PK, N, true, false>(v[q], tw);
-          }
-        }
+        middle(v, s);
         stage_write<T, PK, N, true, 0, Rows, NT>(v, [&](int bl, int n, C<T> x) { buf[Rows::at(bl, n)] = x; });
         __syncthreads();
       }
@@ -394,8 +398,14 @@ __device__ __forceinline__ void slab_body(const LaunchList &L, int e, int t, uns
 // Pencil pass on tile (state s, slow x2 frequency k1, x3 columns c0 .. c0 + TT - 1): B, forward x1,
 // x e^{-dt T(k)}/N^3, inverse x1, B^-1.  The state (alt in the A/B update) is in split order with
 // plane groups of XI.  Next to a plane pass at the chunk's edges x2 is transformed as a whole there
-// and B (M_PRE) or B^-1 (M_POST) is left out.
-template <typename T, int N, int N2, int TT, int NT, int XI, int PK>
+// and B (M_PRE) or B^-1 (M_POST) is left out.  HX: the values stay in registers between the stages, and
+// LDS holds one part of them at a time (the real parts are exchanged, then the imaginary parts): half the
+// LDS and twice the barriers.  It pays where a whole tile leaves one or two blocks per compute unit and
+// the registers allow more (us per step, relativistic, one / three states on one stream: complex64 192^3
+// 88 / 215 -> 77 / 172, 240^3 144 / 452 -> 129 / 403; complex128 216^3 245 / 735 -> 210 / 580), and costs
+// elsewhere (complex64 160^3 49 / 113 -> 51 / 115, 180^3 90 / 199 -> 95 / 210; complex128 256^3 330 / 925 -> 346 /
+// 961, whose 200 registers allow no more blocks).
+template <typename T, int N, int N2, int TT, int NT, int XI, int PK, bool HX>
 __device__ __forceinline__ void pencil_body(const LaunchList &L, int e, int t, unsigned char *smem) {
   constexpr int N1 = N / N2;
   constexpr int NH = N / XI;
@@ -463,6 +473,61 @@ __device__ __forceinline__ void pencil_body(const LaunchList &L, int e, int t, u
       for (int k2 = 0; k2 < N2; ++k2) buf[Geo::at(k2 * TT + c, i1)] = v[k2];
     }
   };
+  if constexpr (HX) {
+    static_assert(PPT == 1, "one position per thread");
+    constexpr int R0 = StageOf<PK, N, false, 0>::R, R1 = StageOf<PK, N, true, 1>::R;
+    T *hb = (T *)buf;
+    C<T> v[N2];
+    b_load(v, 0);
+    fill_twiddles<T, PK, N, NT>(tw, (const C<T> *)d.tw);
+    for (int i = threadIdx.x; i < N; i += NT) ktl[i] = ((const T *)d.ktab)[i];
+    const int pos = (int)threadIdx.x, i1 = pos / TT, c = pos - (pos / TT) * TT;
+    const bool act = (N * TT) % NT == 0 || pos < N * TT;
+    if (act && !(mode & M_PRE)) Dft<N2, false, C<T>>::run(v);
+    C<T> w[SG<Geo, N, R0, NT>::CAPQ][R0];
+    exchange_parts(
+        [&](auto p) {
+          if (act) {
+#pragma unroll
+            for (int k2 = 0; k2 < N2; ++k2) hb[Geo::at(k2 * TT + c, i1)] = part_of<decltype(p)::value, T>(v[k2]);
+          }
+        },
+        [&](auto p) { part_read<decltype(p)::value, T, PK, N, false, 0, Geo, NT>(w, hb); });
+    part_stages<T, PK, N, false, false, Geo, NT, 0, NST>(hb, tw, w, [&](auto &x) {
+      constexpr int R = StageOf<PK, N, false, M>::R;
+      using SS = SG<Geo, N, R, NT>;
+#pragma unroll
+      for (int q = 0; q < SS::CAPQ; ++q) {
+        if (SS::active(q)) {
+          int j, l;
+          SS::jb(q, j, l);
+          const int k2 = l / TT, cc = l - (l / TT) * TT;
+#pragma unroll
+          for (int r = 0; r < R; ++r) x[q][r] = cscale(x[q][r], kfac(j + r * SS::NR, k1 + N1 * k2, c0 + cc));
+          stage_first<T, PK, N, true, true>(x[q], tw);
+        }
+      }
+      C<T> y[SG<Geo, N, R1, NT>::CAPQ][R1];
+      exchange_parts([&](auto p) { part_write<decltype(p)::value, T, PK, N, true, 0, Geo, NT>(x, hb); },
+                     [&](auto p) { part_read<decltype(p)::value, T, PK, N, true, 1, Geo, NT>(y, hb); });
+      part_stages<T, PK, N, true, true, Geo, NT, 1, NST>(hb, tw, y, [&](auto &z) {
+        exchange_parts([&](auto p) { part_write<decltype(p)::value, T, PK, N, true, M, Geo, NT>(z, hb); },
+                       [&](auto p) {
+                         if (act) {
+#pragma unroll
+                           for (int k2 = 0; k2 < N2; ++k2)
+                             part_of<decltype(p)::value, T>(v[k2]) = hb[Geo::at(k2 * TT + c, i1)];
+                         }
+                       });
+      });
+    });
+    if (act) {
+      if (!(mode & M_POST)) Dft<N2, true, C<T>>::run(v);
+#pragma unroll
+      for (int bb = 0; bb < N2; ++bb) sb.store(v[bb], at(i1, c), (uint32_t)(bb * N * sizeof(C<T>)));
+    }
+    return;
+  }
   {
     // the first position's loads are in flight while the tables are filled
     C<T> v[N2];
@@ -720,6 +785,7 @@ __device__ __forceinline__ void pencil_meas_body(const PassDesc &d, int t, unsig
 //   of complex64 up to N = 128, with the factors of the plane pass.
 struct SplitDef {
   int N, dbl, v, N1, XI, TT, slab_nt, slab_plan, pencil_nt, pencil_plan;
+  bool pencil_hx = false;
 };
 constexpr SplitDef SPLIT_DEFS[] = {
     {32, 0, 0, 4, 1, 4, 64, rp(8, 4), 128, rp(8, 4)},
@@ -779,17 +845,17 @@ constexpr SplitDef SPLIT_DEFS[] = {
     {180, 0, 0, 18, 1, 4, 192, rp(4, 9, 5), 768, rp(4, 9, 5)},
     {180, 0, 1, 18, 1, 2, 192, rp(4, 9, 5), 384, rp(4, 9, 5)},
     {180, 0, 3, 10, 1, 4, 256, rp(4, 9, 5), 768, rp(4, 9, 5)},
-    {192, 0, 0, 16, 2, 2, 256, rp(8, st(8, 3)), 384, rp(8, 8, 3)},
-    {192, 0, 1, 16, 2, 4, 256, rp(8, st(8, 3)), 768, rp(8, st(8, 3))},
+    {192, 0, 0, 16, 1, 4, 192, rp(8, st(8, 3)), 768, rp(8, 8, 3), true},
+    {192, 0, 1, 16, 2, 2, 256, rp(8, st(8, 3)), 384, rp(8, 8, 3)},
     {192, 0, 3, 12, 1, 4, 192, rp(8, 8, 3), 768, rp(8, st(8, 3))},
     {200, 0, 0, 20, 1, 4, 256, rp(8, st(5, 5)), 832, rp(8, 5, 5)},
     {200, 0, 1, 20, 1, 2, 256, rp(8, st(5, 5)), 448, rp(8, 5, 5)},
     {200, 0, 3, 10, 1, 4, 256, rp(8, 5, 5), 832, rp(8, st(5, 5))},
-    {216, 0, 0, 18, 2, 2, 448, rp(8, 9, 3), 448, rp(8, 9, 3)},
+    {216, 0, 0, 18, 2, 2, 448, rp(8, st(9, 3)), 448, rp(8, 9, 3)},
     {216, 0, 1, 18, 1, 2, 256, rp(8, st(9, 3)), 448, rp(8, 9, 3)},
     {216, 0, 3, 12, 1, 4, 128, rp(8, st(9, 3)), 896, rp(8, st(9, 3))},
-    {240, 0, 0, 16, 1, 4, 256, rp(16, st(3, 5)), 960, rp(16, st(3, 5))},
-    {240, 0, 1, 16, 1, 2, 256, rp(16, st(3, 5)), 512, rp(16, st(3, 5))},
+    {240, 0, 0, 16, 2, 2, 512, rp(16, st(3, 5)), 512, rp(16, st(3, 5)), true},
+    {240, 0, 1, 16, 1, 4, 256, rp(16, st(3, 5)), 960, rp(16, st(3, 5))},
     {240, 0, 3, 15, 1, 2, 256, rp(16, st(3, 5)), 512, rp(16, st(3, 5))},
     {250, 0, 0, 25, 1, 2, 256, rp(10, st(5, 5)), 512, rp(10, 5, 5)},
     {250, 0, 1, 25, 1, 2, 256, rp(10, st(5, 5)), 512, rp(10, st(5, 5))},
@@ -831,7 +897,7 @@ constexpr SplitDef SPLIT_DEFS[] = {
     {192, 1, 0, 12, 2, 1, 384, rp(12, 16), 192, rp(12, 16)},
     {192, 1, 1, 12, 1, 2, 192, rp(16, 12), 384, rp(12, 16)},
     {200, 1, 0, 10, 1, 2, 256, rp(5, 8, 5), 448, rp(10, 20)},
-    {216, 1, 0, 12, 2, 2, 448, rp(18, 12), 448, rp(12, 18)},
+    {216, 1, 0, 12, 2, 1, 448, rp(12, 18), 256, rp(12, 18), true},
     {216, 1, 1, 12, 1, 2, 256, rp(12, 18), 448, rp(12, 18)},
     {240, 1, 0, 15, 1, 2, 256, rp(15, 16), 512, rp(15, 16)},
     {250, 1, 0, 25, 1, 2, 256, rp(25, 10), 512, rp(25, 10)},
@@ -849,7 +915,7 @@ __host__ __device__ constexpr int split_same(int N, int dbl, int v) {
   for (int u = 0; u < v; ++u) {
     const SplitDef b = split_def(N, dbl, u);
     if (a.N1 == b.N1 && a.XI == b.XI && a.TT == b.TT && a.slab_nt == b.slab_nt && a.slab_plan == b.slab_plan &&
-        a.pencil_nt == b.pencil_nt && a.pencil_plan == b.pencil_plan)
+        a.pencil_nt == b.pencil_nt && a.pencil_plan == b.pencil_plan && a.pencil_hx == b.pencil_hx)
       return u;
   }
   return v;
@@ -873,7 +939,7 @@ __global__ void __launch_bounds__((split_def(N, PKT<T>, V).pencil_nt)) k_pencil_
   constexpr SplitDef D = split_def(N, PKT<T>, V);
   const int blk = xcd_block_chunked(blockIdx.x, gridDim.x, PENCIL_XCD_RUN);
   const int e = find_entry(L, blk);
-  pencil_body<T, N, N / D.N1, D.TT, D.pencil_nt, D.XI, D.pencil_plan>(L, e, blk - L.tile_start[e], smem);
+  pencil_body<T, N, N / D.N1, D.TT, D.pencil_nt, D.XI, D.pencil_plan, D.pencil_hx>(L, e, blk - L.tile_start[e], smem);
 }
 
 template <typename T, int N, int V> void register_split_variant(FftKernels *tab) {
@@ -882,7 +948,7 @@ template <typename T, int N, int V> void register_split_variant(FftKernels *tab)
     constexpr int U = split_same(N, PKT<T>, V);
     constexpr bool F = sizeof(T) == 4;
     static_assert(slab_lds_t<T, N, D.N1, D.XI, D.slab_plan>() <= 160 * 1024, "slab tile fits LDS");
-    static_assert(pencil_lds_t<T, N, N / D.N1, D.TT, D.pencil_plan>() <= 160 * 1024, "pencil tile fits LDS");
+    static_assert(pencil_lds_t<T, N, N / D.N1, D.TT, D.pencil_plan, D.pencil_hx>() <= 160 * 1024, "pencil tile fits LDS");
     SplitKernels &k = tab[N].split[PKT<T>][V];
     k.plane_edges = F && (N < 96 || V == 4);
     static_assert(!(F && (N < 96 || V == 4)) || (D.XI == 1 && plan_of<0, N, false>().n == 2 &&
@@ -900,7 +966,7 @@ template <typename T, int N, int V> void register_split_variant(FftKernels *tab)
     k.xi = D.XI;
     k.pencil = (const void *)k_pencil_t<T, N, U>;
     k.pencil_nt = D.pencil_nt;
-    k.pencil_lds = pencil_lds_t<T, N, N / D.N1, D.TT, D.pencil_plan>();
+    k.pencil_lds = pencil_lds_t<T, N, N / D.N1, D.TT, D.pencil_plan, D.pencil_hx>();
     k.pencil_tt = D.TT;
   }
 }
@@ -937,7 +1003,7 @@ template <int N> void register_meas(FftKernels *tab) {
   k.slab[1] = (const void *)k_slab_meas_t<double, N>;
   k.pencil = (const void *)k_pencil_meas_t<N>;
   k.slab_lds = slab_lds_t<double, N, D.N1, D.XI, D.slab_plan>();
-  k.pencil_lds = pencil_lds_t<double, N, N / D.N1, D.TT, D.pencil_plan>();
+  k.pencil_lds = pencil_lds_t<double, N, N / D.N1, D.TT, D.pencil_plan, false>();
   k.slab_nt = D.slab_nt;
   k.pencil_nt = D.pencil_nt;
   k.tps = N / D.XI * (N / D.N1);
