@@ -26,6 +26,7 @@
 #include <atomic>
 
 #include "common.h"
+#include "lanes.h"
 #include "qfdtd.h"
 #include <hip/hip_ext.h>
 
@@ -669,6 +670,19 @@ void split_real(qfdtd_ctx *c, int which, int k, int s, int n, std::vector<Entry>
   slab.push_back({c, which, mode, ps * slab_tiles(c), ps > 1 ? 1 : 0});
 }
 
+// Stream and event calls of fork_join, failures noted on `c`
+struct HipStreams {
+  using Stream = hipStream_t;
+  using Event = hipEvent_t;
+  using Status = qfdtd_status;
+  qfdtd_ctx *c;
+  Status ok() const { return QFDTD_OK; }
+  Status record(Event e, Stream s) { QF_HIP(c, hipEventRecord(e, s)); return QFDTD_OK; }
+  Status wait(Stream s, Event e) { QF_HIP(c, hipStreamWaitEvent(s, e, 0)); return QFDTD_OK; }
+  Status sync(Stream s) { QF_HIP(c, hipStreamSynchronize(s)); return QFDTD_OK; }
+};
+using HipSide = SideStream<HipStreams>;
+
 // One FFT member with its states split into two or three groups, each group's pass
 // chain on its own stream: a group's plane pass (transform arithmetic bound)
 // overlaps the other group's column pass (memory bound); with the split-x2
@@ -677,35 +691,34 @@ void split_real(qfdtd_ctx *c, int which, int k, int s, int n, std::vector<Entry>
 // to the context stream, so ordering with the caller is unchanged.
 qfdtd_status run_chunk_grouped(qfdtd_ctx *c, int n) {
   const bool dbl = c->dbl;
-  QF_HIP(c, hipEventRecord(c->ev_fork, c->st));
-  for (int g = 0; g < c->ngroups; ++g) QF_HIP(c, hipStreamWaitEvent(c->gst[g], c->ev_fork, 0));
-  // step by step over the groups, so that every group starts at once (a launch costs the host about
-  // 4 us, directly or as a node of a graph: a whole chunk of one group first left the others idle for
-  // its 100 launches)
-  for (int s = 0; s <= n; ++s) {
-    for (int g = 0; g < c->ngroups; ++g) {
-      const int which = 2 + g, kg = c->gk[g];
-      hipStream_t st = c->gst[g];
-      std::vector<Entry> pe, c1, sl, pl;
-      if (c->split) {
-        if (s > 0) pe.push_back(split_pencil(c, which, kg, s - 1, n));
-        split_real(c, which, kg, s, n, sl, pl);
-      } else {
-        if (s > 0) c1.push_back({c, which, M_FWD | M_KIN | M_INV | M_AXIS1, col_tiles(c->N, kg, dbl), 0});
-        const uint32_t mode = s == 0 ? M_PRE | M_FWD : s == n ? M_INV | M_POST : M_INV | M_MID | M_FWD;
-        pl.push_back({c, which, mode, plane_tiles(c->N, kg), 0});
+  std::vector<HipSide> sides;
+  for (int g = 0; g < c->ngroups; ++g) sides.push_back({c->gst[g], c->ev_join[g]});
+  HipStreams hs{c};
+  return fork_join(hs, c->st, c->ev_fork, sides, [&]() -> qfdtd_status {
+    // step by step over the groups, so that every group starts at once (a launch costs the host about
+    // 4 us, directly or as a node of a graph: a whole chunk of one group first left the others idle for
+    // its 100 launches)
+    for (int s = 0; s <= n; ++s) {
+      for (int g = 0; g < c->ngroups; ++g) {
+        const int which = 2 + g, kg = c->gk[g];
+        hipStream_t st = c->gst[g];
+        std::vector<Entry> pe, c1, sl, pl;
+        if (c->split) {
+          if (s > 0) pe.push_back(split_pencil(c, which, kg, s - 1, n));
+          split_real(c, which, kg, s, n, sl, pl);
+        } else {
+          if (s > 0) c1.push_back({c, which, M_FWD | M_KIN | M_INV | M_AXIS1, col_tiles(c->N, kg, dbl), 0});
+          const uint32_t mode = s == 0 ? M_PRE | M_FWD : s == n ? M_INV | M_POST : M_INV | M_MID | M_FWD;
+          pl.push_back({c, which, mode, plane_tiles(c->N, kg), 0});
+        }
+        QF_TRY(run_family(F_PENCIL, pe, dbl, 0, st));
+        QF_TRY(run_family(F_COL, c1, dbl, 0, st));
+        QF_TRY(run_family(F_SLAB, sl, dbl, 0, st));
+        QF_TRY(run_family(F_PLANE, pl, dbl, 0, st));
       }
-      QF_TRY(run_family(F_PENCIL, pe, dbl, 0, st));
-      QF_TRY(run_family(F_COL, c1, dbl, 0, st));
-      QF_TRY(run_family(F_SLAB, sl, dbl, 0, st));
-      QF_TRY(run_family(F_PLANE, pl, dbl, 0, st));
     }
-  }
-  for (int g = 0; g < c->ngroups; ++g) {
-    QF_HIP(c, hipEventRecord(c->ev_join[g], c->gst[g]));
-    QF_HIP(c, hipStreamWaitEvent(c->st, c->ev_join[g], 0));
-  }
-  return QFDTD_OK;
+    return QFDTD_OK;
+  });
 }
 
 // The passes of one chunk of the members (n[j] steps each), one launch per pass kind and size, on
@@ -837,18 +850,18 @@ qfdtd_status on_lanes(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n, int r0,
       if (n[j] > 0 && lane_key(ms[j]) == x.key) { lm[l].push_back(ms[j]); ln[l].push_back(n[j]); }
   }
   hipStream_t st = ms[0]->st;
-  QF_HIP(ms[0], hipEventRecord(lead->lane_fork, st));
+  std::vector<HipSide> sides;
   for (int l = 1; l < LANES; ++l)
-    if (!lm[l].empty()) QF_HIP(ms[0], hipStreamWaitEvent(lead->lane_st[l - 1], lead->lane_fork, 0));
-  for (int q = 1; q <= LANES; ++q) {
-    const int l = q % LANES;      // the common stream, with the costliest members, last
-    if (lm[l].empty()) continue;
-    for (int r = r0; r < r1; ++r) QF_TRY(run(lm[l], ln[l], r, l ? lead->lane_st[l - 1] : st));
-    if (l) QF_HIP(ms[0], hipEventRecord(lead->lane_join[l - 1], lead->lane_st[l - 1]));
-  }
-  for (int l = 1; l < LANES; ++l)
-    if (!lm[l].empty()) QF_HIP(ms[0], hipStreamWaitEvent(st, lead->lane_join[l - 1], 0));
-  return QFDTD_OK;
+    if (!lm[l].empty()) sides.push_back({lead->lane_st[l - 1], lead->lane_join[l - 1]});
+  HipStreams hs{ms[0]};
+  return fork_join(hs, st, lead->lane_fork, sides, [&]() -> qfdtd_status {
+    for (int q = 1; q <= LANES; ++q) {
+      const int l = q % LANES;      // the common stream, with the costliest members, last
+      if (lm[l].empty()) continue;
+      for (int r = r0; r < r1; ++r) QF_TRY(run(lm[l], ln[l], r, l ? lead->lane_st[l - 1] : st));
+    }
+    return QFDTD_OK;
+  });
 }
 
 // A chunk of one or several members.  While launches are timed everything runs on one stream, so that
