@@ -822,33 +822,25 @@ int lane_key(const qfdtd_ctx *c) {
 // (as the state groups of one solve are) the batch of 12 took 22.2 instead of 19.7 ms.
 template <class Run>
 qfdtd_status on_lanes(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n, int r0, int r1, qfdtd_ctx *lead, Run run) {
-  struct Share { int key; double cost; };
-  std::vector<Share> shares;
+  std::vector<LaneMember> lms;
   for (size_t j = 0; j < ms.size(); ++j) {
-    if (n[j] <= 0) continue;
     const qfdtd_ctx *c = ms[j];
-    const int key = lane_key(c);
-    auto it = std::find_if(shares.begin(), shares.end(), [&](const Share &x) { return x.key == key; });
-    // per step: the state's traffic at 5 TB/s, and two launches
-    if (it == shares.end()) { shares.push_back({key, 8e-6}); it = shares.end() - 1; }
-    it->cost += 4.0 * (double)c->k * (double)c->n3() * (double)c->csz() / 5e12 * (c->fft() && !c->plane && !c->split ? 2 : 1);
+    // per step: the state's traffic at 5 TB/s
+    const double cost = 4.0 * (double)c->k * (double)c->n3() * (double)c->csz() / 5e12 *
+                        (c->fft() && !c->plane && !c->split ? 2 : 1);
+    lms.push_back({lane_key(c), cost, n[j] > 0, c->timer.every > 0});
   }
-  if (shares.size() < 2 || !lead || !lead->lane_fork) {
+  const std::vector<std::vector<size_t>> dealt = deal_lanes(lms, lead && lead->lane_fork ? LANES : 1);
+  bool forks = false;
+  for (size_t l = 1; l < dealt.size(); ++l) forks = forks || !dealt[l].empty();
+  if (!forks) {      // in the members' own order
     for (int r = r0; r < r1; ++r) QF_TRY(run(ms, n, r, ms[0]->st));
     return QFDTD_OK;
   }
-  std::sort(shares.begin(), shares.end(), [](const Share &x, const Share &y) {
-    return x.cost != y.cost ? x.cost > y.cost : x.key < y.key;
-  });
-  double load[LANES] = {0};
   std::vector<qfdtd_ctx *> lm[LANES];
   std::vector<int> ln[LANES];
-  for (const Share &x : shares) {
-    const int l = (int)(std::min_element(load, load + LANES) - load);
-    load[l] += x.cost;
-    for (size_t j = 0; j < ms.size(); ++j)
-      if (n[j] > 0 && lane_key(ms[j]) == x.key) { lm[l].push_back(ms[j]); ln[l].push_back(n[j]); }
-  }
+  for (int l = 0; l < LANES; ++l)
+    for (size_t j : dealt[l]) { lm[l].push_back(ms[j]); ln[l].push_back(n[j]); }
   hipStream_t st = ms[0]->st;
   std::vector<HipSide> sides;
   for (int l = 1; l < LANES; ++l)
@@ -864,15 +856,11 @@ qfdtd_status on_lanes(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n, int r0,
   });
 }
 
-// A chunk of one or several members.  While launches are timed everything runs on one stream, so that
-// every timed launch has the device to itself (as under a profiler) and its duration is the kernel's
-// own.
+// A chunk of one or several members; on one stream while launches are timed (see deal_lanes).
 qfdtd_status run_chunk(std::vector<qfdtd_ctx *> &ms, std::vector<int> &n, qfdtd_ctx *lead) {
   if (ms.empty()) return QFDTD_OK;
-  bool timed = false;
-  for (auto *c : ms) timed = timed || c->timer.every > 0;
-  if (!timed && ms.size() == 1 && ms[0]->ngroups >= 2 && n[0] > 0) return run_chunk_grouped(ms[0], n[0]);
-  return on_lanes(ms, n, -1, *std::max_element(n.begin(), n.end()), timed ? nullptr : lead, chunk_step);
+  if (ms.size() == 1 && ms[0]->ngroups >= 2 && n[0] > 0 && ms[0]->timer.every <= 0) return run_chunk_grouped(ms[0], n[0]);
+  return on_lanes(ms, n, -1, *std::max_element(n.begin(), n.end()), lead, chunk_step);
 }
 
 // E_i = <psi_i|H|psi_i>/<psi_i|psi_i> in FP64, to device and pinned host memory; with_trace also records a

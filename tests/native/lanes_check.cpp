@@ -1,5 +1,6 @@
 // fork_join on a model of streams and events: whatever fails, the work that was launched on a side stream
-// comes before anything that follows on the common stream, or has been waited for on the host.
+// comes before anything that follows on the common stream, or has been waited for on the host.  And
+// deal_lanes: every active member once, keys together, one stream while launches are timed.
 #include <cstdio>
 #include <map>
 #include <set>
@@ -29,7 +30,42 @@ static void check(bool ok, const std::string &what) {
   if (!ok) { ++failures; std::printf("FAIL %s\n", what.c_str()); }
 }
 
+static void check_deal() {
+  for (unsigned seed = 1; seed <= 200; ++seed) {
+    unsigned r = seed * 2654435761u;
+    auto next = [&](unsigned n) { r = r * 1664525u + 1013904223u; return (r >> 16) % n; };
+    std::vector<qf::LaneMember> ms;
+    const unsigned count = 1 + next(12);
+    for (unsigned j = 0; j < count; ++j) ms.push_back({(int)next(6), 1e-6 * (1 + next(500)), next(5) != 0, next(20) == 0});
+    const int n = 1 + (int)next(4);
+    const auto lanes = qf::deal_lanes(ms, n);
+    const std::string at = "deal " + std::to_string(seed);
+    std::map<size_t, int> where;
+    std::set<int> keys;
+    bool timed = false, together = true;
+    size_t dealt = 0, used = 0;
+    for (size_t l = 0; l < lanes.size(); ++l) {
+      used += !lanes[l].empty();
+      for (size_t j : lanes[l]) { where[j] = (int)l; ++dealt; }
+    }
+    size_t active = 0;
+    for (size_t j = 0; j < ms.size(); ++j)
+      if (ms[j].active) {
+        ++active;
+        keys.insert(ms[j].key);
+        timed = timed || ms[j].timed;
+        for (size_t i = 0; i < j; ++i)
+          if (ms[i].active && ms[i].key == ms[j].key) together = together && where[i] == where[j];
+      }
+    check((int)lanes.size() == n && dealt == active && where.size() == active, at + ": every active member once");
+    check(together, at + ": members of a key together");
+    if (timed) check(lanes[0].size() == active, at + ": timed launches on the common stream");
+    else check(used == std::min(keys.size(), (size_t)n), at + ": every stream used");
+  }
+}
+
 int main() {
+  check_deal();
   for (int nside = 0; nside <= 3; ++nside)
     for (int run_fails = -1; run_fails <= 2 * nside; ++run_fails)       // the launch that fails, -1: none
       for (int fail_at = -1; fail_at <= 1 + 3 * nside; ++fail_at) {     // the stream or event call that fails

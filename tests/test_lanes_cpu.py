@@ -1,5 +1,5 @@
-"""Work forked over streams is joined again, also where a launch or a stream call fails (host code on a
-model of streams and events)."""
+"""Work forked over streams is joined again, also where a launch or a stream call fails, and a batch whose
+launches are timed keeps one stream (host code on a model of streams and events)."""
 import os
 import shutil
 import subprocess
