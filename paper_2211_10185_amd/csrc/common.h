@@ -18,6 +18,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "kernel_table.h"
+
 namespace qf {
 
 template <typename T> struct CT;
@@ -226,41 +228,6 @@ __device__ __forceinline__ int find_entry(const LaunchList &L, int blk) {
   }
   return lo;
 }
-
-// Kernels of one split-x2 variant (x2 = n1 x N/n1, plane groups of xi, pencil tiles of pencil_tt x3
-// columns); pencil is null where the variant does not exist, and a slab entry where the variant has
-// no use for that kind.  plane_edges: chunks start and end with plane passes (M_SPLIT) instead of
-// slab passes.
-enum { SLAB_REAL = 0, SLAB_COMPLEX = 1, SLAB_EDGE = 2, SLAB_AB = 3, SLAB_KINDS = 4 };
-constexpr int SPLIT_VARIANTS = 5;
-struct SplitKernels {
-  const void *slab[SLAB_KINDS];
-  const void *pencil;
-  size_t slab_lds, pencil_lds;
-  int slab_nt, pencil_nt, n1, xi, pencil_tt;
-  bool plane_edges;
-};
-
-// Kernels of the FP64 energy measurement of one lattice size (slab: by state precision); pencil is null
-// where the size has none.  tps, pps: tiles of one state.
-struct MeasKernels {
-  const void *slab[2];
-  const void *pencil;
-  size_t slab_lds, pencil_lds;
-  int slab_nt, pencil_nt, tps, pps;
-};
-
-// Transform-pass kernels instantiated for one lattice size (index 0: complex64,
-// 1: complex128); plane entries are null where an N^2 plane does not fit LDS.
-struct FftKernels {
-  const void *plane[2];
-  const void *row[2];
-  const void *col[2];
-  size_t plane_lds[2], row_lds[2], col_lds[2];
-  int plane_nt;
-  SplitKernels split[2][SPLIT_VARIANTS];   // two-pass split-x2 schedule: precision, variant
-  MeasKernels meas;
-};
 
 // Multi-size transform-pass kernels of one size group (see fft_inst.hip).
 struct GroupKernels {

@@ -152,29 +152,12 @@ hipError_t fft_table_init() {
           if (e != hipSuccess) return e;
         }
     }
-  for (int n = 0; n <= 256; ++n)
-    for (int w = 0; w < 2; ++w) {
-      const void *fs[3] = {g_fft[n].plane[w], g_fft[n].row[w], g_fft[n].col[w]};
-      const size_t ls[3] = {g_fft[n].plane_lds[w], g_fft[n].row_lds[w], g_fft[n].col_lds[w]};
-      for (int q = 0; q < 3; ++q)
-        if (fs[q]) {
-          hipError_t e = hipFuncSetAttribute(fs[q], hipFuncAttributeMaxDynamicSharedMemorySize, (int)ls[q]);
-          if (e != hipSuccess) return e;
-        }
-    }
-  for (int n = 0; n <= 256; ++n)
-    for (int w = 0; w < 2; ++w)
-      for (int v = 0; v < SPLIT_VARIANTS; ++v) {
-        const SplitKernels &k = g_fft[n].split[w][v];
-        if (!k.pencil) continue;
-        hipError_t e = hipFuncSetAttribute(k.pencil, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.pencil_lds);
-        if (e != hipSuccess) return e;
-        for (const void *f : k.slab) {
-          if (!f) continue;
-          e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.slab_lds);
-          if (e != hipSuccess) return e;
-        }
-      }
+  for (const FftKernels &k : g_fft) {
+    const hipError_t e = for_each_kernel(k, hipSuccess, [](const void *f, size_t lds) {
+      return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    });
+    if (e != hipSuccess) return e;
+  }
   done = true;
   return hipSuccess;
 }

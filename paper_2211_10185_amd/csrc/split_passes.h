@@ -591,6 +591,7 @@ __device__ __forceinline__ void pencil_body(const LaunchList &L, int e, int t, u
 
 // Fixed-order block sums of NV values per thread: wave shuffles, then the waves in order.  Thread 0
 // returns with the sums in acc.
+template <int NV, int NT> __host__ __device__ constexpr size_t block_sums_lds() { return (NT + 63) / 64 * NV * sizeof(double); }
 template <int NV, int NT> __device__ __forceinline__ void block_sums(double (&acc)[NV]) {
   constexpr int NW = (NT + 63) / 64;
   __shared__ double red[NW][NV];
@@ -998,6 +999,10 @@ __global__ void __launch_bounds__((split_def(N, 1, 0).pencil_nt)) k_pencil_meas_
 }
 template <int N> void register_meas(FftKernels *tab) {
   constexpr SplitDef D = split_def(N, 1, 0);
+  static_assert(slab_lds_t<double, N, D.N1, D.XI, D.slab_plan>() + block_sums_lds<3, D.slab_nt>() <= 160 * 1024,
+                "slab tile and block sums fit LDS");
+  static_assert(pencil_lds_t<double, N, N / D.N1, D.TT, D.pencil_plan, false>() + block_sums_lds<1, D.pencil_nt>() <= 160 * 1024,
+                "pencil tile and block sums fit LDS");
   MeasKernels &k = tab[N].meas;
   k.slab[0] = (const void *)k_slab_meas_t<float, N>;
   k.slab[1] = (const void *)k_slab_meas_t<double, N>;
