@@ -35,6 +35,7 @@ SPLIT_C128_SIZES = (32, 36, 40, 48, 50, 54, 60, 64, 72, 80, 90, 96, 100, 108, 12
                     200, 216, 240, 250, 256)
 SPLIT_SMALL_SIZES = (32, 36, 40, 48, 50, 54, 60, 64, 72, 80, 90)     # complex64, one tile shape
 SPLIT_C128_SECOND = (40, 48, 72, 80, 96, 108, 120, 150, 160, 162, 192, 216, 250)
+SPLIT_C64_SECOND = (150, 162, 250)     # complex64: the second tile shape where 4 does not divide N
 _cache: Optional[Dict[str, dict]] = None
 
 
@@ -108,7 +109,7 @@ def candidates(N: int, precision: int, k: int):
         for g in groups:
             out.append({"rowcol": rowcol, "single_stream": g == 1, "groups": g, "split": False})
     if N in SPLIT_SIZES[precision]:
-        # variant 1 (2-column tiles) differs from variant 0 only where 4 divides N
+        # variant 1 where 4 does not divide N: more_candidates
         variants = ([0] + ([1] if N % 4 == 0 else []) + ([2] if N in SPLIT_WIDE_SIZES[precision] else [])
                     + ([3] if N in SPLIT_SWAPPED_SIZES[precision] else []))
         groups = [1, 2, 3] if k >= 3 else ([1, 2] if k >= 2 else [1])
@@ -125,16 +126,26 @@ def single_shape_split(N: int, precision: int) -> bool:
 
 
 def more_candidates(N: int, precision: int, k: int):
-    """Split-x2 candidates of the sizes with one or two tile shapes and no choice of factors."""
-    if not single_shape_split(N, precision):
-        return []
-    variants = [0] + ([1] if precision == 1 and N in SPLIT_C128_SECOND else [])
+    """The split-x2 candidates that ``candidates`` leaves out: every one of the sizes without a choice of
+    factors, and the second tile shape of complex64 where 4 does not divide N."""
+    if precision == 1:
+        variants = ([0] if N in SPLIT_C128_SIZES else []) + ([1] if N in SPLIT_C128_SECOND else [])
+    else:
+        variants = ([0] if N in SPLIT_SMALL_SIZES else []) + ([1] if N in SPLIT_C64_SECOND else [])
     groups = [1, 2, 3] if k >= 3 else ([1, 2] if k >= 2 else [1])
     return [{"rowcol": False, "single_stream": g == 1, "groups": g, "split": True, "split_variant": v}
             for v in variants for g in groups]
 
 
+def schedule_name(c: dict) -> str:
+    """The schedule as a word of its own: what ``tune`` files times under."""
+    kind = "split/v%d" % c.get("split_variant", 0) if c.get("split") else ("rowcol" if c["rowcol"] else "plane")
+    return "%s/%d" % (kind, c.get("groups", 1))
+
+
 def candidate_name(c: dict, N: int = 256) -> str:
+    """A short description of one of ``candidates`` by its tile columns (complex64; not a key: variants of
+    other sizes and precisions may share it)."""
     if c.get("split"):
         v = c.get("split_variant", 0)
         cols = 4 if N % 4 == 0 else 2
@@ -191,7 +202,7 @@ def tune(sizes: Iterable[int], precisions: Iterable[int] = (0,), states: Iterabl
                     continue
                 times, cands = {}, {}
                 for c in candidates(N, prec, k) + more_candidates(N, prec, k):
-                    name = candidate_name(c, N)
+                    name = schedule_name(c)
                     cands[name] = c
                     times[name] = time_schedule(N, prec, k, c, steps)
                 best = min(times, key=times.get)

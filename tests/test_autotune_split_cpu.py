@@ -1,0 +1,56 @@
+"""The autotuner's split-x2 candidates against the kernels that are built, and what ``tune`` keeps of them, on the
+CPU (the timing is replaced)."""
+import json
+import os
+import re
+
+import pytest
+
+import synthetic as S
+from paper_2211_10185_amd import autotune as A
+
+SIZES = list(S.smooth_even_sizes(32, 256))
+
+
+def all_candidates(N, prec, k):
+    return A.candidates(N, prec, k) + A.more_candidates(N, prec, k)
+
+
+def built_variants():
+    """(N, precision) -> the variants of the shape table that a flag can select (4 is the A/B update's own)."""
+    src = open(os.path.join(A.HERE, "csrc", "split_passes.h")).read()
+    rows = re.findall(r"^    \{(\d+), ([01]), (\d), ", src, re.M)
+    assert len(rows) > 100
+    out = {}
+    for n, p, v in rows:
+        if v != "4":
+            out.setdefault((int(n), int(p)), set()).add(int(v))
+    return out
+
+
+def test_every_built_variant_is_a_candidate_and_no_other():
+    built = built_variants()
+    for N in SIZES:
+        for prec in (0, 1):
+            offered = {c["split_variant"] for c in all_candidates(N, prec, 3) if c["split"]}
+            assert offered == built.get((N, prec), set()), (N, prec)
+
+
+@pytest.mark.parametrize("k", [1, 2, 3])
+def test_tune_times_and_records_every_candidate(tmp_path, monkeypatch, k):
+    path = str(tmp_path / "tuning.json")
+    monkeypatch.setattr(A, "_device_name", lambda: "test")
+    monkeypatch.setattr(A, "_cache", None)
+    for prec in (0, 1):
+        for N in SIZES:
+            cands = all_candidates(N, prec, k)
+            assert len({A.schedule_name(c) for c in cands}) == len(cands), (N, prec)
+            # each in turn is the fastest, and is what the entry says
+            for want in cands:
+                monkeypatch.setattr(A, "time_schedule", lambda N, p, k, s, steps: 1.0 if s == want else 2.0)
+                if os.path.exists(path):
+                    os.remove(path)
+                e = A.tune([N], precisions=(prec,), states=(k,), path=path, verbose=False)[A.key(N, prec, k)]
+                assert len(e["us_per_step"]) == len(cands), (N, prec)
+                assert (e["split"], e["rowcol"], e["groups"], e["split_variant"]) == (
+                    want["split"], want["rowcol"], want["groups"], want.get("split_variant", 0)), (N, prec)
