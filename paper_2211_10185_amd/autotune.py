@@ -16,6 +16,7 @@ cache; ``schedule_for`` is what ``Solver`` consults at creation.
 Cache: ``$QFDTD_TUNING`` if set, else ``tuning.json`` next to this file.
 Entry key: "N/precision/states" with states clipped to {1, 2+}.  An entry with a "pinned" note
 was chosen from another measurement (the note says which) and ``tune`` leaves it as it is.
+A complex64 entry keeps its rounding (``rounding``) when it is tuned again.
 """
 from __future__ import annotations
 
@@ -143,6 +144,22 @@ def schedule_name(c: dict) -> str:
     return "%s/%d" % (kind, c.get("groups", 1))
 
 
+def rounding(c: dict, N: int, precision: int) -> Optional[str]:
+    """What decides the roundings of a complex64 step under the schedule: the radix sequence of its line
+    transforms and the factors of x2, not its tiles or groups.  The energies of complex64 solves (FP64 sums
+    over FP32 states) keep their digits only as long as this stays: other factors move them by up to 1e-6.
+    Complex128 results move within 1e-14, so there it decides nothing (None)."""
+    if precision == 1:
+        return None
+    if not c.get("split"):
+        return "rowcol" if c["rowcol"] else "plane"
+    if N in SPLIT_SMALL_SIZES:
+        return "plane"                      # the operations of the plane passes
+    v = c.get("split_variant", 0)
+    # the 8-row tiles are the default factors at 128 (16 x 8) and others at 256 (32 x 8)
+    return "swapped" if v == 3 else "32 x 8" if v == 2 and N == 256 else "default"
+
+
 def candidate_name(c: dict, N: int = 256) -> str:
     """A short description of one of ``candidates`` by its tile columns (complex64; not a key: variants of
     other sizes and precisions may share it)."""
@@ -182,10 +199,18 @@ def time_schedule(N: int, precision: int, k: int, sched: dict, steps: int = 400,
 
 
 def tune(sizes: Iterable[int], precisions: Iterable[int] = (0,), states: Iterable[int] = (1, 3),
-         steps: int = 400, path: Optional[str] = None, verbose: bool = True) -> Dict[str, dict]:
-    """Time every candidate schedule and write the winners to the cache."""
+         steps: int = 400, path: Optional[str] = None, verbose: bool = True, keep: Optional[str] = None) -> Dict[str, dict]:
+    """Time every candidate schedule and write the winners to the cache at `path`.
+
+    Where the cache at `keep` (default: the one that is written) has a complex64 entry, only candidates
+    with the roundings of that entry are timed (see ``rounding``)."""
     global _cache
     path = path or cache_path()
+    try:
+        with open(keep or path) as f:
+            kept = json.load(f).get("entries", {})
+    except (OSError, ValueError):
+        kept = {}
     try:
         with open(path) as f:
             doc = json.load(f)
@@ -201,7 +226,10 @@ def tune(sizes: Iterable[int], precisions: Iterable[int] = (0,), states: Iterabl
                         print("tune N=%d prec=%d k=%d: pinned, kept" % (N, prec, k), flush=True)
                     continue
                 times, cands = {}, {}
+                old = kept.get(key(N, prec, k))
                 for c in candidates(N, prec, k) + more_candidates(N, prec, k):
+                    if old and rounding(c, N, prec) != rounding(old, N, prec):
+                        continue
                     name = schedule_name(c)
                     cands[name] = c
                     times[name] = time_schedule(N, prec, k, c, steps)
@@ -239,4 +267,4 @@ if __name__ == "__main__":
     ap.add_argument("--precisions", type=int, nargs="*", default=[0, 1], help="0: complex64, 1: complex128")
     a = ap.parse_args()
     sizes = a.sizes or [n for n in S.smooth_even_sizes(32, 256)]
-    tune(sizes, precisions=a.precisions, states=(1, 3), steps=a.steps, path=a.out)
+    tune(sizes, precisions=a.precisions, states=(1, 3), steps=a.steps, path=a.out, keep=cache_path())

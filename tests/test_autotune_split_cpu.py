@@ -54,3 +54,38 @@ def test_tune_times_and_records_every_candidate(tmp_path, monkeypatch, k):
                 assert len(e["us_per_step"]) == len(cands), (N, prec)
                 assert (e["split"], e["rowcol"], e["groups"], e["split_variant"]) == (
                     want["split"], want["rowcol"], want["groups"], want.get("split_variant", 0)), (N, prec)
+
+
+@pytest.mark.parametrize("N", [64, 108, 128, 150, 162, 180, 250, 256])
+def test_tuning_again_keeps_the_roundings_of_complex64(tmp_path, monkeypatch, N):
+    """A faster schedule with other factors of x2 does not take an entry over; one with the same does."""
+    path = str(tmp_path / "tuning.json")
+    monkeypatch.setattr(A, "_device_name", lambda: "test")
+    monkeypatch.setattr(A, "_cache", None)
+    cands = all_candidates(N, 0, 3)
+    for old in cands:
+        entry = dict(old, split_variant=old.get("split_variant", 0))
+        same = [c for c in cands if A.rounding(c, N, 0) == A.rounding(old, N, 0)]
+        assert old in same
+        for out in (path, str(tmp_path / "other.json")):
+            with open(path, "w") as f:
+                json.dump({"entries": {A.key(N, 0, 3): entry}}, f)
+            # the others are faster than all of its kind, and of its kind the last one is
+            times = {A.schedule_name(c): 5.0 - i / 100 if c in same else 1.0 for i, c in enumerate(cands)}
+            monkeypatch.setattr(A, "time_schedule", lambda N, p, k, s, steps: times[A.schedule_name(s)])
+            e = A.tune([N], precisions=(0,), states=(3,), path=out, verbose=False, keep=path)[A.key(N, 0, 3)]
+            assert sorted(e["us_per_step"]) == sorted(A.schedule_name(c) for c in same)
+            assert A.schedule_name(e) == A.schedule_name(same[-1])
+
+
+def test_roundings_follow_the_factors_of_the_shape_table():
+    src = open(os.path.join(A.HERE, "csrc", "split_passes.h")).read()
+    n1 = {(int(n), int(v)): int(f) for n, v, f in re.findall(r"^    \{(\d+), 0, (\d), (\d+), ", src, re.M) if v != "4"}
+    for N in SIZES:
+        if N < 96:
+            continue
+        for c in all_candidates(N, 0, 1):
+            for d in all_candidates(N, 0, 1):
+                if c["split"] and d["split"]:
+                    same = n1[N, c["split_variant"]] == n1[N, d["split_variant"]]
+                    assert (A.rounding(c, N, 0) == A.rounding(d, N, 0)) == same, (N, c, d)
