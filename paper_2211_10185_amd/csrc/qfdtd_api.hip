@@ -209,7 +209,7 @@ struct qfdtd_ctx {
   int N = 0, kin = 0, prec = 0, k = 0, K = 50;
   double a = 0, m = 0;
   int sectors[MAX_STATES] = {0};
-  bool any_parity = false, vcomplex = false, dbl = false, plane = false, plane64 = false;
+  bool any_parity = false, vcomplex = false, dbl = false, plane = false, plane_fft = false, plane64 = false;
   bool split = false;           // FFT kinds: the two-pass split-x2 schedule (slab and pencil passes)
   int split_v = 0;              // split-x2 variant (x2 = N1 x N2 and the pencil tile width)
   int scheme = SCHEME_SPLIT;    // FFT kinds: split-operator step or A/B update
@@ -1176,6 +1176,11 @@ qfdtd_status qfdtd_create(qfdtd_ctx **out, int32_t N, double a, double m, int32_
   c->split_v = c->scheme == SCHEME_AB && !c->dbl ? 4 : (int)QFDTD_SPLIT_VARIANT(o.flags);
   c->split = c->fft() && (o.flags & QFDTD_F_SPLIT_X2) && split_of(c).pencil != nullptr;
   c->plane = c->fft() && g_fft[N].plane[c->dbl ? 1 : 0] != nullptr && !(o.flags & QFDTD_F_ROWCOL) && !c->split;
+  // one transform of a state takes the plane pass too where the split-x2 steps have its roundings, or FP64;
+  // elsewhere the row and column passes (their inverse takes the axes in another order, so the FP32
+  // results would change)
+  c->plane_fft = c->plane || (c->split && !(o.flags & QFDTD_F_ROWCOL) && g_fft[N].plane[c->dbl ? 1 : 0] != nullptr &&
+                              (c->dbl || split_of(c).plane_edges));
   c->plane64 = c->fft() && g_fft[N].plane[1] != nullptr;
   c->nblk_red = red_blocks(n3);
   c->trace_on = o.trace_energies ? 1 : 0;
@@ -1563,7 +1568,7 @@ qfdtd_status qfdtd_transform_state(qfdtd_ctx *c, int32_t i, int32_t sign) {
   std::vector<Entry> pl, rw, c2, c1;
   const uint32_t dir = sign < 0 ? M_FWD : M_INV;
   const bool dbl = c->dbl;
-  if (c->plane) pl.push_back({c, 0, dir, plane_tiles(c->N, 1), 0});
+  if (c->plane_fft) pl.push_back({c, 0, dir, plane_tiles(c->N, 1), 0});
   else {
     rw.push_back({c, 0, dir, row_tiles(c->N, 1, dbl), 0});
     c2.push_back({c, 0, dir, col_tiles(c->N, 1, dbl), 0});
