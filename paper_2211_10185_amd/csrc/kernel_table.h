@@ -15,7 +15,7 @@ struct SplitKernels {
   const void *slab[SLAB_KINDS];
   const void *pencil;
   size_t slab_lds, pencil_lds;
-  int slab_nt, pencil_nt, n1, xi, pencil_tt;
+  int slab_nt[SLAB_KINDS], pencil_nt, n1, xi, pencil_tt;
   bool plane_edges;
 };
 

@@ -504,7 +504,7 @@ qfdtd_status run_family(Fam f, std::vector<Entry> &es, bool dbl, int KS, hipStre
       if (tix >= 0) (void)hipExtLaunchKernel(fn, dim3(total), dim3(nt), kargs, sh, st, ea, eb, 0);
       else (void)hipLaunchKernel(fn, dim3(total), dim3(nt), kargs, sh, st);
     };
-    if (f >= F_SLAB_KIND) go(split_of(c0).slab[f - F_SLAB_KIND], split_of(c0).slab_nt, lds);
+    if (f >= F_SLAB_KIND) go(split_of(c0).slab[f - F_SLAB_KIND], split_of(c0).slab_nt[f - F_SLAB_KIND], lds);
     else switch (f) {
       case F_PLANE: go(fplane, ntplane, lds); break;
       case F_ROW: go(frow, LINE_THREADS, lds); break;

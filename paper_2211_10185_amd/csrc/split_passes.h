@@ -777,7 +777,12 @@ __device__ __forceinline__ void pencil_meas_body(const PassDesc &d, int t, unsig
 //   - pencil pieces of 32 bytes and more (XI TT >= 4 in complex64, >= 2 in complex128): the L1 is
 //     bound by requests below that; 64 bytes where the LDS holds the tile (256^3, complex128, one / three
 //     states: 420 / 1169 -> 330 / 925 us per step; one pencil tile of 157 KB per CU);
-//   - at small N more, smaller tiles: one per (plane, row digit) with 64 to 256 threads.
+//   - at small N more, smaller tiles: one per (plane, row digit) with 64 to 256 threads;
+//   - a complex factor takes twice the registers of a real one in the slab pass's middle stage.  Where that
+//     goes past the 256 of a lane or costs a wave per SIMD the kernel has threads (and fused stages) of its
+//     own, found by timing them at every size (us per step with a complex V, one / three states, the
+//     threads of the real factor -> its own): complex64 150^3 59 / 124 -> 57 / 121, 180^3 131 / 275 -> 92 /
+//     194, 192^3 94 / 211 -> 85 / 187, 216^3 three states 460 -> 383, complex128 216^3 315 / 816 -> 284 / 729.
 // Variants:
 //   0: the fastest for three states;  1: complex64 from 96 up: the fastest other shape of the same
 //   factors (complex128: the fastest for one state or for the A/B
@@ -787,6 +792,7 @@ __device__ __forceinline__ void pencil_meas_body(const PassDesc &d, int t, unsig
 struct SplitDef {
   int N, dbl, v, N1, XI, TT, slab_nt, slab_plan, pencil_nt, pencil_plan;
   bool pencil_hx = false;
+  int slab_c_nt = 0, slab_c_plan = 0;      // of the slab pass with a complex factor, where they are its own
 };
 constexpr SplitDef SPLIT_DEFS[] = {
     {32, 0, 0, 4, 1, 4, 64, rp(8, 4), 128, rp(8, 4)},
@@ -834,7 +840,7 @@ constexpr SplitDef SPLIT_DEFS[] = {
     {144, 0, 0, 16, 1, 4, 256, rp(16, 9), 576, rp(16, 9)},
     {144, 0, 1, 16, 2, 2, 512, rp(16, 9), 320, rp(16, 9)},
     {144, 0, 3, 9, 2, 2, 192, rp(16, 9), 320, rp(16, 9)},
-    {150, 0, 0, 15, 1, 2, 128, rp(6, st(5, 5)), 320, rp(6, 5, 5)},
+    {150, 0, 0, 15, 1, 2, 128, rp(6, st(5, 5)), 320, rp(6, 5, 5), false, 256, rp(6, 5, 5)},
     {150, 0, 1, 15, 2, 2, 320, rp(6, st(5, 5)), 320, rp(6, 5, 5)},
     {150, 0, 3, 10, 1, 2, 256, rp(6, 5, 5), 320, rp(6, 5, 5)},
     {160, 0, 0, 16, 1, 4, 256, rp(16, 10), 640, rp(16, 10)},
@@ -843,16 +849,16 @@ constexpr SplitDef SPLIT_DEFS[] = {
     {162, 0, 0, 18, 1, 2, 192, rp(18, 9), 384, rp(18, 9)},
     {162, 0, 1, 18, 2, 2, 384, rp(18, 9), 384, rp(18, 9)},
     {162, 0, 3, 9, 1, 2, 192, rp(18, 9), 384, rp(18, 9)},
-    {180, 0, 0, 18, 1, 4, 192, rp(4, 9, 5), 768, rp(4, 9, 5)},
-    {180, 0, 1, 18, 1, 2, 192, rp(4, 9, 5), 384, rp(4, 9, 5)},
+    {180, 0, 0, 18, 1, 4, 192, rp(4, 9, 5), 768, rp(4, 9, 5), false, 256},
+    {180, 0, 1, 18, 1, 2, 192, rp(4, 9, 5), 384, rp(4, 9, 5), false, 256},
     {180, 0, 3, 10, 1, 4, 256, rp(4, 9, 5), 768, rp(4, 9, 5)},
-    {192, 0, 0, 16, 1, 4, 192, rp(8, st(8, 3)), 768, rp(8, 8, 3), true},
+    {192, 0, 0, 16, 1, 4, 192, rp(8, st(8, 3)), 768, rp(8, 8, 3), true, 256, rp(8, 8, 3)},
     {192, 0, 1, 16, 2, 2, 256, rp(8, st(8, 3)), 384, rp(8, 8, 3)},
     {192, 0, 3, 12, 1, 4, 192, rp(8, 8, 3), 768, rp(8, st(8, 3))},
     {200, 0, 0, 20, 1, 4, 256, rp(8, st(5, 5)), 832, rp(8, 5, 5)},
     {200, 0, 1, 20, 1, 2, 256, rp(8, st(5, 5)), 448, rp(8, 5, 5)},
     {200, 0, 3, 10, 1, 4, 256, rp(8, 5, 5), 832, rp(8, st(5, 5))},
-    {216, 0, 0, 18, 2, 2, 448, rp(8, st(9, 3)), 448, rp(8, 9, 3)},
+    {216, 0, 0, 18, 2, 2, 448, rp(8, st(9, 3)), 448, rp(8, 9, 3), false, 512},
     {216, 0, 1, 18, 1, 2, 256, rp(8, st(9, 3)), 448, rp(8, 9, 3)},
     {216, 0, 3, 12, 1, 4, 128, rp(8, st(9, 3)), 896, rp(8, st(9, 3))},
     {240, 0, 0, 16, 2, 2, 512, rp(16, st(3, 5)), 512, rp(16, st(3, 5)), true},
@@ -898,13 +904,19 @@ constexpr SplitDef SPLIT_DEFS[] = {
     {192, 1, 0, 12, 2, 1, 384, rp(12, 16), 192, rp(12, 16)},
     {192, 1, 1, 12, 1, 2, 192, rp(16, 12), 384, rp(12, 16)},
     {200, 1, 0, 10, 1, 2, 256, rp(5, 8, 5), 448, rp(10, 20)},
-    {216, 1, 0, 12, 2, 1, 448, rp(12, 18), 256, rp(12, 18), true},
+    {216, 1, 0, 12, 2, 1, 448, rp(12, 18), 256, rp(12, 18), true, 256},
     {216, 1, 1, 12, 1, 2, 256, rp(12, 18), 448, rp(12, 18)},
     {240, 1, 0, 15, 1, 2, 256, rp(15, 16), 512, rp(15, 16)},
     {250, 1, 0, 25, 1, 2, 256, rp(25, 10), 512, rp(25, 10)},
     {250, 1, 1, 10, 2, 1, 512, rp(5, 10, 5), 256, rp(5, 10, 5)},
     {256, 1, 0, 16, 2, 2, 512, rp(16, 16), 512, rp(16, 16)},
 };
+__host__ __device__ constexpr int slab_threads(const SplitDef &s, int kind) {
+  return kind == SLAB_COMPLEX && s.slab_c_nt ? s.slab_c_nt : s.slab_nt;
+}
+__host__ __device__ constexpr int slab_plan_of(const SplitDef &s, int kind) {
+  return kind == SLAB_COMPLEX && s.slab_c_plan ? s.slab_c_plan : s.slab_plan;
+}
 __host__ __device__ constexpr SplitDef split_def(int N, int dbl, int v) {
   for (const SplitDef &s : SPLIT_DEFS)
     if (s.N == N && s.dbl == dbl && s.v == v) return s;
@@ -916,7 +928,8 @@ __host__ __device__ constexpr int split_same(int N, int dbl, int v) {
   for (int u = 0; u < v; ++u) {
     const SplitDef b = split_def(N, dbl, u);
     if (a.N1 == b.N1 && a.XI == b.XI && a.TT == b.TT && a.slab_nt == b.slab_nt && a.slab_plan == b.slab_plan &&
-        a.pencil_nt == b.pencil_nt && a.pencil_plan == b.pencil_plan && a.pencil_hx == b.pencil_hx)
+        a.pencil_nt == b.pencil_nt && a.pencil_plan == b.pencil_plan && a.pencil_hx == b.pencil_hx && a.slab_c_nt == b.slab_c_nt &&
+        a.slab_c_plan == b.slab_c_plan)
       return u;
   }
   return v;
@@ -927,11 +940,11 @@ __host__ __device__ constexpr int split_same(int N, int dbl, int v) {
 constexpr int PENCIL_XCD_RUN = 128;
 
 template <typename T, int N, int V, int KIND>
-__global__ void __launch_bounds__((split_def(N, PKT<T>, V).slab_nt)) k_slab_t(const LaunchList L) {
+__global__ void __launch_bounds__((slab_threads(split_def(N, PKT<T>, V), KIND))) k_slab_t(const LaunchList L) {
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr SplitDef D = split_def(N, PKT<T>, V);
   const int e = find_entry(L, blockIdx.x);
-  slab_body<T, N, D.N1, D.slab_nt, D.XI, D.slab_plan, KIND>(L, e, blockIdx.x - L.tile_start[e], smem);
+  slab_body<T, N, D.N1, slab_threads(D, KIND), D.XI, slab_plan_of(D, KIND), KIND>(L, e, blockIdx.x - L.tile_start[e], smem);
 }
 
 template <typename T, int N, int V>
@@ -961,7 +974,7 @@ template <typename T, int N, int V> void register_split_variant(FftKernels *tab)
     }
     if constexpr (!F || (N >= 96 && V != 4)) k.slab[SLAB_EDGE] = (const void *)k_slab_t<T, N, U, SLAB_EDGE>;
     if constexpr (!F || V == 4) k.slab[SLAB_AB] = (const void *)k_slab_t<T, N, U, SLAB_AB>;
-    k.slab_nt = D.slab_nt;
+    for (int kind = 0; kind < SLAB_KINDS; ++kind) k.slab_nt[kind] = slab_threads(D, kind);
     k.slab_lds = slab_lds_t<T, N, D.N1, D.XI, D.slab_plan>();
     k.n1 = D.N1;
     k.xi = D.XI;
