@@ -89,3 +89,18 @@ def test_roundings_follow_the_factors_of_the_shape_table():
                 if c["split"] and d["split"]:
                     same = n1[N, c["split_variant"]] == n1[N, d["split_variant"]]
                     assert (A.rounding(c, N, 0) == A.rounding(d, N, 0)) == same, (N, c, d)
+
+
+def test_states_of_the_size_of_the_cache_run_on_one_stream(tmp_path, monkeypatch):
+    path = str(tmp_path / "tuning.json")
+    e = {"rowcol": False, "single_stream": False, "groups": 3, "split": True, "split_variant": 0}
+    plane = dict(e, split=False)
+    with open(path, "w") as f:
+        json.dump({"entries": {"162/0/2": e, "160/1/2": e, "180/0/2": plane}}, f)
+    monkeypatch.setenv("QFDTD_TUNING", path)
+    monkeypatch.setattr(A, "_cache", None)
+    for N, prec, k, groups in [(162, 0, 7, 3), (162, 0, 8, 1), (160, 1, 3, 3), (160, 1, 4, 1), (160, 1, 5, 3), (180, 0, 6, 3)]:
+        s = A.schedule_for(N, 2, prec, k)
+        assert (s["groups"], s["single_stream"]) == (groups, groups == 1), (N, prec, k)
+        assert s["split_variant"] == 0 and not s["rowcol"]
+    A._cache = None
