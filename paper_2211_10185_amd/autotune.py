@@ -66,16 +66,15 @@ def default_schedule(N: int, kinetic: int, precision: int, k: int) -> dict:
 
 
 def cache_sized(N: int, precision: int, k: int) -> bool:
-    """States that together are a little larger than the 256 MB Infinity Cache.  On one stream the passes then
-    still find most of them there; groups on streams of their own, each at another place of its states,
-    lose that.  us per step, the tuned two or three groups (timed at three states) against one stream, with
-    a real / complex V: complex64 160^3 x 8 states (262 MB) 283 / 300 -> 278 / 277, 162^3 x 8 (272 MB) 433 /
-    441 -> 402 / 420, 180^3 x 6 (280 MB) 426 / 429 -> 394 / 391, 200^3 x 4 (256 MB) 352 / 380 -> 341 / 360,
-    complex128 160^3 x 4 (262 MB) 310 / 322 -> 290 / 286, 150^3 x 5 (270 MB) 327 / 336 -> 316 / 315; but even
-    at 162^3 x 4 (272 MB) 394 / 438 -> 397 / 439 and 144^3 x 6 (287 MB) 292 / 292 -> 290 / 294, and groups win
-    below (162^3 x 6 complex64, 204 MB: 257 / 268 against 269 / 272) and above (complex128 150^3 x 8, 432 MB,
-    two groups 527 / 512 against 519 / 523; 180^3 x 4, 373 MB, 494 / 501 against 507 / 513)."""
-    return 256e6 <= k * N ** 3 * (16 if precision else 8) <= 290e6
+    """Complex64 states that together are a little larger than the 256 MB Infinity Cache.  On one stream the
+    passes then still find most of them there; groups on streams of their own, each at another place of its
+    states, lose that.  us per step, the three groups that three states are tuned to against one stream, with
+    a real / complex V: 160^3 x 8 states (262 MB) 283 / 300 -> 278 / 277, 162^3 x 8 (272 MB) 433 / 441 -> 402 /
+    420, 180^3 x 6 (280 MB) 426 / 429 -> 394 / 391, 200^3 x 4 (256 MB) 352 / 380 -> 341 / 360.  Groups win below
+    (162^3 x 6, 204 MB: 257 / 268 against 269 / 272) and are within 3% above (200^3 x 5, 320 MB: 466 / 476 against
+    464 / 466).  In complex128 it goes either way (160^3 x 4, 262 MB: 310 / 322 -> 290 / 286; 162^3 x 4, 272 MB:
+    394 / 438 -> 397 / 439), so the tuned groups stay there."""
+    return precision == 0 and 256e6 <= k * N ** 3 * 8 <= 290e6
 
 
 def schedule_for(N: int, kinetic: int, precision: int, k: int) -> dict:
