@@ -12,6 +12,7 @@
 // All reductions are two-level with a fixed grid and a fixed summation order,
 // so repeated runs, and a member run alone or inside a batch, give identical bits.
 #include "common.h"
+#include "stencil_rows.h"
 
 namespace qf {
 
@@ -129,7 +130,7 @@ __global__ void k_dt_tables(const double *v64, int vcomplex, size_t N3, double d
 // outside its 4), x3 neighbours from the adjacent lanes by wavefront shifts
 // (memory only at the tile's x3 edges), so each site is read from memory about
 // once per sweep.  Loads of ST_ZU planes are issued together.
-constexpr int ST_TX = 64, ST_RPT = 4, ST_TY = (RED_THREADS / 64) * ST_RPT, ST_ZU = 2;
+constexpr int ST_TX = 64, ST_TY = (RED_THREADS / 64) * ST_RPT, ST_ZU = 2;
 
 // Planes per tile: 8 (4 and 16 are slower at 128^3), down to 2 where the tiles would not fill the chip
 // (64^3 x 3 states: 96 tiles of 8 planes 14.4 us, 384 of 2 planes 11.6).
@@ -195,14 +196,10 @@ __device__ __forceinline__ void stencil_tile(const C<T> *__restrict__ sp, C<T> *
                                              int z0, int z1, T c, T hdt) {
   const int N2 = N * N;
   const C<T> zero = mkc<T>(0, 0);
-  const bool xin = i3 < N;
-  bool rin[ST_RPT];
-#pragma unroll
-  for (int r = 0; r < ST_RPT; ++r) rin[r] = xin && (y0 + r < N);
-  const bool up_ok = xin && y0 > 0, dn_ok = xin && y0 + ST_RPT < N;
+  const StencilRows in = stencil_rows(N, y0, i3, lane);
+  const bool (&rin)[ST_RPT] = in.rin;
   // x3 neighbour outside the wave: lane 0 needs i3-1, lane 63 needs i3+1
   const int xe_off = lane == 0 ? -1 : 1;
-  const bool xe_mem = (lane == 0 && xin && i3 > 0) || (lane == 63 && i3 + 1 < N);
   const bool xr_wall = i3 + 1 >= N;
   using VT = typename VType<T, VC>::type;
   VT vzero;
@@ -226,10 +223,10 @@ __device__ __forceinline__ void stencil_tile(const C<T> *__restrict__ sp, C<T> *
       for (int r = 0; r < ST_RPT; ++r) {
         nx[u][r] = (rin[r] && zz + 1 < N && zin) ? sp[o + r * N + N2] : zero;
         V[u][r] = (rin[r] && zin) ? load_v<T, VC>(vtab, o + r * N) : vzero;
-        xe[u][r] = (rin[r] && zin && xe_mem) ? sp[o + r * N + xe_off] : zero;
+        xe[u][r] = (rin[r] && zin && in.xe) ? sp[o + r * N + xe_off] : zero;
       }
-      up[u] = (up_ok && zin) ? sp[o - N] : zero;
-      dn[u] = (dn_ok && zin) ? sp[o + ST_RPT * N] : zero;
+      up[u] = (in.up && zin) ? sp[o - N] : zero;
+      dn[u] = (in.dn && zin) ? sp[o + ST_RPT * N] : zero;
     }
 #pragma unroll
     for (int u = 0; u < ST_ZU; ++u) {
