@@ -226,7 +226,7 @@ struct qfdtd_ctx {
   PassDesc hd[2 + MAX_GROUPS];
   int ngroups = 1;              // 2 or 3: states split into groups pipelined on their own streams
   int gk[MAX_GROUPS] = {0, 0, 0};   // states per group
-  hipStream_t gst[MAX_GROUPS] = {nullptr, nullptr, nullptr};   // of the groups after the first
+  hipStream_t gst[MAX_GROUPS] = {nullptr, nullptr, nullptr};
   hipEvent_t ev_fork = nullptr, ev_join[MAX_GROUPS] = {nullptr, nullptr, nullptr};
   hipStream_t lane_st[LANES - 1] = {nullptr, nullptr, nullptr};
   hipEvent_t lane_fork = nullptr, lane_join[LANES - 1] = {nullptr, nullptr, nullptr};
@@ -671,14 +671,11 @@ using HipSide = SideStream<HipStreams>;
 // overlaps the other group's column pass (memory bound); with the split-x2
 // schedule a group's pencil pass (one tile per CU, its loads, transforms and
 // stores in turn) overlaps the other group's slab pass.  Forked from and joined
-// to the context stream, so ordering with the caller is unchanged.  The first group
-// runs on the context stream itself: a stream costs about 24 us to create (128^3 x 3
-// states, three groups: 178 -> 155 us per context), and 90^3 x 2 states take
-// 39.8 -> 33.7 us per step.
+// to the context stream, so ordering with the caller is unchanged.
 qfdtd_status run_chunk_grouped(qfdtd_ctx *c, int n) {
   const bool dbl = c->dbl;
   std::vector<HipSide> sides;
-  for (int g = 1; g < c->ngroups; ++g) sides.push_back({c->gst[g], c->ev_join[g]});
+  for (int g = 0; g < c->ngroups; ++g) sides.push_back({c->gst[g], c->ev_join[g]});
   HipStreams hs{c};
   return fork_join(hs, c->st, c->ev_fork, sides, [&]() -> qfdtd_status {
     // step by step over the groups, so that every group starts at once (a launch costs the host about
@@ -687,7 +684,7 @@ qfdtd_status run_chunk_grouped(qfdtd_ctx *c, int n) {
     for (int s = 0; s <= n; ++s) {
       for (int g = 0; g < c->ngroups; ++g) {
         const int which = 2 + g, kg = c->gk[g];
-        hipStream_t st = g ? c->gst[g] : c->st;
+        hipStream_t st = c->gst[g];
         std::vector<Entry> pe, c1, sl, pl;
         if (c->split) {
           if (s > 0) pe.push_back(split_pencil(c, which, kg, s - 1, n));
@@ -1324,9 +1321,8 @@ qfdtd_status qfdtd_create(qfdtd_ctx **out, int32_t N, double a, double m, int32_
       if (c->alt) c->hd[2 + g].alt = (char *)c->alt + first * n3 * cs;
       c->hd[2 + g].k = c->gk[g];
       first += (size_t)c->gk[g];
-      if (g > 0)
-        okg = okg && hipStreamCreateWithFlags(&c->gst[g], hipStreamNonBlocking) == hipSuccess &&
-              hipEventCreateWithFlags(&c->ev_join[g], hipEventDisableTiming) == hipSuccess;
+      okg = okg && hipStreamCreateWithFlags(&c->gst[g], hipStreamNonBlocking) == hipSuccess &&
+            hipEventCreateWithFlags(&c->ev_join[g], hipEventDisableTiming) == hipSuccess;
     }
     if (!okg) return bail(QFDTD_E_DEVICE, "stream creation failed");
   }
