@@ -813,7 +813,7 @@ __global__ void __launch_bounds__(FIN_THREADS) k_gram_finalize(const LaunchList 
   if (residuals) {
     // R_jj = the norm of state j after projection against the earlier states of its sector
     // (G = R^H R per sector); qfdtd_gram_residuals reads it, nothing else changes
-    if (i == 0 && j < KS) d.energy[ENERGY_RDIAG + j] = d.h_energy[3 * MAX_STATES + j] = rdiag[j];
+    if (i == 0 && j < KS) d.h_energy[3 * MAX_STATES + j] = rdiag[j];
     return;
   }
   if (i < KS && j < KS) {

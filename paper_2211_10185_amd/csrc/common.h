@@ -105,8 +105,7 @@ constexpr int MAX_STAGES = 12;
 constexpr int MAX_STATES = 8;
 constexpr int MAX_PAIRS = MAX_STATES * (MAX_STATES + 1) / 2;
 constexpr int MAX_LAUNCH = 64;       // members per launch list
-constexpr int ENERGY_RDIAG = 2 * MAX_STATES + 8;           // offset of the Cholesky diagonal
-constexpr int ENERGY_WORDS = ENERGY_RDIAG + MAX_STATES;    // doubles in PassDesc::energy
+constexpr int ENERGY_WORDS = 2 * MAX_STATES + 1;           // doubles in PassDesc::energy
 constexpr int HOST_WORDS = 4 * MAX_STATES + 1;             // doubles in PassDesc::h_energy, then the evolve status
 
 // Blocks of the FP64 energy sums over n sites of H_K^(0) and of sizes without split-x2 kernels: one
@@ -169,8 +168,7 @@ struct PassDesc {
   double *partials;       // FP64 partial sums: Gram [2 pairs][nblk_red]; energies [k][en_nq][en_nb] and
                           // (FFT kinds) [k][en_nbk]
   double *coef;           // [MAX_STATES][MAX_STATES][2] FP64 orthonormalisation coefficients
-  double *energy;         // [MAX_STATES][2] last energies; [2*MAX_STATES] status word;
-                          // [ENERGY_RDIAG + j] Gram-Cholesky diagonal of state j (residual mode)
+  double *energy;         // [MAX_STATES][2] last energies; [2*MAX_STATES] status word
   double *trace;          // [cap][k][2] energy trace (or null)
   int32_t N, k, kin, vcomplex;
   int32_t nst;

@@ -209,7 +209,7 @@ struct qfdtd_ctx {
   int N = 0, kin = 0, prec = 0, k = 0, K = 50;
   double a = 0, m = 0;
   int sectors[MAX_STATES] = {0};
-  bool any_parity = false, vcomplex = false, dbl = false, plane = false, plane_fft = false, plane64 = false;
+  bool any_parity = false, vcomplex = false, dbl = false, plane = false, plane_fft = false;
   bool split = false;           // FFT kinds: the two-pass split-x2 schedule (slab and pencil passes)
   int split_v = 0;              // split-x2 variant (x2 = N1 x N2 and the pencil tile width)
   int scheme = SCHEME_SPLIT;    // FFT kinds: split-operator step or A/B update
@@ -584,22 +584,16 @@ qfdtd_status orthonormalise(std::vector<qfdtd_ctx *> &ms) {
   return QFDTD_OK;
 }
 
-// FP64 forward transform of the scratch copy (FFT members without split-x2 kernels)
+// FP64 forward transform of the scratch copy (FFT members without split-x2 kernels: N < 32, whose planes
+// fit LDS in FP64)
 qfdtd_status fwd64(std::vector<qfdtd_ctx *> &ms, hipStream_t st) {
-  std::vector<Entry> pl, rw, c2, c1;
+  std::vector<Entry> pl, c1;
   for (auto *c : ms) {
-    if (c->plane64) pl.push_back({c, 1, M_FWD, plane_tiles(c->N, c->k), 0});
-    else {
-      rw.push_back({c, 1, M_FWD, row_tiles(c->N, c->k, true), 0});
-      c2.push_back({c, 1, M_FWD, col_tiles(c->N, c->k, true), 0});
-    }
+    pl.push_back({c, 1, M_FWD, plane_tiles(c->N, c->k), 0});
     c1.push_back({c, 1, M_FWD | M_AXIS1, col_tiles(c->N, c->k, true), 0});
   }
   QF_TRY(run_family(F_PLANE, pl, true, 0, st));
-  QF_TRY(run_family(F_ROW, rw, true, 0, st));
-  QF_TRY(run_family(F_COL, c2, true, 0, st));
-  QF_TRY(run_family(F_COL, c1, true, 0, st));
-  return QFDTD_OK;
+  return run_family(F_COL, c1, true, 0, st);
 }
 
 // The sums of the energies of the members (any N, kind), on stream `st`
@@ -1181,7 +1175,6 @@ qfdtd_status qfdtd_create(qfdtd_ctx **out, int32_t N, double a, double m, int32_
   // results would change)
   c->plane_fft = c->plane || (c->split && !(o.flags & QFDTD_F_ROWCOL) && g_fft[N].plane[c->dbl ? 1 : 0] != nullptr &&
                               (c->dbl || split_of(c).plane_edges));
-  c->plane64 = c->fft() && g_fft[N].plane[1] != nullptr;
   c->nblk_red = red_blocks(n3);
   c->trace_on = o.trace_energies ? 1 : 0;
   c->graphs = !(o.flags & QFDTD_F_NO_GRAPH);

@@ -117,9 +117,8 @@ template <typename V> __device__ __forceinline__ V uniform(V x) { V r; r.x = uni
 //     x3, A to HBM;
 //   SLAB_AB: the steady mode of the A/B update (M_INV | M_COMB | M_FWD | M_ALT): the same on alt, with
 //     psi' = A psi - B (dt H_K psi) as the fused middle stage (psi in natural order);
-//   SLAB_EDGE: the other modes: chunk start (M_PRE | M_FWD: x h, forward x3, A; A/B: M_FWD | M_ALT
-//     from psi to alt), chunk end (M_INV | M_POST: A^-1, inverse x3, x h; A/B: M_INV | M_COMB) and
-//     plain transforms.
+//   SLAB_EDGE: the chunk's start (M_PRE | M_FWD: x h, forward x3, A; A/B: M_FWD | M_ALT from psi to
+//     alt) and end (M_INV | M_POST: A^-1, inverse x3, x h; A/B: M_INV | M_COMB).
 // Kernels of their own, so that the registers of one kind do not weigh on another.
 template <typename T, int N, int N1, int NT, int XI, int PK, int KIND>
 __device__ __forceinline__ void slab_body(const LaunchList &L, int e, int t, unsigned char *smem) {
@@ -290,7 +289,7 @@ __device__ __forceinline__ void slab_body(const LaunchList &L, int e, int t, uns
     }
     return;
   }
-  // Natural-order tile accesses (chunk edges, plain transforms): each thread takes elements
+  // Natural-order tile accesses of the chunk's edges: each thread takes elements
   // threadIdx.x + it NT, UB at a time, with all UB global loads issued before they are used.
   constexpr int NE = NR * N;
   constexpr int EPT = (NE + NT - 1) / NT;
@@ -329,20 +328,18 @@ __device__ __forceinline__ void slab_body(const LaunchList &L, int e, int t, uns
     }
     __syncthreads();
   };
-  // LDS lines (times the factor f if given) to the state rows
+  // LDS lines times the factor f to the state rows
   auto lds_to_natural = [&](C<T> *g, const void *f) {
     const StateBuf<T, true> sb(g);
 #pragma unroll 1
     for (int it0 = 0; it0 < EPT; it0 += UB) {
       C<T> h[UB];
-      if (f) {
 #pragma unroll
-        for (int u = 0; u < UB; ++u) {
-          const int idx = (int)threadIdx.x + (it0 + u) * NT;
-          if (it0 + u < EPT && (NE % NT == 0 || idx < NE)) {
-            const int bl = idx / N, n = idx - bl * N, pl = bl / N1, a = bl - pl * N1;
-            h[u] = fac(f, site(pl, a, n));
-          }
+      for (int u = 0; u < UB; ++u) {
+        const int idx = (int)threadIdx.x + (it0 + u) * NT;
+        if (it0 + u < EPT && (NE % NT == 0 || idx < NE)) {
+          const int bl = idx / N, n = idx - bl * N, pl = bl / N1, a = bl - pl * N1;
+          h[u] = fac(f, site(pl, a, n));
         }
       }
 #pragma unroll
@@ -351,13 +348,12 @@ __device__ __forceinline__ void slab_body(const LaunchList &L, int e, int t, uns
         if (it0 + u < EPT && (NE % NT == 0 || idx < NE)) {
           const int bl = idx / N, n = idx - bl * N, pl = bl / N1, a = bl - pl * N1;
           C<T> x = buf[Rows::at(bl, n)];
-          if (f) x = vc ? cmul(x, h[u]) : cscale(x, h[u].x);
+          x = vc ? cmul(x, h[u]) : cscale(x, h[u].x);
           sb.store(x, (uint32_t)(site(pl, a, n) * sizeof(C<T>)), 0);
         }
       }
     }
   };
-  const void *fmid = (mode & M_MID) ? d.h2fac : (mode & M_POST) ? d.hfac : nullptr;
   const bool comb = (mode & M_COMB) != 0;
   for (int s = s0; s < s1; ++s) {
     const size_t so = (size_t)s * N3 + voff;
@@ -376,21 +372,10 @@ __device__ __forceinline__ void slab_body(const LaunchList &L, int e, int t, uns
       continue;            // the chunk's last combine: no forward transform follows
     }
     if (mode & M_FWD) {
-      if (fmid) {
-        for (int idx = threadIdx.x; idx < NE; idx += NT) {
-          const int bl = idx / N, n = idx - bl * N;
-          const int pl = bl / N1, a = bl - pl * N1;
-          const C<T> h = fac(fmid, site(pl, a, n));
-          const int o = Rows::at(bl, n);
-          buf[o] = vc ? cmul(buf[o], h) : cscale(buf[o], h.x);
-        }
-        __syncthreads();
-      }
       fft_lines_t<T, PK, N, false, Rows, NT>(buf, tw);
       a_forward_from_lds(gs);
     } else {
-      // the factor of the chunk end (or a middle factor) is applied on the way out
-      lds_to_natural(gp, fmid);
+      lds_to_natural(gp, d.hfac);     // the factor of the chunk's end is applied on the way out
     }
   }
 }
