@@ -93,14 +93,21 @@ def schedule_for(N: int, kinetic: int, precision: int, k: int) -> dict:
 def ab_schedule(N: int, precision: int, k: int) -> Optional[dict]:
     """Split-x2 schedule of the A/B update of an FFT kinetic term, None where the other schedules stay.
 
-    Measured (us per step, best plane or row/column schedule against split-x2; one state / three):
-    complex64 32: 16.0 -> 12.9 / 16.4 -> 13.3, 64: 20.9 -> 16.2 / 25.7 -> 21.9, 90: 41.9 -> 29.9 /
-    58.4 -> 43.6, 128: 45.1 -> 34.4 / 90.9 -> 66.3 (above 128 the row/column passes stay: the split-x2
-    factors would change the FP32 results); complex128 64: 24.7 -> 17.3 / 34.8 -> 29.8, 128: 71.0 ->
-    45.7 / 187 -> 108, 160: 137 -> 104 / 413 -> 318, 240: 549 -> 477 / 1741 -> 1342, 256: 606 -> 513 /
-    1848 -> 1418, but 216: 366 -> 368 and 250: 616 -> 636 with one state.  At 160 and 250 the other shape
-    is the better one for this update (three states: 318 against 365 and 2250).  Groups of states on their own
-    streams win where a pass of one state does not fill the chip but its launches are long enough."""
+    Measured (sin^2 kinetic term, us per step).  The best plane or row/column schedule against split-x2, one
+    state / three: complex64 32: 15.8 -> 10.9 / 16.1 -> 11.7, 64: 20.9 -> 15.7 / 25.7 -> 21.4, 90: 42.5 -> 30.0 /
+    58.4 -> 44.7, 128: 44.9 -> 34.4 / 92.5 -> 67.6 (above 128 the row/column passes stay: the split-x2 factors
+    would change the FP32 results); complex128 64: 24.7 -> 17.4 / 31.9 -> 29.9, 128: 71.2 -> 45.9 / 187 -> 108,
+    160: 139 -> 105 / 417 -> 323, 240: 556 -> 478 / 1752 -> 1357, 256: 613 -> 510 / 1853 -> 1430, but 216: 368 ->
+    390 and 250: 622 -> 642 with one state.
+    The second tile shape against the first, complex128 (fewer plane groups and registers beside the psi that
+    this update also reads): 120 one state 65 -> 52 (three 114 -> 123), 160 three states 357 -> 323 (one 105
+    either way), 162 151 -> 121 / 474 -> 427, 192 250 -> 219 / 723 -> 640, 250 three states 2182 -> 1831; at the
+    other sizes that have one it is within 7% (80, one state: 29.2 -> 27.2) or slower (150 three states 316 -> 344).
+    Three groups of states against one stream, three states: complex64 80: 40.0 -> 34.3, 90: 49.6 -> 44.7, 96:
+    46.1 -> 43.7, 100: 52.7 -> 46.7, 120: 86.4 -> 66.5, 128: 78.2 -> 67.6, but 108: 58.0 -> 56.8 (no more than runs
+    differ) and below 80 slower (72: 30.4 -> 30.5, 64: 21.4 -> 27.8); complex128 90: 60.0 -> 52.6, 96: 61.9 -> 54.4,
+    100: 78.7 -> 69.9, 108: 94.0 -> 82.5, 120: 163 -> 114, 128: 120 -> 108, 160: 350 -> 323, but 80: 38.1 -> 39.8, 144:
+    230 -> 231, 150: 323 -> 335, 162: 427 -> 430, 192: 640 -> 652, 240: 1357 -> 1349."""
     if precision == 0:
         if N not in SPLIT_SMALL_SIZES + (96, 100, 108, 120, 128):
             return None
@@ -110,7 +117,7 @@ def ab_schedule(N: int, precision: int, k: int) -> Optional[dict]:
         if N not in SPLIT_C128_SIZES or (k == 1 and N in (216, 250)):
             return None
         groups = min(k, 3) if N in (90, 96, 100, 108, 120, 128, 160) else 1
-        variant = 1 if N in (160, 162, 192, 250) else 0
+        variant = 1 if N in (160, 162, 192, 250) or (N == 120 and k == 1) else 0
     return {"rowcol": False, "single_stream": groups == 1, "groups": groups, "split": True, "split_variant": variant}
 
 

@@ -104,3 +104,15 @@ def test_states_of_the_size_of_the_cache_run_on_one_stream(tmp_path, monkeypatch
         assert (s["groups"], s["single_stream"]) == (groups, groups == 1), (N, prec, k)
         assert s["split_variant"] == 0 and not s["rowcol"]
     A._cache = None
+
+
+def test_ab_rule_names_kernels_that_are_built():
+    built = built_variants()
+    for N in SIZES:
+        for prec in (0, 1):
+            for k in (1, 2, 3, 8):
+                e = A.ab_schedule(N, prec, k)
+                if e is not None:
+                    assert e["split_variant"] in built[N, prec] and 1 <= e["groups"] <= k
+    # the sizes and state counts whose second shape was measured to be the better one
+    assert [A.ab_schedule(120, 1, k)["split_variant"] for k in (1, 3)] == [1, 0]

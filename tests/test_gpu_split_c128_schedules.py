@@ -67,3 +67,18 @@ def test_default_schedule_of_several_states_matches_oracle(N, kind, vkind, k, ab
     E, psi = s.states()
     s.close()
     check(p, init, E, psi)
+
+
+@pytest.mark.parametrize("N,kind,k", [(120, S.K_NR_SIN2, 1), (162, S.K_REL, 2)])
+def test_default_ab_schedule_with_the_second_shape_matches_oracle(N, kind, k):
+    from paper_2211_10185_amd.solver import Solver
+    p = problem(N, kind, S.V_CORNELL, k, True, 3)
+    init = p.init_states()
+    s = Solver.from_problem(p)
+    print("complex128 A/B, N", N, "kind", kind, s.schedule, flush=True)
+    assert s.schedule["split"] and s.schedule["split_variant"] == 1
+    s.set_states(init)
+    s.evolve(p.steps, p.dt)
+    E, psi = s.states()
+    s.close()
+    check(p, init, E, psi)
