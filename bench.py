@@ -374,8 +374,8 @@ def bench_serve(args):
             "converged": int(sum(r.converged for r in out32["results"]))}
 
 
-KERNEL_SOURCES = ("common.h", "fft_core.h", "fft_passes.h", "fft_inst.hip", "split_passes.h", "split_inst.hip",
-                  "aux_kernels.hip")
+KERNEL_SOURCES = ("common.h", "kernel_table.h", "stencil_rows.h", "fft_core.h", "fft_passes.h", "fft_inst.hip",
+                  "split_passes.h", "split_inst.hip", "aux_kernels.hip")
 
 
 def source_hash():

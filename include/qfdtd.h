@@ -149,14 +149,15 @@ typedef struct {
                                      above N = 128). */
 /* Flag bits 7-8: the split-x2 variant (schedule autotuning), read as QFDTD_SPLIT_VARIANT(flags):
  *   0: the size's default factors x2 = N1 x N2 with its fastest tiles;
- *   1 (QFDTD_F_SPLIT_NARROW): the same factors with other tiles (mostly pencil tiles of fewer
- *      columns, so that two tiles share a compute unit);
+ *   1 (QFDTD_F_SPLIT_NARROW): the size's second tile shape (mostly pencil tiles of fewer columns, so
+ *      that two tiles share a compute unit); complex64: of the same factors and line plans;
  *   2 (QFDTD_F_SPLIT_WIDE), N = 128 and 256: 8 consecutive rows per pencil tile and 8 columns
  *      (row pieces twice as long as with 4 columns);
  *   3 (QFDTD_F_SPLIT_SWAPPED): the default factors swapped, x2 = N2 x N1 (fewer rows per slab
  *      tile, more per pencil tile), at the sizes where they differ.
  * Complex128 has variant 0 and, at some sizes, 1; complex64 below N = 96 has variant 0, with the
- * operations of the plane passes (the same bits).  Tiles do not change results, factors do (rounding).
+ * operations of the plane passes (the same bits).  Complex64 variants 0 and 1 give the same bits; other
+ * factors or line plans, which complex128 variant 1 has at most sizes, change the rounding.
  * A variant a size does not have runs the schedule the other flags select. */
 #define QFDTD_F_SPLIT_NARROW 128u
 #define QFDTD_F_SPLIT_WIDE 256u

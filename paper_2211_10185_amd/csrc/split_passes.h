@@ -570,9 +570,10 @@ __device__ __forceinline__ void pencil_body(const LaunchList &L, int e, int t, u
 // so the transform's last stage feeds the sum and its output is never written; the slab pass reads the
 // state as it is stored (complex64 or complex128), adds up |psi|^2 and V |psi|^2 on the way, and leaves
 // x3 and the slab part of x2 transformed in scratch64.  40 B per site and state (complex64) instead of
-// the 152 B of a copy, three transform passes and two sums.  128^3 x 3 states: slab pass 44 us, pencil
-// pass 25 us, with the final sums 73 us for a readout that took 203; 256^3 x 3 states with complex V: 438
-// and 555 us of 1.68 ms before.  Bound by the slab pass's natural-order loads and by HBM.
+// the 152 B of a copy, three transform passes and two sums.  128^3 x 3 states: slab pass 45 us, pencil
+// pass 25 us, with the final sums 75 us for a readout that took 203; 256^3 x 3 states with complex V: 432
+// and 358 us of 1.68 ms before.  Bound by the slab pass's natural-order loads and by HBM; its tiles are taken
+// state by state, so V is read once per state.
 
 // Fixed-order block sums of NV values per thread: wave shuffles, then the waves in order.  Thread 0
 // returns with the sums in acc.
@@ -752,8 +753,9 @@ __device__ __forceinline__ void pencil_meas_body(const PassDesc &d, int t, unsig
 // (other two-stage plans moved them by 1e-6).  So the plans are make_rplan's, with adjacent stages
 // fused in registers where that is faster, and up to N = 90 the factors are those of the plane pass
 // (see split_row).  The rest, and all of a complex128 shape, was found by timing: plane groups,
-// columns, threads, fused stages (complex128: factors up to 18 and two-stage plans), each slab kernel
-// in turn with the pencil kernels of the same factors, with one and three states on an MI355X.  (In
+// columns, threads, fused stages (complex128: factors up to 25, line plans of two stages and, at 162, 200
+// and 250, of three), each slab kernel in turn with the pencil kernels of the same factors, with one and
+// three states on an MI355X.  (In
 // turn, because at small N a pass run by itself finds in its XCD's L2 what it has just written there:
 // 128^3, one state, 21 us for the two passes by themselves and 30 us in turn.)  What decides:
 //   - an LDS exchange less per direction: 240^3, one complex64 state, 16 x (3 x 5) against 16 x 3 x 5:
@@ -761,7 +763,10 @@ __device__ __forceinline__ void pencil_meas_body(const PassDesc &d, int t, unsig
 //   - the passes are bound by latency, so registers decide: at most 128 leave four waves per SIMD;
 //   - pencil pieces of 32 bytes and more (XI TT >= 4 in complex64, >= 2 in complex128): the L1 is
 //     bound by requests below that; 64 bytes where the LDS holds the tile (256^3, complex128, one / three
-//     states: 420 / 1169 -> 330 / 925 us per step; one pencil tile of 157 KB per CU);
+//     states: 420 / 1169 -> 330 / 925 us per step; one pencil tile of 157 KB per CU).  The complex64
+//     defaults at 40, 48, 50, 54, 90, 150, 162 and 250 have pieces of 16 bytes all the same: of 1, 2, 4 and 8
+//     columns only 1 and 2 divide 50, 54, 90, 150, 162 and 250, and there plane pairs were slower (150^3,
+//     one state, 58.1 -> 61.6 us per step);
 //   - at small N more, smaller tiles: one per (plane, row digit) with 64 to 256 threads;
 //   - a complex factor takes twice the registers of a real one in the slab pass's middle stage.  Where that
 //     goes past the 256 of a lane or costs a wave per SIMD the kernel has threads (and fused stages) of its
@@ -769,11 +774,12 @@ __device__ __forceinline__ void pencil_meas_body(const PassDesc &d, int t, unsig
 //     threads of the real factor -> its own): complex64 150^3 59 / 124 -> 57 / 121, 180^3 131 / 275 -> 92 /
 //     194, 192^3 94 / 211 -> 85 / 187, 216^3 three states 460 -> 383, complex128 216^3 315 / 816 -> 284 / 729.
 // Variants:
-//   0: the fastest for three states;  1: complex64 from 96 up: the fastest other shape of the same
-//   factors (complex128: the fastest for one state or for the A/B
-//   update, where that is another);  2: 8 consecutive rows per
-//   pencil tile and 8 columns;  3: the factors swapped;  4 (not selectable by flags): the A/B update
-//   of complex64 up to N = 128, with the factors of the plane pass.
+//   0: the fastest for three states with a real potential when the shapes were searched (at 162 in
+//   complex128 the second one is, in the solver: 250.7 against 254.3 us per step);  1: complex64 from 96
+//   up: the fastest other shape of the same factors and line plans; complex128: the fastest for one state
+//   or for the A/B update where that is another shape, with factors or plans of its own at most sizes;
+//   2: 8 consecutive rows per pencil tile and 8 columns;  3: the factors swapped;  4 (not selectable by
+//   flags): the A/B update of complex64 up to N = 128, with the factors of the plane pass.
 struct SplitDef {
   int N, dbl, v, N1, XI, TT, slab_nt, slab_plan, pencil_nt, pencil_plan;
   bool pencil_hx = false;
