@@ -121,6 +121,14 @@ def ab_schedule(N: int, precision: int, k: int) -> Optional[dict]:
     return {"rowcol": False, "single_stream": groups == 1, "groups": groups, "split": True, "split_variant": variant}
 
 
+def ab_schedule_for(N: int, precision: int, k: int, tuned: dict) -> dict:
+    """Schedule of the A/B update beside the cache's choice for the split step: its own rule where it has
+    split-x2 kernels, else plane or row/column passes on one stream.  A cache that asks for row and column
+    passes in complex64 gets them: they round in another order than the plane passes."""
+    ab = None if precision == 0 and tuned["rowcol"] else ab_schedule(N, precision, k)
+    return ab or dict(tuned, split=False)
+
+
 def candidates(N: int, precision: int, k: int):
     out = []
     plane_ok = N <= PLANE_LIMIT[precision]

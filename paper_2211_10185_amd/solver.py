@@ -101,13 +101,10 @@ class Solver:
         if groups is not None:
             single_stream = int(groups) <= 1
         if single_stream is None or rowcol is None or groups is None or split is None:
-            from .autotune import ab_schedule, schedule_for, single_shape_split
+            from .autotune import ab_schedule_for, schedule_for, single_shape_split
             tuned = schedule_for(self.N, self.kinetic, self.precision, self.k)
             if int(scheme) == 1 and self.kinetic != FDTD and split is None:
-                # the A/B update: its own rule where it has split-x2 kernels, else plane or
-                # row/column passes on one stream
-                ab = ab_schedule(self.N, self.precision, self.k) if rowcol is None else None
-                tuned = ab or dict(tuned, split=False)
+                tuned = dict(tuned, split=False) if rowcol is not None else ab_schedule_for(self.N, self.precision, self.k, tuned)
             if split is None and rowcol is not None and single_shape_split(self.N, self.precision):
                 split = False       # plane or row/column passes were asked for
             single_stream = tuned["single_stream"] if single_stream is None else single_stream

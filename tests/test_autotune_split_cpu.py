@@ -116,3 +116,12 @@ def test_ab_rule_names_kernels_that_are_built():
                     assert e["split_variant"] in built[N, prec] and 1 <= e["groups"] <= k
     # the sizes and state counts whose second shape was measured to be the better one
     assert [A.ab_schedule(120, 1, k)["split_variant"] for k in (1, 3)] == [1, 0]
+
+
+def test_ab_update_keeps_row_and_column_passes_that_a_complex64_cache_asks_for():
+    plane = {"rowcol": False, "single_stream": True, "groups": 1, "split": False, "split_variant": 0}
+    rowcol = dict(plane, rowcol=True)
+    assert A.ab_schedule_for(64, 0, 1, rowcol) == rowcol
+    assert A.ab_schedule_for(64, 0, 1, plane) == A.ab_schedule(64, 0, 1)
+    assert A.ab_schedule_for(100, 1, 1, rowcol) == A.ab_schedule(100, 1, 1)      # complex128: faster, within 1e-14
+    assert A.ab_schedule_for(160, 0, 3, dict(plane, split=True)) == plane        # no split-x2 kernels: as before
